@@ -67,15 +67,16 @@ __global__ __launch_bounds__(kTraceBlock) void k_batch_trace(const BatchScene *s
                                                              const bvh_ray *rays, bvh_hit *hits,
                                                              Fallback fb, SpillArea sa) {
     using Tr = typename TracerFor<Layout>::type;
-    __shared__ uint32_t s_ref[SL * kTraceBlock];
-    __shared__ float s_t[(Tr::kWithT ? SL : 1) * kTraceBlock];
+    __shared__ typename Tr::Entry s_stack[SL * kTraceBlock];
+    __shared__ WaveLeafLds s_wl[kWavesPerBlock];
+    WaveLeafLds *wl = &s_wl[threadIdx.x >> 6];
     const uint32_t lane = threadIdx.x & 63u;
-    SpillStack<Tr::kWithT, SL> st(s_ref, s_t, sa);
+    RingStack<typename Tr::Entry, SL> st(s_stack, sa);
     // per lane
     uint32_t ray = kNoRay;  // ray index within the launch's ray array
     Ray r{};
     typename Tr::Prep prep{};
-    typename Tr::State ts = Tr::start(0);
+    typename Tr::State ts = Tr::none();
     uint32_t nf = 0, nt = 0;
     bool incomplete = false;
     // wave-uniform
@@ -83,6 +84,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_batch_trace(const BatchScene *s
     uint64_t pool = 0, pool_end = 0;
     uint32_t pending = kNoTile;  // claimed tile of another scene
     bool drained = false;
+    bool coherent = true, fast = true;  // of the wave's rays at its last refill
     SceneData sd{};
     const void *nodes = nullptr;
     int64_t n_nodes = 0;
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_batch_trace(const BatchScene *s
                     ray = (uint32_t)(pool + rank);
                     r = load_ray(rays, ray, sd.coord_max);
                     prep = Tr::prep(r);
-                    ts = Tr::start(n_nodes);
+                    ts = Tr::start(n_nodes, r);
                     st.reset();
                     nf = nt = 0;
                     incomplete = false;
@@ -140,17 +142,14 @@ __global__ __launch_bounds__(kTraceBlock) void k_batch_trace(const BatchScene *s
             if (drained && pending == kNoTile && pool == pool_end) break;
             continue;
         }
-        const bool coherent = rays_share_octant(r, ray != kNoRay, busy);
+        if (nidle >= kBatchRefill) {
+            coherent = rays_share_octant(r, ray != kNoRay, busy);
+            fast = __builtin_amdgcn_ballot_w64(ray != kNoRay && !r.fast) == 0;
+        }
+        Tr::template wave<BVH_LEAF_COMPACT, BVH_TRACE_CLOSEST>(nodes, n_nodes, sd, r, prep, fast,
+                                                               coherent, st, ts, wl, nf, nt,
+                                                               incomplete);
         if (ray != kNoRay) {
-            const bool fast = wave_fast(r);
-            if (coherent)
-                Tr::template round<BVH_LEAF_COMPACT, BVH_TRACE_CLOSEST>(nodes, n_nodes, sd, r, prep,
-                                                                        fast, st, ts, nf, nt,
-                                                                        incomplete);
-            else
-                Tr::template step<BVH_LEAF_COMPACT, BVH_TRACE_CLOSEST>(nodes, n_nodes, sd, r, prep,
-                                                                       fast, st, ts, nf, nt,
-                                                                       incomplete);
             if (Tr::done(ts)) {
                 if (incomplete) fallback_append(fb, ray);
                 else store_hit(hits, ray, ts.best);
@@ -184,8 +183,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_batch_fallback(const BatchScene
                                {sc.ft[0], sc.ft[1], sc.ft[2]}, sc.topo};
         uint32_t nf = 0, nt = 0;
         bool incomplete = false;
-        GlobalStack<TracerFor<Layout>::type::kWithT> st(fb.stack_ref + (size_t)lane * kStackMax,
-                                                        fb.stack_t + (size_t)lane * kStackMax);
+        GlobalStack<typename TracerFor<Layout>::type::Entry> st(fb.stack + (size_t)lane * kStackMax);
         const Best b = trace_ray<Layout, BVH_LEAF_COMPACT, BVH_TRACE_CLOSEST>(
             sc.nodes, sc.n_nodes, ld, r, st, nf, nt, incomplete);
         store_hit(hits, i, b);
@@ -549,7 +547,7 @@ int32_t make_graph(bvh_batch_s *b, const bvh_ray *rays, const int64_t *offsets, 
             b->g_mem.push_back(spill);
         }
         SpillArea sa;
-        sa.ent = static_cast<uint2 *>(spill);
+        sa.ent = static_cast<uint64_t *>(spill);
         sa.lanes = lanes;
         sa.cap = kBatchSpillCap;
         void *args[] = {&d_sc, &d_toff, &nsc, (void *)&total, &ctr, &r, &hh, &fb, &sa};

@@ -8,35 +8,6 @@
 namespace bvhlib {
 namespace {
 
-// One ray per lane, LDS stack of SL entries.  A ray whose stack would
-// overflow is appended to the fallback list instead of writing a hit.
-template <int Layout, int LeafMode, int Mode, bool Count, int SL>
-__global__ __launch_bounds__(kTraceBlock) void k_trace(const void *nodes, int64_t n_nodes,
-                                                       SceneData ld, const bvh_ray *rays,
-                                                       uint64_t n, bvh_hit *hits,
-                                                       uint32_t *counts, Fallback fb) {
-    using Tr = typename TracerFor<Layout>::type;
-    __shared__ uint32_t s_ref[SL * kTraceBlock];
-    __shared__ float s_t[(Tr::kWithT ? SL : 1) * kTraceBlock];
-    const uint64_t i = (uint64_t)blockIdx.x * kTraceBlock + threadIdx.x;
-    if (i >= n) return;
-    const Ray r = load_ray(rays, i, ld.coord_max);
-    uint32_t nfetch = 0, ntri = 0;
-    bool incomplete = false;
-    LdsStack<Tr::kWithT, SL> st(s_ref, s_t);
-    const Best best =
-        trace_ray<Layout, LeafMode, Mode>(nodes, n_nodes, ld, r, st, nfetch, ntri, incomplete);
-    if (incomplete) {
-        fallback_append(fb, (uint32_t)i);
-        return;
-    }
-    store_hit(hits, i, best);
-    if (Count) {
-        counts[2 * i] = nfetch;
-        counts[2 * i + 1] = ntri;
-    }
-}
-
 // Persistent kernel: the grid holds as many blocks as fit on the GPU at
 // once, and every lane traces ray after ray.  A lane whose ray ends is
 // refilled from its wave's pool of claimed rays once enough lanes of the
@@ -62,15 +33,14 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
                                                                uint32_t *counts, Fallback fb,
                                                                SpillArea sa) {
     using Tr = typename TracerFor<Layout>::type;
-    __shared__ uint32_t s_ref[SL * kTraceBlock];
-    __shared__ float s_t[(Tr::kWithT ? SL : 1) * kTraceBlock];
-    __shared__ WaveLeafLds s_wl[Tr::kBatchLeaves ? kWavesPerBlock : 1];
-    WaveLeafLds *wl = &s_wl[Tr::kBatchLeaves ? (threadIdx.x >> 6) : 0];
-    SpillStack<Tr::kWithT, SL> st(s_ref, s_t, sa);
+    __shared__ typename Tr::Entry s_stack[SL * kTraceBlock];
+    __shared__ WaveLeafLds s_wl[kWavesPerBlock];
+    WaveLeafLds *wl = &s_wl[threadIdx.x >> 6];
+    RingStack<typename Tr::Entry, SL> st(s_stack, sa);
     uint32_t ray = kNoRay;
     Ray r{};
     typename Tr::Prep prep{};
-    typename Tr::State ts = Tr::start(0);
+    typename Tr::State ts = Tr::none();
     uint32_t nfetch = 0, ntri = 0;
     bool incomplete = false;
     // wave-uniform: the wave's pool of claimed rays [pool, pool_end), and
@@ -84,7 +54,8 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
     const uint64_t static_end = static_rounds * waves * kClaim;
     uint64_t round = 0;  // static chunks taken by this wave
     uint32_t queue = wave % kQueues;  // the wave's current dynamic queue (wave-uniform)
-    bool coherent = true;  // the wave's last rays all pointed into one octant
+    bool coherent = true;  // the wave's rays at its last refill all pointed into one octant
+    bool fast = true;      // and can all use the one-FMA slab distances
     for (;;) {
         const uint64_t idle = __builtin_amdgcn_ballot_w64(ray == kNoRay);
         const uint32_t nidle = (uint32_t)__builtin_popcountll(idle);
@@ -114,7 +85,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
                     ray = (uint32_t)my;
                     r = load_ray(rays, my, ld.coord_max);
                     prep = Tr::prep(r);
-                    ts = Tr::start(n_nodes);
+                    ts = Tr::start(n_nodes, r);
                     st.reset();
                     nfetch = ntri = 0;
                     incomplete = false;
@@ -129,26 +100,19 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
             } else {
                 pool = pool_end;
             }
+            const uint64_t busy = __builtin_amdgcn_ballot_w64(ray != kNoRay);
+            if (busy == 0) {
+                if (drained && pool == pool_end) break;
+                continue;
+            }
+            // by every lane (converged), so the values stay wave-uniform
+            coherent = rays_share_octant(r, ray != kNoRay, busy);
+            fast = __builtin_amdgcn_ballot_w64(ray != kNoRay && !r.fast) == 0;
+        } else if (nidle == 64u) {
+            break;
         }
-        const uint64_t busy = __builtin_amdgcn_ballot_w64(ray != kNoRay);
-        if (busy == 0) {
-            if (drained && pool == pool_end) break;
-            continue;
-        }
-        // computed by every lane (converged), so the values stay wave-uniform
-        coherent = rays_share_octant(r, ray != kNoRay, busy);
-        const bool fast = __builtin_amdgcn_ballot_w64(ray != kNoRay && !r.fast) == 0;
-        if (coherent) {
-            if (ray != kNoRay)
-                Tr::template round<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, ts,
-                                                   nfetch, ntri, incomplete);
-        } else if constexpr (Tr::kBatchLeaves) {
-            Tr::template round_wave<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, ts,
-                                                    ray != kNoRay, wl, nfetch, ntri, incomplete);
-        } else if (ray != kNoRay) {
-            Tr::template step<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, ts, nfetch,
-                                              ntri, incomplete);
-        }
+        Tr::template wave<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, coherent, st, ts, wl,
+                                          nfetch, ntri, incomplete);
         if (ray != kNoRay) {
             if (Tr::done(ts)) {
                 if (incomplete) {
@@ -183,8 +147,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_fallback(const void *node
         const Ray r = load_ray(rays, i, ld.coord_max);
         uint32_t nfetch = 0, ntri = 0;
         bool incomplete = false;
-        GlobalStack<Tr::kWithT> st(fb.stack_ref + (size_t)lane * kStackMax,
-                                   fb.stack_t + (size_t)lane * kStackMax);
+        GlobalStack<typename Tr::Entry> st(fb.stack + (size_t)lane * kStackMax);
         const Best best =
             trace_ray<Layout, LeafMode, Mode>(nodes, n_nodes, ld, r, st, nfetch, ntri, incomplete);
         store_hit(hits, i, best);
@@ -231,9 +194,9 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_slab(const bvh_node_slab 
                 lo[k] = (uint32_t)k == sa ? nd.slo : lo[k];
                 hi[k] = (uint32_t)k == sa ? nd.shi : hi[k];
             }
-            const float tcur = best_bound<Mode>(r, best);
-            const float tn = r.fast ? slab<true>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], tcur)
-                                    : slab<false>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], tcur);
+            const float cull = cull_bound<Mode>(r, best);
+            const float tn = r.fast ? slab<true>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], cull)
+                                    : slab<false>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], cull);
             if (tn == INFINITY) {
                 cur = kRefEmpty;
                 continue;
@@ -274,8 +237,6 @@ int32_t launch_slab(const bvh_handle_s *h, const SceneData &ld, const bvh_ray *r
     return BVH_OK;
 }
 
-constexpr bool kPersistent = true;
-
 // Fallback grid of a launch that brings its own (fixed-size) work area.
 constexpr int kFixedFallbackBlocks = 16;
 
@@ -288,38 +249,28 @@ constexpr size_t kNoAllocScratchBytes =
     fallback_bytes(kNoAllocMaxRays, (size_t)kFixedFallbackBlocks * kTraceBlock);
 static_assert(kNoAllocMaxRays == BVH_NOALLOC_MAX_RAYS, "bvh.h states the limit");
 
-// fixed: when non-null, the launch uses this work area: one ray per lane with
-// the LDS stack only, overflowing rays re-traced by a fallback grid of
-// kFixedFallbackBlocks blocks.  Otherwise the area comes
-// from the stream's grow-only work area and the persistent kernel runs.
+// fixed: when non-null, the launch uses this work area: rays that outgrow
+// the LDS ring are re-traced by a fallback grid of kFixedFallbackBlocks
+// blocks.  Otherwise the area, with a spill run per lane, comes from the
+// stream's grow-only work area.
 template <int Layout, int LeafMode, int Mode, bool Count, int SL>
 int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_ray *rays, uint64_t n,
                       bvh_hit *hits, uint32_t *counts, const Fallback *fixed, hipStream_t s) {
     const uint64_t need = (n + kTraceBlock - 1) / kTraceBlock;
-    if (fixed) {
-        k_trace<Layout, LeafMode, Mode, Count, SL><<<(unsigned)need, kTraceBlock, 0, s>>>(
-            h->nodes, h->n_nodes, ld, rays, n, hits, counts, *fixed);
-        k_trace_fallback<Layout, LeafMode, Mode, Count>
-            <<<kFixedFallbackBlocks, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, rays, hits,
-                                                           counts, *fixed);
-        return BVH_OK;
-    }
+    auto kernel = k_trace_persist<Layout, LeafMode, Mode, Count, SL>;
+    unsigned resident = 0;
+    BVH_TRY(resident_blocks(kernel, resident));
+    const unsigned grid = (unsigned)std::min<uint64_t>(resident, need);
     TraceArea ta;
-    if (kPersistent) {
-        auto kernel = k_trace_persist<Layout, LeafMode, Mode, Count, SL>;
-        unsigned resident = 0;
-        BVH_TRY(resident_blocks(kernel, resident));
-        const unsigned grid = (unsigned)std::min<uint64_t>(resident, need);
+    if (fixed)
+        ta = TraceArea{*fixed, SpillArea{nullptr, grid * kTraceBlock, 0}};
+    else
         BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
-        kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, rays, n, hits, counts, ta.fb,
-                                            ta.sa);
-    } else {
-        BVH_TRY(trace_area(s, n, 0, ta));
-        k_trace<Layout, LeafMode, Mode, Count, SL><<<(unsigned)need, kTraceBlock, 0, s>>>(
-            h->nodes, h->n_nodes, ld, rays, n, hits, counts, ta.fb);
-    }
-    k_trace_fallback<Layout, LeafMode, Mode, Count><<<kFallbackBlocks, kTraceBlock, 0, s>>>(
-        h->nodes, h->n_nodes, ld, rays, hits, counts, ta.fb);
+    kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, rays, n, hits, counts, ta.fb,
+                                        ta.sa);
+    k_trace_fallback<Layout, LeafMode, Mode, Count>
+        <<<fixed ? kFixedFallbackBlocks : kFallbackBlocks, kTraceBlock, 0, s>>>(
+            h->nodes, h->n_nodes, ld, rays, hits, counts, ta.fb);
     return BVH_OK;
 }
 
@@ -482,7 +433,7 @@ extern "C" int32_t bvh_trace_noalloc(bvh_handle_t h, const bvh_ray *rays, int64_
     void *ptr = nullptr;
     BVH_TRY(scratch_address(h->device, &ptr));
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const Fallback fb = fallback_view(ptr, (uint64_t)n, (size_t)kFixedFallbackBlocks * kTraceBlock);
+    const Fallback fb = fallback_view(ptr, (uint64_t)n);
     k_zero_words<<<1, kTraceBlock, 0, s>>>(static_cast<uint32_t *>(ptr),
                                             (uint32_t)(kFallbackHeaderBytes / 4));
     return launch<false>(h, rays, (uint64_t)n, hits, mode, nullptr, s, &fb);

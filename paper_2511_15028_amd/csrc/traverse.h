@@ -98,13 +98,6 @@ __device__ inline bool rays_share_octant(const Ray &r, bool has, uint64_t mask) 
     return (nx == 0 || nx == mask) && (ny == 0 || ny == mask) && (nz == 0 || nz == mask);
 }
 
-// True when the active lanes' rays all point into the same octant (a cheap
-// wave-uniform coherence test: camera rays of neighbouring pixels pass it,
-// scattered secondary rays do not).
-__device__ inline bool wave_coherent(const Ray &r) {
-    return rays_share_octant(r, true, __builtin_amdgcn_ballot_w64(true));
-}
-
 // Ray/box test (the slab method of Kay and Kajiya; the paper's traversal
 // tests node boxes with it, App. G) on planes already ordered by the ray:
 // (nx, ny, nz) are the planes the ray enters through (the lower plane of an
@@ -119,10 +112,10 @@ __device__ inline bool wave_coherent(const Ray &r) {
 // (plane - o) * rdir by more than one rounding and the exit distance never
 // falls short of it by more than one rounding.  Either way the relative
 // error of each distance against the exact (plane - o) / d stays below the
-// far-distance widening, so no box that the ray meets before tcur is culled.
+// far-distance widening, so no box that the ray meets before the best hit is culled.
 template <bool Fast>
 __device__ inline float slab_nf(const Ray &r, float nx, float ny, float nz, float fx, float fy,
-                                float fz, float tcur) {
+                                float fz, float cull) {
     float tnx, tny, tnz, tfx, tfy, tfz;
     if (Fast) {
         tnx = fmaf(nx, r.rx, r.knx); tfx = fmaf(fx, r.rx, r.kfx);
@@ -134,17 +127,17 @@ __device__ inline float slab_nf(const Ray &r, float nx, float ny, float nz, floa
         tnz = (nz - r.oz) * r.rz; tfz = (fz - r.oz) * r.rz;
     }
     const float t_near = fmaxf(0.0f, fmaxf(tnx, fmaxf(tny, tnz)));
-    const float t_far = fminf(tcur, fminf(tfx, fminf(tfy, tfz)));
-    return (t_near <= t_far * kFarScale) ? t_near : INFINITY;
+    const float t_far = fminf(tfx, fminf(tfy, tfz)) * kFarScale;
+    return (t_near <= fminf(cull, t_far)) ? t_near : INFINITY;
 }
 
 // The same test on a box given as (lo, hi): the entry and exit planes are
 // chosen by the sign bit of each direction component.
 template <bool Fast>
 __device__ inline float slab(const Ray &r, float lox, float loy, float loz, float hix, float hiy,
-                             float hiz, float tcur) {
+                             float hiz, float cull) {
     return slab_nf<Fast>(r, r.nx ? hix : lox, r.ny ? hiy : loy, r.nz ? hiz : loz,
-                         r.nx ? lox : hix, r.ny ? loy : hiy, r.nz ? loz : hiz, tcur);
+                         r.nx ? lox : hix, r.ny ? loy : hiy, r.nz ? loz : hiz, cull);
 }
 
 // Ray/triangle test: Moller and Trumbore (1997), with App. G's acceptance
@@ -415,112 +408,109 @@ __device__ inline bool wave_test_leaves(const SceneData &ld, const Ray &r, bool 
 }
 
 // ---------------------------------------------------------------------------
-// Traversal stacks.  The fast path keeps SL entries per lane in LDS (one
-// column per lane, so lanes never share a bank) and has no overflow area: a
-// push beyond SL fails, the ray stops and is re-traced by the fallback pass,
-// which keeps a deep stack (kStackMax entries, the build's bound) in a
-// global-memory workspace.  No private (scratch) memory is used.
+// Traversal stacks.  An entry is a node reference (E = uint32_t, binary
+// layouts) or a reference with its entry distance (E = uint64_t: the distance's
+// bits in the upper word, so that entries compare like their distances, which
+// are never negative).  A node visit makes room for its children once, then
+// puts them: put() always writes the slot at the top and moves the top only
+// when the entry is kept, so the put itself has no branch.  It therefore needs
+// room for at least one entry even where it keeps none.
+//   reset()       empties the stack
+//   room(n)       n >= 1 entries fit (moving older ones away if need be);
+//                 false: the ray is re-traced by the fallback pass
+//   put(e, keep)  writes e at the top
+//   take()        takes the top entry; kBottom when the stack is empty
+// The top is kept in bytes of LDS, so that a slot's address is one VALU
+// operation.
 // ---------------------------------------------------------------------------
-template <bool WithT, int SL>
-struct LdsStack {
-    uint32_t *lds_ref;  // [SL][kTraceBlock]
-    float *lds_t;
-    uint32_t sp = 0;
-    __device__ LdsStack(uint32_t *r, float *t) : lds_ref(r), lds_t(t) {}
-    __device__ bool push(uint32_t ref, float t) {
-        if (sp >= (uint32_t)SL) return false;
-        const uint32_t slot = sp * kTraceBlock + threadIdx.x;
-        lds_ref[slot] = ref;
-        if (WithT) lds_t[slot] = t;
-        sp++;
-        return true;
-    }
-    __device__ uint32_t pop(float &t) {
-        sp--;
-        const uint32_t slot = sp * kTraceBlock + threadIdx.x;
-        t = WithT ? lds_t[slot] : 0.0f;
-        return lds_ref[slot];
-    }
-};
+// kRefDone: no reference of a tree, and like a leaf's its low bit is 0, so
+// that one bit tells whether a lane has an interior node to visit.
+constexpr uint32_t kRefDone = 0xFFFFFFFEu;
+// What an empty stack gives: no reference; with a distance, one that no bound
+// culls (-inf).
+template <typename E>
+inline constexpr E kBottom = kRefEmpty;
+template <>
+inline constexpr uint64_t kBottom<uint64_t> = (uint64_t)0xFF800000u << 32 | kRefDone;
 
-// Deep stack of one lane in global memory: ref[kStackMax], t[kStackMax].
-template <bool WithT>
+// Deep stack of one lane in global memory: kStackMax entries, the build's
+// bound on what a ray can need.
+template <typename E>
 struct GlobalStack {
-    uint32_t *ref;
-    float *tt;
+    uint64_t *ent;  // [kStackMax]
     uint32_t sp = 0;
-    __device__ GlobalStack(uint32_t *r, float *t) : ref(r), tt(t) {}
-    __device__ bool push(uint32_t r, float t) {
-        if (sp >= (uint32_t)kStackMax) return false;  // the build bounds the depth by kStackMax
-        ref[sp] = r;
-        if (WithT) tt[sp] = t;
-        sp++;
-        return true;
+    __device__ explicit GlobalStack(uint64_t *e) : ent(e) {}
+    __device__ void reset() { sp = 0; }
+    __device__ bool room(uint32_t) { return true; }
+    __device__ void put(E e, bool keep) {
+        if (keep && sp < (uint32_t)kStackMax) ent[sp++] = e;
     }
-    __device__ uint32_t pop(float &t) {
-        sp--;
-        t = WithT ? tt[sp] : 0.0f;
-        return ref[sp];
-    }
+    __device__ E take() { return sp > 0 ? (E)ent[--sp] : kBottom<E>; }
 };
 
 // Stack of one lane of a persistent kernel: a ring of SL entries in LDS
-// (one column per lane) over a spill area in global memory that belongs to
-// the lane for the whole launch.  When the ring is full, a push first moves
-// its oldest half to the spill area; when it is empty, a pop first brings the
-// newest spilled half back.  Entries [0, lo) live in the spill area, entries
-// [lo, sp) in the ring (entry e in slot e mod SL).  A push fails only when
-// the spill area (cap entries) is full.  A lane's spill entries are
-// contiguous (reference and entry distance side by side), so moving half a
-// ring writes or reads one run of SL/2 * 8 bytes (a 64-byte line for SL = 16)
+// (one column per lane, so lanes never share a bank) over a spill area in
+// global memory that belongs to the lane for the whole launch (a cap of 0
+// leaves the ring alone).  No private (scratch) memory is used.  Where the ring lacks room, its oldest half
+// (or all it holds, if less) moves to the spill area; when it is empty, a pop
+// first brings the newest half of the spilled entries back.  Entries [0, lo) live in the spill area, entries
+// [lo, sp) in the ring.  room() fails only when the spill area (cap entries)
+// is full.  A lane's spill entries are contiguous, so moving half a ring
+// writes or reads one run (a 64-byte line for SL = 16 and 8-byte entries)
 // instead of SL scattered words.
 struct SpillArea {
-    uint2 *ent;       // [lanes][cap]: (reference, entry-distance bits)
+    uint64_t *ent;    // [lanes][cap] entries of at most 8 bytes
     uint32_t lanes;   // lanes of the launch (the grid's threads)
-    uint32_t cap;     // spill entries per lane (a multiple of SL / 2)
+    uint32_t cap;     // spill entries per lane
 };
 
-template <bool WithT, int SL>
-struct SpillStack {
-    static_assert((SL & (SL - 1)) == 0 && SL >= 2, "ring size must be a power of two");
-    uint32_t *lds_ref;  // [SL][kTraceBlock]
-    float *lds_t;       // [SL][kTraceBlock] when WithT
-    SpillArea area;     // uniform across the launch
+template <typename E, int SL>
+struct RingStack {
+    static_assert((SL & (SL - 1)) == 0 && SL >= 2 && SL <= 32, "ring size must be a power of two");
+    static constexpr uint32_t kStep = kTraceBlock * sizeof(E);
+    static constexpr uint32_t kHalf = (SL / 2) * kStep;
+    E *lds;               // [SL][kTraceBlock]
+    SpillArea area;       // uniform across the launch
     uint32_t sp = 0, lo = 0;
-    __device__ SpillStack(uint32_t *r, float *t, const SpillArea &a) : lds_ref(r), lds_t(t), area(a) {}
-    __device__ void reset() { sp = lo = 0; }
-    __device__ static uint32_t slot(uint32_t e) { return (e & (SL - 1)) * kTraceBlock + threadIdx.x; }
-    // entry e of this lane's spill run (the lane's index in the grid)
-    __device__ size_t spill_index(uint32_t e) const {
-        return ((size_t)blockIdx.x * kTraceBlock + threadIdx.x) * area.cap + e;
+    __device__ RingStack(E *l, const SpillArea &a) : lds(l), area(a) {}
+    __device__ E &slot(uint32_t at) const {
+        return *reinterpret_cast<E *>(reinterpret_cast<char *>(lds) +
+                                      ((at & ((SL - 1) * kStep)) | (threadIdx.x * (uint32_t)sizeof(E))));
     }
-    __device__ bool push(uint32_t ref, float t) {
-        if (sp - lo == (uint32_t)SL) {
-            constexpr uint32_t H = SL / 2;
-            if (lo + H > area.cap) return false;
-            for (uint32_t e = lo; e < lo + H; e++)
-                area.ent[spill_index(e)] =
-                    make_uint2(lds_ref[slot(e)], WithT ? __float_as_uint(lds_t[slot(e)]) : 0u);
-            lo += H;
+    __device__ void reset() { sp = lo = 0; }
+    // the lane's spill run (the lane's index in the grid), as entries of type E
+    __device__ E *run() const {
+        return reinterpret_cast<E *>(area.ent + ((size_t)blockIdx.x * kTraceBlock + threadIdx.x) * area.cap);
+    }
+    __device__ bool room(uint32_t n) {
+        while (sp - lo + n * kStep > SL * kStep) {
+            const uint32_t m = min(kHalf, sp - lo);
+            if (lo + m > area.cap * kStep) return false;
+            E *to = run() + lo / kStep;
+            for (uint32_t e = 0; e < m; e += kStep) to[e / kStep] = slot(lo + e);
+            lo += m;
         }
-        lds_ref[slot(sp)] = ref;
-        if (WithT) lds_t[slot(sp)] = t;
-        sp++;
         return true;
     }
-    __device__ uint32_t pop(float &t) {  // requires sp > 0
-        if (sp == lo) {
-            const uint32_t n = lo < (uint32_t)(SL / 2) ? lo : (uint32_t)(SL / 2);
-            for (uint32_t e = lo - n; e < lo; e++) {
-                const uint2 x = area.ent[spill_index(e)];
-                lds_ref[slot(e)] = x.x;
-                if (WithT) lds_t[slot(e)] = __uint_as_float(x.y);
-            }
-            lo -= n;
+    __device__ void put(E e, bool keep) {
+        slot(sp) = e;
+        sp += keep ? kStep : 0u;
+    }
+    __device__ E take() {
+        if (sp == lo) refill();
+        sp -= kStep;
+        return slot(sp);
+    }
+    // the ring is empty: brings spilled entries back, or puts kBottom
+    __device__ void refill() {
+        if (lo == 0) {
+            put(kBottom<E>, true);
+            return;
         }
-        sp--;
-        t = WithT ? lds_t[slot(sp)] : 0.0f;
-        return lds_ref[slot(sp)];
+        const uint32_t m = min(kHalf, lo);
+        lo -= m;
+        const E *from = run() + lo / kStep;
+        for (uint32_t e = 0; e < m; e += kStep) slot(lo + e) = from[e / kStep];
     }
 };
 
@@ -534,11 +524,11 @@ __device__ inline void store_hit(bvh_hit *hits, uint64_t i, const Best &b) {
 }
 
 
-// The best-hit bound that culls nodes: the best hit so far (closest-hit
-// queries) or tmax.
+// The distance that culls nodes: the best hit so far (closest-hit queries)
+// or tmax, widened like the far distances of the slab test.
 template <int Mode>
-__device__ inline float best_bound(const Ray &r, const Best &b) {
-    return (Mode == BVH_TRACE_ANY) ? r.tmax : fminf(b.t, r.tmax);
+__device__ inline float cull_bound(const Ray &r, const Best &b) {
+    return ((Mode == BVH_TRACE_ANY) ? r.tmax : fminf(b.t, r.tmax)) * kFarScale;
 }
 
 // ---------------------------------------------------------------------------
@@ -549,23 +539,20 @@ __device__ inline float best_bound(const Ray &r, const Best &b) {
 // ---------------------------------------------------------------------------
 struct BinState {
     Best best;
+    float cull;     // boxes entered beyond this are culled: the best hit so far or tmax, widened
     uint32_t node;  // next node to visit; kRefEmpty when no node is left
     uint32_t leaf;  // leaf parked by the two-phase order (kRefEmpty: none)
-    uint32_t hold;  // a second leaf met while one is parked
+    uint32_t hold;  // a second leaf met while one is parked; the lane then waits
+    __device__ bool progress() const { return node != kRefEmpty && hold == kRefEmpty; }
 };
 
-__device__ inline BinState bin_start(int64_t n_nodes) {
+__device__ inline BinState bin_start(int64_t n_nodes, const Ray &r) {
     BinState s;
     s.best = Best{INFINITY, 0.0f, 0.0f, 0xFFFFFFFFu};
+    s.cull = r.tmax * kFarScale;
     s.node = n_nodes > 0 ? 0u : kRefEmpty;
     s.leaf = s.hold = kRefEmpty;
     return s;
-}
-
-template <class Stack>
-__device__ inline uint32_t bin_pop(Stack &st) {
-    float unused;
-    return st.sp > 0 ? st.pop(unused) : kRefEmpty;
 }
 
 // Binary node formats: load node i as its box, triangle count (0 for an
@@ -727,82 +714,104 @@ __device__ inline void split_meta(const void *nodes, uint32_t i, const SceneData
         Node::load_meta(i, sd, cnt, off, axis);
 }
 
-// Visits bs.node; returns the leaf reference when the node is a leaf whose
-// box the ray meets (kRefEmpty otherwise).  bs.node moves on to the next node.
-template <class Node, int Mode, class Stack>
-__device__ inline uint32_t bin_visit(const void *nodes, int64_t n_nodes, const SceneData &sd,
-                                     const Ray &r, bool fast, Stack &st, BinState &bs,
-                                     uint32_t &nfetch, bool &incomplete) {
-    if (bs.node >= (uint64_t)n_nodes) {  // bounds guard; a valid tree never takes it
-        bs.node = bs.leaf = bs.hold = kRefEmpty;
-        return kRefEmpty;
-    }
+// Visits bs.node: an interior node whose box the ray meets continues with the
+// near child (split axis and ray direction sign) and stacks the far one; a
+// leaf whose box it meets is parked (or held, if one is parked already).
+// bs.node moves on to the next node.  The node's loads are issued at a raised
+// priority, as in the wide layouts' visits.
+template <class Node, class Stack>
+__device__ inline void bin_visit(const void *nodes, int64_t n_nodes, const SceneData &sd,
+                                 const Ray &r, bool fast, Stack &st, BinState &bs,
+                                 uint32_t &nfetch, bool &incomplete) {
+    // bounds guard; equal on a valid tree
+    const uint32_t at = min(bs.node, (uint32_t)n_nodes - 1u);
     float lo[3], hi[3];
     uint32_t cnt = 0, off = 0, axis = 0;
+    __builtin_amdgcn_s_setprio(3);
     if constexpr (Node::kSplit)
-        Node::load_box(nodes, bs.node, sd, lo, hi);
+        Node::load_box(nodes, at, sd, lo, hi);
     else
-        Node::load(nodes, bs.node, sd, lo, hi, cnt, off, axis);
+        Node::load(nodes, at, sd, lo, hi, cnt, off, axis);
+    __builtin_amdgcn_s_setprio(0);
     nfetch++;
-    const float tcur = best_bound<Mode>(r, bs.best);
-    const float tn = fast ? slab<true>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], tcur)
-                          : slab<false>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], tcur);
-    if (tn != INFINITY) {
-        if constexpr (Node::kSplit) split_meta<Node>(nodes, bs.node, sd, cnt, off, axis);
-        if (cnt > 0) {
-            bs.node = bin_pop(st);
-            return ref_leaf(off, cnt);
-        }
+    const float tn = fast ? slab<true>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], bs.cull)
+                          : slab<false>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], bs.cull);
+    const bool met = tn != INFINITY;
+    if constexpr (Node::kSplit)
+        if (met) split_meta<Node>(nodes, at, sd, cnt, off, axis);
+    if (met && cnt == 0) {
         const bool neg = axis == 0 ? r.nx : (axis == 1 ? r.ny : (axis == 2 ? r.nz : false));
-        const uint32_t left = bs.node + 1, right = bs.node + off;
-        if (!st.push(neg ? left : right, 0.0f)) {
+        const uint32_t left = at + 1, right = at + off;
+        if (st.room(1)) {
+            st.put(neg ? left : right, true);
+            bs.node = neg ? right : left;
+        } else {
             incomplete = true;
             bs.node = bs.leaf = bs.hold = kRefEmpty;
-            return kRefEmpty;
         }
-        bs.node = neg ? right : left;
-        return kRefEmpty;
+        return;
     }
-    bs.node = bin_pop(st);
-    return kRefEmpty;
+    if (met) {
+        const uint32_t leaf = ref_leaf(off, cnt);
+        if (bs.leaf == kRefEmpty) bs.leaf = leaf;
+        else bs.hold = leaf;
+    }
+    bs.node = st.take();
 }
 
-// Tests the triangles of a leaf reference; a satisfied any-hit query ends
-// the ray.
+// After the parked leaf has been tested; a satisfied any-hit query ends the
+// ray.
+template <int Mode>
+__device__ inline void bin_tested(const Ray &r, bool ended, BinState &bs) {
+    bs.leaf = bs.hold;
+    bs.hold = kRefEmpty;
+    if (ended) bs.node = bs.leaf = kRefEmpty;
+    if (Mode == BVH_TRACE_CLOSEST) bs.cull = cull_bound<Mode>(r, bs.best);
+}
+
+// Tests the parked leaf in the lane.
 template <int LeafMode, int Mode>
-__device__ inline bool bin_test_leaf(const SceneData &ld, const Ray &r, uint32_t leaf,
-                                     BinState &bs, uint32_t &ntri) {
-    const uint32_t first = leaf >> 5, cnt = ((leaf >> 1) & 0xFu) + 1u;
-    if (test_leaf<LeafMode, Mode>(ld, r, first, cnt, bs.best, ntri)) {
-        bs.node = bs.leaf = bs.hold = kRefEmpty;
-        return true;
-    }
-    return false;
+__device__ inline void bin_test_parked(const SceneData &ld, const Ray &r, BinState &bs,
+                                       uint32_t &ntri) {
+    const uint32_t first = bs.leaf >> 5, cnt = ((bs.leaf >> 1) & 0xFu) + 1u;
+    bin_tested<Mode>(r, test_leaf<LeafMode, Mode>(ld, r, first, cnt, bs.best, ntri), bs);
 }
 
 // ---------------------------------------------------------------------------
 // Wide layouts: the node holds its children's boxes.  Decoders expose
 //   K                      arity
-//   Prep prep(ray)         per-ray constants (which plane arrays are near/far)
-//   test(node ptr, node, ray, prep, tcur, tn[K], ref[K])
-// writing the entry distance of every child the ray meets (+inf otherwise).
+//   kWords                 16-byte words of a node that a visit reads
+//   Prep prep(ray)         per-ray constants
+//   fetch(node buffer, node, prep, m)   those words, m[kWords]
+//   test(m, ray, cull, tn[K], ref[K])
+// test writes the entry distance of every child the ray meets (+inf
+// otherwise).  Node buffers of the wide layouts are below 4 GiB (the builder
+// sees to it), so each load is base + one 32-bit offset.
+//
+// What bounds a visit of scattered rays is the vector L1: it serves one lookup per
+// clock (a wave's load of 16 bytes per lane from 64 lines takes 65 clocks,
+// measured), so a visit's seven loads occupy it for 448, and the 64 lines of
+// each of the CU's 16 waves together exceed its 32 KB: a line that leaves
+// between two loads of one wave is fetched again.  The wave's priority is
+// therefore raised while it issues a visit's loads, so that the waves of a
+// SIMD do not take turns at theirs (BVH4: bounce rays of the terrain 572 -> 507 us, 4 M
+// uniform rays on the spheres scene 11.1 -> 9.4 ms).
 // ---------------------------------------------------------------------------
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+struct NoPrep {};
 
 // BVH4: the near and far plane arrays of an axis are picked by address (the
 // sign of the direction component decides whether lo_a or hi_a is entered
 // first), so the per-child slab test needs no plane selects.
 struct DecodeBVH4 {
     static constexpr int K = 4;
+    static constexpr int kWords = 7;
     // scattered waves end a round's interior phase at <= kStall progressing
-    // lanes (terrain bounce rays: 0.674 ms with the single-loop order and
-    // batched leaves; 0.616 / 0.600 / 0.577 / 0.559 / 0.563 / 0.585 / 0.646
-    // ms at 8 / 16 / 24 / 32 / 40 / 48 / 56)
+    // lanes (terrain bounce rays: 0.616 / 0.600 / 0.577 / 0.559 / 0.563 /
+    // 0.585 / 0.646 ms at 8 / 16 / 24 / 32 / 40 / 48 / 56)
     static constexpr uint32_t kStall = 32;
     struct Prep {
-        // byte offsets of the entry-plane arrays in a node; the exit-plane
-        // array of an axis is the other one of the pair (lo_a, hi_a), at
-        // (lo_a + hi_a offsets) - entry offset
-        uint32_t nx, ny, nz;
+        uint32_t nx, ny, nz;  // byte offsets of the entry-plane arrays in a node
     };
     __device__ static Prep prep(const Ray &r) {
         Prep p;
@@ -811,28 +820,30 @@ struct DecodeBVH4 {
         p.nz = r.nz ? 80u : 32u;
         return p;
     }
+    // m: entry planes of x, y, z, exit planes of x, y, z, references.  The
+    // offsets of the two plane arrays of an axis (0 and 48, 16 and 64, 32 and
+    // 80) turn into each other by one exclusive or, also in 128-byte aligned
+    // nodes' addresses.
+    __device__ static void fetch(const void *nodes, uint32_t node, const Prep &p, u32x4 *m) {
+        const char *b = static_cast<const char *>(nodes);
+        const uint32_t o = node << 7, x = o + p.nx, y = o + p.ny, z = o + p.nz;
+        m[0] = *reinterpret_cast<const u32x4 *>(b + x);
+        m[1] = *reinterpret_cast<const u32x4 *>(b + y);
+        m[2] = *reinterpret_cast<const u32x4 *>(b + z);
+        m[3] = *reinterpret_cast<const u32x4 *>(b + (x ^ 48u));
+        m[4] = *reinterpret_cast<const u32x4 *>(b + (y ^ 80u));
+        m[5] = *reinterpret_cast<const u32x4 *>(b + (z ^ 112u));
+        m[6] = *reinterpret_cast<const u32x4 *>(b + (size_t)o + 96);
+    }
     template <bool Fast>
-    __device__ static void test(const void *base, uint32_t node, const Ray &r, const Prep &pp,
-                                float tcur, float *tn, uint32_t *ref) {
-        // 32-bit byte offsets from the buffer base (the builder keeps wide
-        // node buffers below 4 GiB), so each fetch is base + one offset
-        const char *b = static_cast<const char *>(base);
-        const uint32_t o = node * 128u;
-        const float4 nx = *reinterpret_cast<const float4 *>(b + (o + pp.nx));
-        const float4 ny = *reinterpret_cast<const float4 *>(b + (o + pp.ny));
-        const float4 nz = *reinterpret_cast<const float4 *>(b + (o + pp.nz));
-        const float4 fx = *reinterpret_cast<const float4 *>(b + ((o + 48u) - pp.nx));
-        const float4 fy = *reinterpret_cast<const float4 *>(b + ((o + 80u) - pp.ny));
-        const float4 fz = *reinterpret_cast<const float4 *>(b + ((o + 112u) - pp.nz));
-        const uint4 ch = *reinterpret_cast<const uint4 *>(b + (o + 96u));
-        tn[0] = slab_nf<Fast>(r, nx.x, ny.x, nz.x, fx.x, fy.x, fz.x, tcur);
-        tn[1] = slab_nf<Fast>(r, nx.y, ny.y, nz.y, fx.y, fy.y, fz.y, tcur);
-        tn[2] = slab_nf<Fast>(r, nx.z, ny.z, nz.z, fx.z, fy.z, fz.z, tcur);
-        tn[3] = slab_nf<Fast>(r, nx.w, ny.w, nz.w, fx.w, fy.w, fz.w, tcur);
-        ref[0] = ch.x;
-        ref[1] = ch.y;
-        ref[2] = ch.z;
-        ref[3] = ch.w;
+    __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn, uint32_t *ref) {
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            tn[c] = slab_nf<Fast>(r, __uint_as_float(m[0][c]), __uint_as_float(m[1][c]),
+                                  __uint_as_float(m[2][c]), __uint_as_float(m[3][c]),
+                                  __uint_as_float(m[4][c]), __uint_as_float(m[5][c]), cull);
+            ref[c] = m[6][c];
+        }
     }
 };
 
@@ -846,27 +857,28 @@ __device__ inline uint32_t half_of(const uint32_t *w, int c) {
 
 // Quantised layouts: the near/far choice is made once per packed word (four
 // u8 or two u16 planes at a time) before dequantising.
-struct SignPrep {
-    bool nx, ny, nz;
+template <int NodeBytes, int Words>
+struct DecodeBVH8 {
+    static constexpr int K = 8;
+    static constexpr int kWords = Words;
+    // as DecodeBVH4::kStall (terrain bounce rays, BVH8-Q8: 0.705 / 0.653 /
+    // 0.620 / 0.632 / 0.665 ms at 16 / 32 / 40 / 48 / 56)
+    static constexpr uint32_t kStall = 40;
+    using Prep = NoPrep;
+    __device__ static Prep prep(const Ray &) { return Prep{}; }
+    __device__ static void fetch(const void *nodes, uint32_t node, const Prep &, u32x4 *m) {
+        const char *b = static_cast<const char *>(nodes) + (size_t)(node * (uint32_t)NodeBytes);
+#pragma unroll
+        for (int k = 0; k < Words; k++) m[k] = reinterpret_cast<const u32x4 *>(b)[k];
+    }
 };
 
-struct DecodeBVH8Q8 {
-    static constexpr int K = 8;
-    // as DecodeBVH4::kStall (terrain bounce rays: 0.668 ms single-loop;
-    // 0.705 / 0.653 / 0.620 / 0.632 / 0.665 ms at 16 / 32 / 40 / 48 / 56)
-    static constexpr uint32_t kStall = 40;
-    using Prep = SignPrep;
-    __device__ static Prep prep(const Ray &r) { return Prep{r.nx, r.ny, r.nz}; }
+struct DecodeBVH8Q8 : DecodeBVH8<sizeof(bvh_node_bvh8_q8), 7> {
     template <bool Fast>
-    __device__ static void test(const void *base, uint32_t node, const Ray &r, const Prep &,
-                                float tcur, float *tn, uint32_t *ref) {
-        const uint4 *p = static_cast<const uint4 *>(base) + 8 * (size_t)node;
+    __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn, uint32_t *ref) {
         uint32_t w[28];
 #pragma unroll
-        for (int k = 0; k < 7; k++) {
-            const uint4 q = p[k];
-            w[4 * k] = q.x; w[4 * k + 1] = q.y; w[4 * k + 2] = q.z; w[4 * k + 3] = q.w;
-        }
+        for (int k = 0; k < 28; k++) w[k] = m[k / 4][k % 4];
         const float ox = __uint_as_float(w[0]), oy = __uint_as_float(w[1]), oz = __uint_as_float(w[2]);
         const float sx = __uint_as_float(w[3]), sy = __uint_as_float(w[4]), sz = __uint_as_float(w[5]);
         // words: lo_x 6-7, lo_y 8-9, lo_z 10-11, hi_x 12-13, hi_y 14-15, hi_z 16-17
@@ -889,27 +901,18 @@ struct DecodeBVH8Q8 {
             const float fyp = fmaf((float)byte_of(f[2], f[3], c), sy, oy);
             const float fzp = fmaf((float)byte_of(f[4], f[5], c), sz, oz);
             const bool valid = (uint32_t)c < w[26];
-            tn[c] = valid ? slab_nf<Fast>(r, nxp, nyp, nzp, fxp, fyp, fzp, tcur) : INFINITY;
+            tn[c] = valid ? slab_nf<Fast>(r, nxp, nyp, nzp, fxp, fyp, fzp, cull) : INFINITY;
             ref[c] = w[18 + c];
         }
     }
 };
 
-struct DecodeBVH8Q16 {
-    static constexpr int K = 8;
-    static constexpr uint32_t kStall = 40;  // 0.642 ms at 40 (0.688 single-loop)
-    using Prep = SignPrep;
-    __device__ static Prep prep(const Ray &r) { return Prep{r.nx, r.ny, r.nz}; }
+struct DecodeBVH8Q16 : DecodeBVH8<sizeof(bvh_node_bvh8_q16), 10> {
     template <bool Fast>
-    __device__ static void test(const void *base, uint32_t node, const Ray &r, const Prep &,
-                                float tcur, float *tn, uint32_t *ref) {
-        const uint4 *p = static_cast<const uint4 *>(base) + 10 * (size_t)node;
+    __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn, uint32_t *ref) {
         uint32_t w[40];
 #pragma unroll
-        for (int k = 0; k < 10; k++) {
-            const uint4 q = p[k];
-            w[4 * k] = q.x; w[4 * k + 1] = q.y; w[4 * k + 2] = q.z; w[4 * k + 3] = q.w;
-        }
+        for (int k = 0; k < 40; k++) w[k] = m[k / 4][k % 4];
         const float ox = __uint_as_float(w[0]), oy = __uint_as_float(w[1]), oz = __uint_as_float(w[2]);
         const float sx = __uint_as_float(w[3]), sy = __uint_as_float(w[4]), sz = __uint_as_float(w[5]);
         // words: lo_x 6-9, lo_y 10-13, lo_z 14-17, hi_x 18-21, hi_y 22-25, hi_z 26-29
@@ -932,217 +935,208 @@ struct DecodeBVH8Q16 {
             const float fyp = fmaf((float)half_of(f + 4, c), sy, oy);
             const float fzp = fmaf((float)half_of(f + 8, c), sz, oz);
             const bool valid = (uint32_t)c < w[38];
-            tn[c] = valid ? slab_nf<Fast>(r, nxp, nyp, nzp, fxp, fyp, fzp, tcur) : INFINITY;
+            tn[c] = valid ? slab_nf<Fast>(r, nxp, nyp, nzp, fxp, fyp, fzp, cull) : INFINITY;
             ref[c] = w[30 + c];
         }
     }
 };
 
-__device__ inline void cswap(float *t, uint32_t *r, int a, int b) {
-    const bool sw = t[b] < t[a];
-    const float ta = t[a], tb = t[b];
-    const uint32_t ra = r[a], rb = r[b];
-    t[a] = sw ? tb : ta;
-    t[b] = sw ? ta : tb;
-    r[a] = sw ? rb : ra;
-    r[b] = sw ? ra : rb;
+// A stack entry of a wide traversal: entry distance (never negative) above
+// the reference.
+__device__ inline uint64_t entry_of(float t, uint32_t ref) {
+    return ((uint64_t)__float_as_uint(t) << 32) | ref;
+}
+__device__ inline float entry_t(uint64_t e) { return __uint_as_float((uint32_t)(e >> 32)); }
+__device__ inline uint32_t entry_ref(uint64_t e) { return (uint32_t)e; }
+
+// Orders two entries.  Read as 64-bit floats they are positive and finite
+// (the f32 infinity's bits in the upper word are a finite f64), so the f64
+// minimum and maximum order them as integers would, in two full-rate VALU
+// instructions (measured 5.8 cycles each per wave, v_min_f32 5.6) where a
+// compare and selects take five.  Denormals are kept in f64.
+__device__ inline void order_entries(uint64_t &a, uint64_t &b) {
+    const double x = __longlong_as_double((long long)a), y = __longlong_as_double((long long)b);
+    double lo, hi;
+    asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(x), "v"(y));
+    asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(x), "v"(y));
+    a = (uint64_t)__double_as_longlong(lo);
+    b = (uint64_t)__double_as_longlong(hi);
 }
 
 // Ascending sort by entry distance (sorting networks: 5 and 19 exchanges).
 template <int K>
-__device__ inline void sort_children(float *t, uint32_t *r) {
+__device__ inline void sort_entries(uint64_t *e) {
     if (K == 4) {
-        cswap(t, r, 0, 1); cswap(t, r, 2, 3);
-        cswap(t, r, 0, 2); cswap(t, r, 1, 3);
-        cswap(t, r, 1, 2);
+        order_entries(e[0], e[1]); order_entries(e[2], e[3]);
+        order_entries(e[0], e[2]); order_entries(e[1], e[3]);
+        order_entries(e[1], e[2]);
     } else {
-        cswap(t, r, 0, 2); cswap(t, r, 1, 3); cswap(t, r, 4, 6); cswap(t, r, 5, 7);
-        cswap(t, r, 0, 4); cswap(t, r, 1, 5); cswap(t, r, 2, 6); cswap(t, r, 3, 7);
-        cswap(t, r, 0, 1); cswap(t, r, 2, 3); cswap(t, r, 4, 5); cswap(t, r, 6, 7);
-        cswap(t, r, 2, 4); cswap(t, r, 3, 5);
-        cswap(t, r, 1, 4); cswap(t, r, 3, 6);
-        cswap(t, r, 1, 2); cswap(t, r, 3, 4); cswap(t, r, 5, 6);
+        order_entries(e[0], e[2]); order_entries(e[1], e[3]);
+        order_entries(e[4], e[6]); order_entries(e[5], e[7]);
+        order_entries(e[0], e[4]); order_entries(e[1], e[5]);
+        order_entries(e[2], e[6]); order_entries(e[3], e[7]);
+        order_entries(e[0], e[1]); order_entries(e[2], e[3]);
+        order_entries(e[4], e[5]); order_entries(e[6], e[7]);
+        order_entries(e[2], e[4]); order_entries(e[3], e[5]);
+        order_entries(e[1], e[4]); order_entries(e[3], e[6]);
+        order_entries(e[1], e[2]); order_entries(e[3], e[4]); order_entries(e[5], e[6]);
     }
 }
 
-
-// Pops stack entries until one is not culled by tb (the current best hit or
-// tmax); returns kRefEmpty when the stack runs dry.
-template <class Stack>
-__device__ inline uint32_t pop_unculled(Stack &st, float tb, float &t_entry) {
-    while (st.sp > 0) {
-        float t;
-        const uint32_t ref = st.pop(t);
-        if (t <= tb * kFarScale) {
-            t_entry = t;
-            return ref;
-        }
-    }
-    return kRefEmpty;
+// Puts the kept ones of the sorted entries e[1..K) on the stack, farthest
+// first (the kept ones come before the others, whose distance is +inf).
+// False when the stack has no room for them.
+template <int K, class Stack>
+__device__ inline bool put_rest(Stack &st, const uint64_t *e) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int c = 1; c < K; c++) n += entry_t(e[c]) != INFINITY ? 1u : 0u;
+    if (!st.room(n > 0 ? n : 1u)) return false;
+#pragma unroll
+    for (int c = K - 1; c >= 1; c--) st.put(e[c], entry_t(e[c]) != INFINITY);
+    return true;
 }
 
 // Traversal state of one ray in a wide BVH.
 struct WideState {
     Best best;
-    uint32_t cur;    // entry to visit next; kRefEmpty once the ray is done
-    float cur_t;     // entry distance of cur
-    uint32_t leaf;   // leaf parked by the two-phase order (kRefEmpty: none)
+    float cull;      // boxes entered beyond this are culled: the best hit so far or tmax, widened
+    uint64_t cur;    // entry to visit next; reference kRefDone once the ray is done
+    uint32_t leaf;   // leaf parked by the two-phase order (kRefDone: none)
+    __device__ bool interior() const { return ((uint32_t)cur & 1u) != 0u; }
+    __device__ bool live() const { return entry_ref(cur) != kRefDone; }
+    // parks the leaf at hand if none is parked; true: the lane needs another entry
+    __device__ bool park() {
+        const bool p = !interior() && live() && leaf == kRefDone;
+        leaf = p ? entry_ref(cur) : leaf;
+        return p;
+    }
 };
 
-__device__ inline WideState wide_start(int64_t n_nodes) {
+__device__ inline WideState wide_start(int64_t n_nodes, const Ray &r) {
     WideState ws;
     ws.best = Best{INFINITY, 0.0f, 0.0f, 0xFFFFFFFFu};
-    ws.cur = n_nodes > 0 ? ref_interior(0) : kRefEmpty;
-    ws.cur_t = 0.0f;
-    ws.leaf = kRefEmpty;
+    ws.cull = fminf(r.tmax, INFINITY) * kFarScale;  // a NaN tmax culls no box (and accepts no hit)
+    ws.cur = entry_of(0.0f, n_nodes > 0 ? ref_interior(0) : kRefDone);
+    ws.leaf = kRefDone;
     return ws;
 }
 
-// Visits the interior node ws.cur: tests all its children, sorts the hit ones
-// near-first, pushes all but the nearest with their entry distances and
-// continues with the nearest (or with the next unculled stack entry when no
-// child is hit).  A failed push (stack full) ends the ray as incomplete.
+// A closest-hit ray's culling distance after its best hit may have changed.
+template <int Mode>
+__device__ inline void wide_update_cull(const Ray &r, WideState &ws) {
+    if (Mode == BVH_TRACE_CLOSEST) ws.cull = cull_bound<Mode>(r, ws.best);
+}
+
+// One advance of a lane: visits the interior node at hand (tests all its
+// children, sorts those the ray meets near-first, stacks all but the nearest
+// with their entry distances and continues with the nearest); a leaf reached
+// this way or from the stack is parked if none is parked yet, and the lane
+// takes its next unculled entry from the stack.  Afterwards ws.cur is an
+// interior node, a leaf while another is parked, or kRefDone.  A stack
+// without room ends the ray as incomplete.
 template <class Dec, int Mode, class Stack>
-__device__ inline void wide_visit_interior(const void *nodes, int64_t n_nodes, const Ray &r,
-                                           const typename Dec::Prep &prep, bool fast, Stack &st,
-                                           WideState &ws, uint32_t &nfetch, bool &incomplete) {
+__device__ inline void wide_advance(const void *nodes, uint32_t last, const Ray &r,
+                                    const typename Dec::Prep &prep, bool fast, Stack &st,
+                                    WideState &ws, uint32_t &nfetch, bool &incomplete) {
     constexpr int K = Dec::K;
-    const float tcur = best_bound<Mode>(r, ws.best);
-    if ((ws.cur >> 1) >= (uint64_t)n_nodes) {  // bounds guard; never taken on a valid tree
-        ws.cur = kRefEmpty;
-        ws.leaf = kRefEmpty;
-        return;
-    }
-    float tn[K];
-    uint32_t ref[K];
-    if (fast)
-        Dec::template test<true>(nodes, ws.cur >> 1, r, prep, tcur, tn, ref);
-    else
-        Dec::template test<false>(nodes, ws.cur >> 1, r, prep, tcur, tn, ref);
-    nfetch++;
-    sort_children<K>(tn, ref);
-    bool ok = true;
+    bool pop = false;
+    if (ws.interior()) {
+        float tn[K];
+        uint32_t ref[K];
+        u32x4 m[Dec::kWords];
+        __builtin_amdgcn_s_setprio(3);
+        // the index is clamped as a bounds guard, which a valid tree never needs
+        Dec::fetch(nodes, min((uint32_t)ws.cur >> 1, last), prep, m);
+        __builtin_amdgcn_s_setprio(0);
+        if (fast)
+            Dec::template test<true>(m, r, ws.cull, tn, ref);
+        else
+            Dec::template test<false>(m, r, ws.cull, tn, ref);
+        nfetch++;
+        uint64_t e[K];
 #pragma unroll
-    for (int c = K - 1; c >= 1; c--)
-        if (tn[c] != INFINITY) ok = st.push(ref[c], tn[c]) && ok;
-    if (!ok) {
-        incomplete = true;
-        ws.cur = kRefEmpty;
-        ws.leaf = kRefEmpty;
-    } else if (tn[0] != INFINITY) {
-        ws.cur = ref[0];
-        ws.cur_t = tn[0];
-    } else {
-        ws.cur = pop_unculled(st, tcur, ws.cur_t);
+        for (int c = 0; c < K; c++) e[c] = entry_of(tn[c], ref[c]);
+        sort_entries<K>(e);
+        ws.cur = e[0];
+        pop = entry_t(e[0]) == INFINITY;
+        if (!put_rest<K>(st, e)) {
+            incomplete = true;
+            st.reset();
+            pop = true;
+        }
+    }
+    if (!pop) pop = ws.park();
+    while (pop) {
+        const uint64_t e = st.take();
+        const bool keep = entry_t(e) <= ws.cull;
+        ws.cur = keep ? e : ws.cur;
+        pop = !keep || ws.park();
     }
 }
 
-// Tests the triangles of a leaf reference; an any-hit query that is
-// satisfied ends the ray.
-template <int LeafMode, int Mode>
-__device__ inline bool wide_test_leaf(const SceneData &ld, const Ray &r, uint32_t leaf,
-                                      WideState &ws, uint32_t &ntri) {
-    const uint32_t first = leaf >> 5, cnt = ((leaf >> 1) & 0xFu) + 1u;
+// Takes the next unculled entry where the one at hand was taken before the
+// best hit improved and is culled by now.
+template <class Stack>
+__device__ inline void wide_recull(Stack &st, WideState &ws) {
+    while (!(entry_t(ws.cur) <= ws.cull)) ws.cur = st.take();
+}
+
+// Tests the triangles of the parked leaf in the lane; a satisfied any-hit
+// query ends the ray.
+template <int LeafMode, int Mode, class Stack>
+__device__ inline void wide_test_parked(const SceneData &ld, const Ray &r, Stack &st, WideState &ws,
+                                        uint32_t &ntri) {
+    const uint32_t first = ws.leaf >> 5, cnt = ((ws.leaf >> 1) & 0xFu) + 1u;
+    ws.leaf = kRefDone;
     if (test_leaf<LeafMode, Mode>(ld, r, first, cnt, ws.best, ntri)) {
-        ws.cur = kRefEmpty;
-        ws.leaf = kRefEmpty;
-        return true;
-    }
-    return false;
-}
-
-// One step of the single-loop order: visit ws.cur (interior node or leaf),
-// then take the next entry.  The best hit is updated as soon as a leaf is
-// tested, which culls the most.
-template <class Dec, int LeafMode, int Mode, class Stack>
-__device__ inline void wide_step_single(const void *nodes, int64_t n_nodes, const SceneData &ld,
-                                        const Ray &r, const typename Dec::Prep &prep, bool fast,
-                                        Stack &st, WideState &ws, uint32_t &nfetch,
-                                        uint32_t &ntri, bool &incomplete) {
-    if (ws.cur & 1u) {
-        wide_visit_interior<Dec, Mode>(nodes, n_nodes, r, prep, fast, st, ws, nfetch, incomplete);
+        ws.cur = kBottom<uint64_t>;
         return;
     }
-    if (wide_test_leaf<LeafMode, Mode>(ld, r, ws.cur, ws, ntri)) return;
-    ws.cur = pop_unculled(st, best_bound<Mode>(r, ws.best), ws.cur_t);
+    wide_update_cull<Mode>(r, ws);
+    wide_recull(st, ws);
 }
 
-// One round of the two-phase order (the while-while scheme of Aila and
-// Laine 2009, with speculative traversal), wave-wide, so that the lanes test
-// nodes together and triangles together instead of splitting every step
-// between the two:
-//   interior phase: lanes visit interior nodes; a lane that reaches a leaf
-//     parks it (one at a time) and keeps descending; the phase ends when
-//     every lane has a parked leaf or has no entry left;
-//   leaf phase: every lane with a parked leaf tests its triangles.
+// One round of the two-phase order (the while-while scheme of Aila and Laine
+// 2009, with speculative traversal), called by every lane of the wave (lanes
+// without a ray hold kRefDone), so that the lanes test nodes together and
+// triangles together instead of splitting every step between the two:
+//   interior phase: lanes visit interior nodes, park the first leaf they
+//     meet and keep descending; a lane whose next entry is a second leaf
+//     waits.  With coherent rays the phase ends when every lane has a parked
+//     leaf or is done; with scattered rays once at most kStall lanes can
+//     still make progress (waiting for the last stragglers of such a wave
+//     would idle the rest);
+//   leaf phase: the parked leaves are tested, each in its lane where the
+//     rays are coherent (their lanes hold leaves at the same time), else in
+//     one wave-batched leaf phase.
 // Every node that the current best does not cull is still visited, so the
-// result equals the single-loop order's.
+// result equals the plain order's.
 template <class Dec, int LeafMode, int Mode, class Stack>
-__device__ inline void wide_round_two_phase(const void *nodes, int64_t n_nodes,
-                                            const SceneData &ld, const Ray &r,
-                                            const typename Dec::Prep &prep, bool fast,
-                                            Stack &st, WideState &ws, uint32_t &nfetch,
-                                            uint32_t &ntri, bool &incomplete) {
+__device__ inline void wide_round(const void *nodes, uint32_t last, const SceneData &ld,
+                                  const Ray &r, const typename Dec::Prep &prep, bool fast,
+                                  bool coherent, Stack &st, WideState &ws, WaveLeafLds *wl,
+                                  uint32_t &nfetch, uint32_t &ntri, bool &incomplete) {
     for (;;) {
-        if (ws.cur != kRefEmpty && (ws.cur & 1u))
-            wide_visit_interior<Dec, Mode>(nodes, n_nodes, r, prep, fast, st, ws, nfetch,
-                                           incomplete);
-        if (ws.cur != kRefEmpty && !(ws.cur & 1u) && ws.leaf == kRefEmpty) {
-            ws.leaf = ws.cur;
-            ws.cur = pop_unculled(st, best_bound<Mode>(r, ws.best), ws.cur_t);
-        }
-        if (__builtin_amdgcn_ballot_w64(ws.leaf == kRefEmpty && ws.cur != kRefEmpty) == 0) break;
+        wide_advance<Dec, Mode>(nodes, last, r, prep, fast, st, ws, nfetch, incomplete);
+        const uint64_t prog = __builtin_amdgcn_ballot_w64(ws.interior());
+        const uint64_t parked = __builtin_amdgcn_ballot_w64(ws.leaf != kRefDone);
+        if (coherent ? (prog & ~parked) == 0
+                     : (prog == 0 || ((uint32_t)__builtin_popcountll(prog) <= Dec::kStall && parked != 0)))
+            break;
     }
-    if (ws.leaf != kRefEmpty) {
-        const uint32_t leaf = ws.leaf;
-        ws.leaf = kRefEmpty;
-        if (wide_test_leaf<LeafMode, Mode>(ld, r, leaf, ws, ntri)) return;
-        // the entry taken before the leaf test may be culled by the new best
-        const float tb = best_bound<Mode>(r, ws.best);
-        if (ws.cur != kRefEmpty && !(ws.cur_t <= tb * kFarScale))
-            ws.cur = pop_unculled(st, tb, ws.cur_t);
+    if (coherent) {
+        if (ws.leaf != kRefDone) wide_test_parked<LeafMode, Mode>(ld, r, st, ws, ntri);
+        return;
     }
-}
-
-// Two-phase round for scattered rays (called by every lane of the wave;
-// `active` lanes have a ray): lanes visit interior nodes and park the first
-// leaf they meet, continuing speculatively; a lane with a parked leaf whose
-// next entry is a leaf waits.  The interior phase ends once at most `stall`
-// lanes can still make progress (waiting for the last stragglers of an
-// incoherent wave would idle the rest), and the parked leaves are then
-// tested in one wave-batched leaf phase.  Nodes the best hit does not cull
-// are all visited, so the result equals the single-loop order's.
-template <class Dec, int LeafMode, int Mode, class Stack>
-__device__ inline void wide_round_wave(const void *nodes, int64_t n_nodes, const SceneData &ld,
-                                       const Ray &r, const typename Dec::Prep &prep, bool fast,
-                                       Stack &st, WideState &ws, bool active, WaveLeafLds *wl,
-                                       uint32_t stall, uint32_t &nfetch, uint32_t &ntri,
-                                       bool &incomplete) {
-    for (;;) {
-        if (active && ws.cur != kRefEmpty && (ws.cur & 1u))
-            wide_visit_interior<Dec, Mode>(nodes, n_nodes, r, prep, fast, st, ws, nfetch,
-                                           incomplete);
-        if (active && ws.cur != kRefEmpty && !(ws.cur & 1u) && ws.leaf == kRefEmpty) {
-            ws.leaf = ws.cur;
-            ws.cur = pop_unculled(st, best_bound<Mode>(r, ws.best), ws.cur_t);
-        }
-        const uint64_t prog = __builtin_amdgcn_ballot_w64(
-            active && ws.cur != kRefEmpty && ((ws.cur & 1u) || ws.leaf == kRefEmpty));
-        const uint64_t parked = __builtin_amdgcn_ballot_w64(active && ws.leaf != kRefEmpty);
-        if (prog == 0 || ((uint32_t)__builtin_popcountll(prog) <= stall && parked != 0)) break;
-    }
-    const bool want = active && ws.leaf != kRefEmpty;
+    const bool want = ws.leaf != kRefDone;
     const uint32_t first = ws.leaf >> 5, cnt = ((ws.leaf >> 1) & 0xFu) + 1u;
     const bool ended = wave_test_leaves<LeafMode, Mode>(ld, r, want, first, cnt, ws.best, ntri, wl);
     if (want) {
-        ws.leaf = kRefEmpty;
-        if (ended) {
-            ws.cur = kRefEmpty;
-        } else {
-            const float tb = best_bound<Mode>(r, ws.best);
-            if (ws.cur != kRefEmpty && !(ws.cur_t <= tb * kFarScale))
-                ws.cur = pop_unculled(st, tb, ws.cur_t);
-        }
+        ws.leaf = kRefDone;
+        wide_update_cull<Mode>(r, ws);
+        if (ended) ws.cur = kBottom<uint64_t>;
+        wide_recull(st, ws);
     }
 }
 
@@ -1150,107 +1144,86 @@ __device__ inline void wide_round_wave(const void *nodes, int64_t n_nodes, const
 // Tracer policies: the per-layout state and steps behind one interface, so
 // the kernels (one ray per lane, persistent, fallback, batched) are written
 // once for all layouts.
-//   kWithT              stack entries carry entry distances (pop-time cull)
+//   Entry               stack entry (a reference, or one with its distance)
 //   Prep prep(ray)      per-ray layout constants
-//   State start(nodes)  initial state;  done(state);  best(state)
-//   step<LeafMode, Mode>(...)   one node or leaf of the single-loop order
-//   kBatchLeaves, round_wave<LeafMode, Mode>(...)   (wide layouts) one round
-//                       of the two-phase order with a wave-batched leaf phase
-//   round<LeafMode, Mode>(...)  one round of the two-phase order (wave-wide)
+//   State start(nodes, ray), none()   a ray's initial state, that of no ray
+//   done(state)
+//   step<LeafMode, Mode>(...)   one advance of a lane on its own, and its leaf
+//   wave<LeafMode, Mode>(...)   one round of the wave: every lane calls it,
+//                               lanes without a ray with the state none()
 // ---------------------------------------------------------------------------
 template <class Dec>
 struct WideTracer {
-    static constexpr bool kWithT = true;
-    // scattered waves batch their leaf tests across the wave (round_wave)
-    static constexpr bool kBatchLeaves = true;
+    using Entry = uint64_t;
     using State = WideState;
     using Prep = typename Dec::Prep;
     __device__ static Prep prep(const Ray &r) { return Dec::prep(r); }
-    __device__ static State start(int64_t n_nodes) { return wide_start(n_nodes); }
-    __device__ static bool done(const State &s) { return s.cur == kRefEmpty; }
+    __device__ static State start(int64_t n_nodes, const Ray &r) { return wide_start(n_nodes, r); }
+    __device__ static State none() { return wide_start(0, Ray{}); }
+    __device__ static bool done(const State &s) { return !s.live() && s.leaf == kRefDone; }
     template <int LeafMode, int Mode, class Stack>
     __device__ static void step(const void *nodes, int64_t n_nodes, const SceneData &ld,
                                 const Ray &r, const Prep &prep, bool fast, Stack &st, State &s,
                                 uint32_t &nfetch, uint32_t &ntri, bool &incomplete) {
-        wide_step_single<Dec, LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, s, nfetch,
-                                              ntri, incomplete);
+        wide_advance<Dec, Mode>(nodes, (uint32_t)n_nodes - 1u, r, prep, fast, st, s, nfetch,
+                                incomplete);
+        if (s.leaf != kRefDone) wide_test_parked<LeafMode, Mode>(ld, r, st, s, ntri);
     }
     template <int LeafMode, int Mode, class Stack>
-    __device__ static void round(const void *nodes, int64_t n_nodes, const SceneData &ld,
-                                 const Ray &r, const Prep &prep, bool fast, Stack &st, State &s,
-                                 uint32_t &nfetch, uint32_t &ntri, bool &incomplete) {
-        wide_round_two_phase<Dec, LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, s,
-                                                  nfetch, ntri, incomplete);
-    }
-    // scattered waves: the two-phase round with a wave-batched leaf phase
-    template <int LeafMode, int Mode, class Stack>
-    __device__ static void round_wave(const void *nodes, int64_t n_nodes, const SceneData &ld,
-                                      const Ray &r, const Prep &prep, bool fast, Stack &st,
-                                      State &s, bool active, WaveLeafLds *wl, uint32_t &nfetch,
-                                      uint32_t &ntri, bool &incomplete) {
-        wide_round_wave<Dec, LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, s, active, wl,
-                                             Dec::kStall, nfetch, ntri, incomplete);
+    __device__ static void wave(const void *nodes, int64_t n_nodes, const SceneData &ld,
+                                const Ray &r, const Prep &prep, bool fast, bool coherent, Stack &st,
+                                State &s, WaveLeafLds *wl, uint32_t &nfetch, uint32_t &ntri,
+                                bool &incomplete) {
+        wide_round<Dec, LeafMode, Mode>(nodes, (uint32_t)n_nodes - 1u, ld, r, prep, fast, coherent,
+                                        st, s, wl, nfetch, ntri, incomplete);
     }
 };
 
 template <class Node>
 struct BinTracer {
-    static constexpr bool kWithT = false;
-    // a binary node visit is one box test, so a batched leaf phase per visit
-    // costs more than it saves (measured 3-5 % slower on incoherent rays):
-    // incoherent waves use the per-lane step
-    static constexpr bool kBatchLeaves = false;
+    using Entry = uint32_t;
     using State = BinState;
-    struct Prep {};
+    using Prep = NoPrep;
+    // as DecodeBVH4::kStall (AABB2, terrain bounce rays: 1.82 ms visiting one
+    // node per step and testing leaves in their lanes; 1.24 / 1.10 / 1.07 ms
+    // with this round at 16 / 32 / 48)
+    static constexpr uint32_t kStall = 40;
     __device__ static Prep prep(const Ray &) { return Prep{}; }
-    __device__ static State start(int64_t n_nodes) { return bin_start(n_nodes); }
-    __device__ static bool done(const State &s) {
-        return s.node == kRefEmpty && s.leaf == kRefEmpty && s.hold == kRefEmpty;
-    }
-    // single-loop order: visit a node and test a leaf as soon as it is met.
-    // A persistent wave can switch orders between rounds, so a leaf still
-    // parked by the two-phase order is tested first.
+    __device__ static State start(int64_t n_nodes, const Ray &r) { return bin_start(n_nodes, r); }
+    __device__ static State none() { return bin_start(0, Ray{}); }
+    __device__ static bool done(const State &s) { return s.node == kRefEmpty && s.leaf == kRefEmpty; }
     template <int LeafMode, int Mode, class Stack>
     __device__ static void step(const void *nodes, int64_t n_nodes, const SceneData &ld,
                                 const Ray &r, const Prep &, bool fast, Stack &st, State &s,
                                 uint32_t &nfetch, uint32_t &ntri, bool &incomplete) {
-        if (s.leaf != kRefEmpty) {
-            const uint32_t parked = s.leaf;
-            s.leaf = s.hold;
-            s.hold = kRefEmpty;
-            bin_test_leaf<LeafMode, Mode>(ld, r, parked, s, ntri);
+        if (s.progress()) bin_visit<Node>(nodes, n_nodes, ld, r, fast, st, s, nfetch, incomplete);
+        if (s.leaf != kRefEmpty) bin_test_parked<LeafMode, Mode>(ld, r, s, ntri);
+    }
+    // One round of the two-phase order, as wide_round: lanes visit nodes and
+    // park the leaves they meet (one, and one held), then the parked leaves
+    // are tested.
+    template <int LeafMode, int Mode, class Stack>
+    __device__ static void wave(const void *nodes, int64_t n_nodes, const SceneData &ld,
+                                const Ray &r, const Prep &, bool fast, bool coherent, Stack &st,
+                                State &s, WaveLeafLds *wl, uint32_t &nfetch, uint32_t &ntri,
+                                bool &incomplete) {
+        for (;;) {
+            if (s.progress()) bin_visit<Node>(nodes, n_nodes, ld, r, fast, st, s, nfetch, incomplete);
+            const uint64_t prog = __builtin_amdgcn_ballot_w64(s.progress());
+            const uint64_t parked = __builtin_amdgcn_ballot_w64(s.leaf != kRefEmpty);
+            if (coherent ? (prog & ~parked) == 0
+                         : (prog == 0 || ((uint32_t)__builtin_popcountll(prog) <= kStall && parked != 0)))
+                break;
+        }
+        const bool want = s.leaf != kRefEmpty;
+        if (coherent) {
+            if (want) bin_test_parked<LeafMode, Mode>(ld, r, s, ntri);
             return;
         }
-        if (s.node == kRefEmpty) return;
-        const uint32_t leaf =
-            bin_visit<Node, Mode>(nodes, n_nodes, ld, r, fast, st, s, nfetch, incomplete);
-        if (leaf != kRefEmpty) bin_test_leaf<LeafMode, Mode>(ld, r, leaf, s, ntri);
-    }
-    // two-phase order: lanes visit nodes and park the leaves they meet (one,
-    // plus one held while the first is parked, after which the lane waits);
-    // the phase ends when every lane has a parked leaf or no node left; then
-    // the parked leaves are tested together.
-    template <int LeafMode, int Mode, class Stack>
-    __device__ static void round(const void *nodes, int64_t n_nodes, const SceneData &ld,
-                                 const Ray &r, const Prep &, bool fast, Stack &st, State &s,
-                                 uint32_t &nfetch, uint32_t &ntri, bool &incomplete) {
-        for (;;) {
-            if (s.node != kRefEmpty && s.hold == kRefEmpty) {
-                const uint32_t leaf =
-                    bin_visit<Node, Mode>(nodes, n_nodes, ld, r, fast, st, s, nfetch, incomplete);
-                if (leaf != kRefEmpty) {
-                    if (s.leaf == kRefEmpty) s.leaf = leaf;
-                    else s.hold = leaf;
-                }
-            }
-            if (__builtin_amdgcn_ballot_w64(s.leaf == kRefEmpty && s.node != kRefEmpty) == 0) break;
-        }
-        if (s.leaf != kRefEmpty) {
-            const uint32_t leaf = s.leaf;
-            s.leaf = s.hold;
-            s.hold = kRefEmpty;
-            bin_test_leaf<LeafMode, Mode>(ld, r, leaf, s, ntri);
-        }
+        const uint32_t first = s.leaf >> 5, cnt = ((s.leaf >> 1) & 0xFu) + 1u;
+        const bool ended =
+            wave_test_leaves<LeafMode, Mode>(ld, r, want, first, cnt, s.best, ntri, wl);
+        if (want) bin_tested<Mode>(r, ended, s);
     }
 };
 
@@ -1293,9 +1266,7 @@ struct TracerFor<BVH_LAYOUT_BVH8_Q16> {
     using type = WideTracer<DecodeBVH8Q16>;
 };
 
-// Whole-ray traversal: waves of coherent rays use the two-phase order (their
-// lanes reach nodes and leaves in step, so batching the phases pays); other
-// waves use the single-loop order, which updates the best hit earliest.
+// Whole-ray traversal in one lane.
 template <int Layout, int LeafMode, int Mode, class Stack>
 __device__ inline Best trace_ray(const void *nodes, int64_t n_nodes, const SceneData &ld,
                                  const Ray &r, Stack &st, uint32_t &nfetch, uint32_t &ntri,
@@ -1303,16 +1274,10 @@ __device__ inline Best trace_ray(const void *nodes, int64_t n_nodes, const Scene
     using Tr = typename TracerFor<Layout>::type;
     const typename Tr::Prep prep = Tr::prep(r);
     const bool fast = wave_fast(r);
-    typename Tr::State s = Tr::start(n_nodes);
-    if (wave_coherent(r)) {
-        while (!Tr::done(s))
-            Tr::template round<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, s, nfetch,
-                                               ntri, incomplete);
-    } else {
-        while (!Tr::done(s))
-            Tr::template step<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, s, nfetch,
-                                              ntri, incomplete);
-    }
+    typename Tr::State s = Tr::start(n_nodes, r);
+    while (!Tr::done(s))
+        Tr::template step<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, st, s, nfetch, ntri,
+                                          incomplete);
     return s.best;
 }
 
@@ -1331,8 +1296,7 @@ struct Fallback {
     uint32_t *count;     // rays appended by the fast pass
     unsigned long long *queue;  // queue q's next unclaimed offset at queue + q * kQueueStride bytes
     uint32_t *list;      // ray indices (capacity: rays of the launch)
-    uint32_t *stack_ref; // [kFallbackLanes][kStackMax]
-    float *stack_t;      // [kFallbackLanes][kStackMax]
+    uint64_t *stack;     // [fallback lanes][kStackMax]
 };
 
 // Bytes of the header (counter line, queue lines) that must be zero before a launch.
@@ -1341,19 +1305,18 @@ constexpr size_t kFallbackHeaderBytes = kQueueStride * (1 + kQueues);
 // Bytes of a work area for n_rays rays and `lanes` fallback lanes (the
 // fallback grid's threads).
 constexpr size_t fallback_bytes(uint64_t n_rays, size_t lanes = kFallbackLanes) {
-    return kFallbackHeaderBytes + n_rays * 4 + lanes * kStackMax * 8;
+    return kFallbackHeaderBytes + ((n_rays * 4 + 7) & ~(uint64_t)7) + lanes * kStackMax * 8;
 }
 
-// Carves the work area out of one allocation of fallback_bytes(n_rays, lanes).
-inline Fallback fallback_view(void *base, uint64_t n_rays, size_t lanes = kFallbackLanes) {
+// Carves the work area out of one allocation of fallback_bytes(n_rays, ...).
+inline Fallback fallback_view(void *base, uint64_t n_rays) {
     char *p = static_cast<char *>(base);
     Fallback f;
     f.count = reinterpret_cast<uint32_t *>(p);
     f.queue = reinterpret_cast<unsigned long long *>(p + kQueueStride);
     char *q = p + kFallbackHeaderBytes;
     f.list = reinterpret_cast<uint32_t *>(q);
-    f.stack_ref = reinterpret_cast<uint32_t *>(q + n_rays * 4);
-    f.stack_t = reinterpret_cast<float *>(q + n_rays * 4 + lanes * kStackMax * 4);
+    f.stack = reinterpret_cast<uint64_t *>(q + ((n_rays * 4 + 7) & ~(uint64_t)7));
     return f;
 }
 
@@ -1498,7 +1461,7 @@ inline int32_t trace_area(hipStream_t s, uint64_t n, uint32_t lanes, TraceArea &
     BVH_TRY(stream_workspace(s, kAreaTrace, fb_bytes + sp_bytes, &ws));
     ta.fb = fallback_view(ws, n);
     char *sp = static_cast<char *>(ws) + fb_bytes;
-    ta.sa.ent = reinterpret_cast<uint2 *>(sp);
+    ta.sa.ent = reinterpret_cast<uint64_t *>(sp);
     ta.sa.lanes = lanes;
     ta.sa.cap = kSpillCap;
     BVH_HIP_TRY(hipMemsetAsync(ta.fb.count, 0, kFallbackHeaderBytes, s));
