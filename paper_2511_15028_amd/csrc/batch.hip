@@ -11,7 +11,7 @@
 #include <string>
 #include <vector>
 
-#include "traverse.h"
+#include "coop.h"
 
 namespace bvhlib {
 namespace {
@@ -53,7 +53,6 @@ __device__ inline uint32_t find_scene(const uint32_t *tile_off, uint32_t n, uint
 // rays that outgrow both go to the group's fallback list.  Every wave leaves
 // the loop once the queue is drained and its lanes are idle (no wave ever
 // waits on another), so the grid always drains.
-constexpr uint32_t kNoRay = 0xFFFFFFFFu;
 constexpr uint32_t kNoTile = 0xFFFFFFFFu;
 constexpr uint32_t kBatchRefill = 16;
 constexpr uint32_t kBatchSpillCap = 64;  // spill entries per lane beyond the LDS ring
@@ -65,12 +64,13 @@ __global__ __launch_bounds__(kTraceBlock) void k_batch_trace(const BatchScene *s
                                                              uint32_t total_tiles,
                                                              uint32_t *counter,
                                                              const bvh_ray *rays, bvh_hit *hits,
-                                                             Fallback fb, SpillArea sa) {
+                                                             Deal deal, Fallback fb, SpillArea sa) {
     using Tr = typename TracerFor<Layout>::type;
     __shared__ typename Tr::Entry s_stack[SL * kTraceBlock];
     __shared__ WaveLeafLds s_wl[kWavesPerBlock];
     WaveLeafLds *wl = &s_wl[threadIdx.x >> 6];
     const uint32_t lane = threadIdx.x & 63u;
+    using Finish = FinishRays<Tr, BVH_LEAF_COMPACT, BVH_TRACE_CLOSEST>;
     RingStack<typename Tr::Entry, SL> st(s_stack, sa);
     // per lane
     uint32_t ray = kNoRay;  // ray index within the launch's ray array
@@ -141,6 +141,15 @@ __global__ __launch_bounds__(kTraceBlock) void k_batch_trace(const BatchScene *s
         if (busy == 0) {
             if (drained && pending == kNoTile && pool == pool_end) break;
             continue;
+        }
+        if (drained && pending == kNoTile && pool == pool_end &&
+            __builtin_popcountll(busy) <= deal.items &&
+            __builtin_amdgcn_ballot_w64(ray != kNoRay && (!st.in_ring() || Tr::parked(ts))) == 0) {
+            if (ray != kNoRay && !Tr::done(ts)) st.put(Tr::next(ts), true);
+            Finish f{nodes, n_nodes, sd, rays, hits, fb};
+            coop_finish<Finish, SL>(f, s_stack, ray, st.entries(), ts.best, deal.reserve,
+                                    wl);
+            break;
         }
         if (nidle >= kBatchRefill) {
             coherent = rays_share_octant(r, ray != kNoRay, busy);
@@ -232,7 +241,7 @@ __global__ void k_probe_rays(bvh_ray *out, uint32_t n, float lx, float ly, float
 }
 
 using KernelFn = void (*)(const BatchScene *, const uint32_t *, uint32_t, uint32_t, uint32_t *,
-                          const bvh_ray *, bvh_hit *, Fallback, SpillArea);
+                          const bvh_ray *, bvh_hit *, Deal, Fallback, SpillArea);
 using FallbackFn = void (*)(const BatchScene *, uint32_t, const bvh_ray *, bvh_hit *, Fallback);
 
 FallbackFn fallback_for(int layout) {
@@ -533,6 +542,7 @@ int32_t make_graph(bvh_batch_s *b, const bvh_ray *rays, const int64_t *offsets, 
         uint32_t *ctr = counters + g;
         const bvh_ray *r = rays;
         bvh_hit *hh = hits;
+        Deal deal = deal_of(group_rays, resident * waves_per_block, kv.first.second, kRayReserve);
         // fallback work area of this group (list sized for all its rays),
         // then the per-lane stack spill area of its grid
         const uint32_t lanes = grid * kTraceBlock;
@@ -550,7 +560,7 @@ int32_t make_graph(bvh_batch_s *b, const bvh_ray *rays, const int64_t *offsets, 
         sa.ent = static_cast<uint64_t *>(spill);
         sa.lanes = lanes;
         sa.cap = kBatchSpillCap;
-        void *args[] = {&d_sc, &d_toff, &nsc, (void *)&total, &ctr, &r, &hh, &fb, &sa};
+        void *args[] = {&d_sc, &d_toff, &nsc, (void *)&total, &ctr, &r, &hh, &deal, &fb, &sa};
         hipKernelNodeParams p{};
         p.func = reinterpret_cast<void *>(fn);
         p.gridDim = dim3(grid);

@@ -15,7 +15,7 @@
 // stack for the few queries that outgrow both.
 #include <algorithm>
 
-#include "traverse.h"
+#include "coop.h"
 
 namespace bvhlib {
 namespace {
@@ -310,6 +310,31 @@ __device__ inline void cpq_round(const void *nodes, const SceneData &ld, const Q
 // ---------------------------------------------------------------------------
 template <class Node>
 struct CpqBin {
+    static constexpr int K = 2;
+    // a node (whose box lies within the bound): its children within the bound,
+    // nearer first, or its triangles
+    __device__ static void expand(const void *nodes, const SceneData &ld, const Query &q, float bound,
+                                  uint32_t node, uint64_t *kids, uint32_t &n, uint32_t &first,
+                                  uint32_t &cnt) {
+        float lo[3], hi[3];
+        uint32_t off, axis, c, o;
+        Node::load(nodes, node, ld, lo, hi, cnt, off, axis);
+        first = off;
+        if (cnt > 0) return;
+        const uint32_t at[2] = {node + 1u, node + off};
+        uint64_t e[2];
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            Node::load(nodes, at[k], ld, lo, hi, c, o, axis);
+            const float d = box_d2(q, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2]);
+            const bool keep = d <= bound;
+            e[k] = entry_of(keep ? d : INFINITY, keep ? at[k] : kRefEmpty);
+            n += keep ? 1u : 0u;
+        }
+        order_entries(e[0], e[1]);
+        kids[0] = e[0];
+        kids[1] = e[1];
+    }
     struct State {
         CpqBest best;
         uint32_t cur;       // node to visit next (kRefEmpty: take one from the stack; kRefDone: done)
@@ -489,6 +514,36 @@ template <int Layout>
 struct CpqWide {
     using Ch = WideChildren<Layout>;
     static constexpr int K = Ch::K;
+    // a node or leaf (whose box lies within the bound): its children within
+    // the bound, nearest first, or its triangles
+    __device__ static void expand(const void *nodes, const SceneData &, const Query &q, float bound,
+                                  uint32_t at, uint64_t *kids, uint32_t &n, uint32_t &first,
+                                  uint32_t &cnt) {
+        if ((at & 1u) == 0u) {
+            first = at >> 5;
+            cnt = ((at >> 1) & 0xFu) + 1u;
+            return;
+        }
+        n = measure_children(nodes, at >> 1, q, bound, kids);
+    }
+    // The children of a node within the bound, sorted, and their number.
+    // Culled children sort last: an infinite distance and a reference above
+    // every other (a genuine infinite distance keeps its reference).
+    __device__ static uint32_t measure_children(const void *nodes, uint32_t node, const Query &q,
+                                                float bound, uint64_t *e) {
+        float d[K];
+        uint32_t ref[K];
+        Ch::measure(nodes, node, q, d, ref);
+        uint32_t kept = 0;
+#pragma unroll
+        for (int c = 0; c < K; c++) {
+            const bool keep = ref[c] != kRefEmpty && d[c] <= bound;
+            e[c] = entry_of(keep ? d[c] : INFINITY, keep ? ref[c] : kRefEmpty);
+            kept += keep ? 1u : 0u;
+        }
+        sort_entries<K>(e);
+        return kept;
+    }
     struct State {
         CpqBest best;
         uint32_t cur;  // child reference to visit next (kRefEmpty: take one from the stack; kRefDone: done)
@@ -521,21 +576,9 @@ struct CpqWide {
     template <class Stack>
     __device__ static void visit(const void *nodes, const Query &q, Stack &st, State &s,
                                  uint32_t &nfetch, bool &incomplete) {
-        float d[K];
-        uint32_t ref[K];
-        Ch::measure(nodes, s.cur >> 1, q, d, ref);
-        nfetch++;
-        // culled children sort last: an infinite distance and a reference
-        // above every other (a genuine infinite distance keeps its reference)
         uint64_t e[K];
-        uint32_t kept = 0;
-#pragma unroll
-        for (int c = 0; c < K; c++) {
-            const bool keep = ref[c] != kRefEmpty && d[c] <= s.best.d2;
-            e[c] = entry_of(keep ? d[c] : INFINITY, keep ? ref[c] : kRefEmpty);
-            kept += keep ? 1u : 0u;
-        }
-        sort_entries<K>(e);
+        const uint32_t kept = measure_children(nodes, s.cur >> 1, q, s.best.d2, e);
+        nfetch++;
         if (kept > 1u) {
             if (!st.room(kept - 1u)) {
                 incomplete = true;
@@ -571,28 +614,63 @@ __device__ inline void store_closest(bvh_closest *out, uint64_t i, const CpqBest
     reinterpret_cast<int4 *>(out)[i] = w;
 }
 
-constexpr uint32_t kNoQuery = 0xFFFFFFFFu;
+constexpr uint32_t kNoQuery = kNoRay;
+// LDS stack entries per lane, whatever the handle's: 2^20 queries on the terrain
+// (BVH4) take 5.71 ms with 16, 6.74 with 8 (spills), and 32 would halve the
+// resident waves.
+constexpr int kCpqStack = 16;
 constexpr uint32_t kCpqRefill = 16;  // idle lanes of a wave that trigger a refill
-constexpr uint32_t kCpqClaim = 64;   // queries claimed per chunk
+
+// The queries of one handle, for coop_finish.
+template <class Wk, int LeafMode>
+struct FinishQueries {
+    using Entry = uint64_t;
+    using Best = CpqBest;
+    static constexpr int kChildren = Wk::K;
+    const void *nodes;
+    const SceneData &ld;
+    const bvh_point_query *qs;
+    bvh_closest *out;
+    const Fallback &fb;
+    Query q{};
+    __device__ static float &metric(Best &b) { return b.d2; }
+    __device__ void load(uint32_t item) { q = load_query(qs, item); }
+    __device__ float cull(float d2) const { return d2; }
+    // without a bound no child is culled, so the first triangle is sought depth first
+    __device__ uint32_t breadth(float d2, uint32_t lanes) const { return d2 < INFINITY ? lanes : 1u; }
+    __device__ void expand(Entry x, float bound, Entry *kids, uint32_t &n, uint32_t &first,
+                           uint32_t &cnt) const {
+        if (entry_t(x) <= bound) Wk::expand(nodes, ld, q, bound, entry_ref(x), kids, n, first, cnt);
+    }
+    __device__ bool leaves(bool want, uint32_t first, uint32_t cnt, Best &best, WaveLeafLds *wl) const {
+        uint32_t ntri = 0;
+        while (__builtin_amdgcn_ballot_w64(want) != 0)
+            if (wave_cp_leaves<LeafMode>(ld, q, want, first, cnt, best, ntri, wl)) want = false;
+        return false;
+    }
+    __device__ void store(uint32_t item, const Best &best) const { store_closest(out, item, best); }
+    __device__ void list(uint32_t item) const { fallback_append(fb, item); }
+};
 
 // Persistent kernel: lanes take query after query.  A wave hands new queries
 // to its idle lanes once kCpqRefill of them are idle, from its pool of
 // claimed queries; the first three quarters of the queries are dealt to the
 // waves round-robin in 64-query chunks, the rest is claimed from a queue.
 // Every wave leaves once the queue is drained and its lanes are idle.
-template <int Layout, int LeafMode, bool Count, int SL>
+template <int Layout, int LeafMode, bool Count>
 __global__ __launch_bounds__(kTraceBlock) void k_cpq_persist(const void *nodes, int64_t n_nodes,
                                                              SceneData ld,
                                                              const bvh_point_query *qs,
                                                              uint64_t n, bvh_closest *out,
-                                                             uint32_t *counts, Fallback fb,
-                                                             SpillArea sa) {
+                                                             uint32_t *counts, Deal deal,
+                                                             Fallback fb, SpillArea sa) {
     using Wk = typename CpqFor<Layout>::type;
-    __shared__ uint64_t s_stack[SL * kTraceBlock];
+    __shared__ uint64_t s_stack[kCpqStack * kTraceBlock];
     __shared__ WaveLeafLds s_wl[kWavesPerBlock];
     const uint32_t lane = threadIdx.x & 63u;
     WaveLeafLds *const wl = s_wl + (threadIdx.x >> 6);
-    RingStack<uint64_t, SL> st(s_stack, sa);
+    using Finish = FinishQueries<Wk, LeafMode>;
+    RingStack<uint64_t, kCpqStack> st(s_stack, sa);
     uint32_t qi = kNoQuery;
     Query q{};
     typename Wk::State ws{};
@@ -604,8 +682,10 @@ __global__ __launch_bounds__(kTraceBlock) void k_cpq_persist(const void *nodes, 
     const uint32_t waves = gridDim.x * (kTraceBlock / 64u);
     const uint32_t wave =
         blockIdx.x * (kTraceBlock / 64u) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t static_rounds = (n * 3u / 4u) / ((uint64_t)waves * kCpqClaim);
-    const uint64_t static_end = static_rounds * waves * kCpqClaim;
+    // a launch that gives every wave at most one chunk deals all its queries so
+    const bool one_round = n <= (uint64_t)waves * deal.claim;
+    const uint64_t static_rounds = one_round ? 1u : (n * 3u / 4u) / ((uint64_t)waves * deal.claim);
+    const uint64_t static_end = one_round ? n : static_rounds * waves * deal.claim;
     uint64_t round = 0;
     uint32_t queue = wave % kQueues;  // the wave's current dynamic queue (wave-uniform)
     for (;;) {
@@ -616,10 +696,12 @@ __global__ __launch_bounds__(kTraceBlock) void k_cpq_persist(const void *nodes, 
             uint64_t fresh = 0, fresh_end = 0;  // a newly claimed range
             if (avail < nidle && !drained) {
                 if (round < static_rounds) {
-                    fresh = (round * waves + wave) * kCpqClaim;
-                    fresh_end = fresh + kCpqClaim;
+                    fresh = (round * waves + wave) * deal.claim;
+                    fresh_end = min(fresh + deal.claim, static_end);
+                    fresh = min(fresh, fresh_end);
                     round++;
-                } else if (!claim_dynamic(fb, static_end, n, kCpqClaim,
+                    drained = one_round;
+                } else if (!claim_dynamic(fb, static_end, n, deal.claim,
                                           (uint32_t)__builtin_ctzll(idle), queue, fresh,
                                           fresh_end)) {
                     drained = true;
@@ -654,6 +736,15 @@ __global__ __launch_bounds__(kTraceBlock) void k_cpq_persist(const void *nodes, 
         if (busy == 0) {
             if (drained && pool == pool_end) break;
             continue;
+        }
+        if (!Count && drained && pool == pool_end && __builtin_popcountll(busy) <= deal.items &&
+            __builtin_amdgcn_ballot_w64(qi != kNoQuery && !st.in_ring()) == 0) {
+            // a node or leaf at hand (references below kRefDone) goes on top
+            if (qi != kNoQuery && ws.cur < kRefDone) st.put(entry_of(0.0f, ws.cur), true);
+            Finish f{nodes, ld, qs, out, fb};
+            coop_finish<Finish, kCpqStack>(f, s_stack, qi, st.entries(), ws.best, deal.reserve,
+                                    wl);
+            break;
         }
         cpq_round<Wk, LeafMode>(nodes, ld, q, st, ws, nfetch, ntri, incomplete, wl);
         if (qi != kNoQuery) {
@@ -817,45 +908,49 @@ __global__ __launch_bounds__(kTraceBlock) void k_cpq_slab(const bvh_node_slab *n
     }
 }
 
-template <int Layout, int LeafMode, bool Count, int SL>
+template <int Layout, int LeafMode, bool Count>
 int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_point_query *qs,
                       uint64_t n, bvh_closest *out, uint32_t *counts, hipStream_t s) {
-    auto kernel = k_cpq_persist<Layout, LeafMode, Count, SL>;
+    auto kernel = k_cpq_persist<Layout, LeafMode, Count>;
     unsigned resident = 0;
     BVH_TRY(resident_blocks(kernel, resident));
-    const uint64_t need = (n + kTraceBlock - 1) / kTraceBlock;
+    // as in the ray kernel: few queries are spread over all resident waves
+    const uint64_t waves = (uint64_t)resident * (kTraceBlock / 64);
+    const Deal deal = deal_of(n, waves, kCpqStack, (uint32_t)h->max_stack);
+    const uint64_t need = ((n + deal.claim - 1) / deal.claim + kTraceBlock / 64 - 1) / (kTraceBlock / 64);
     const unsigned grid = (unsigned)std::min<uint64_t>(resident, need);
     TraceArea ta;
     BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
-    kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, qs, n, out, counts, ta.fb, ta.sa);
+    kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, qs, n, out, counts, deal,
+                                        ta.fb, ta.sa);
     k_cpq_fallback<Layout, LeafMode, Count><<<kFallbackBlocks, kTraceBlock, 0, s>>>(
         h->nodes, h->n_nodes, ld, qs, out, counts, ta.fb);
     return BVH_OK;
 }
 
-template <int LeafMode, bool Count, int SL>
-int32_t launch_sl(const bvh_handle_s *h, const SceneData &ld, const bvh_point_query *qs, uint64_t n,
+template <int LeafMode, bool Count>
+int32_t launch_by_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_point_query *qs, uint64_t n,
                   bvh_closest *out, uint32_t *counts, hipStream_t s) {
     switch (h->layout) {
         case BVH_LAYOUT_AABB2:
-            return launch_layout<BVH_LAYOUT_AABB2, LeafMode, Count, SL>(h, ld, qs, n, out, counts, s);
+            return launch_layout<BVH_LAYOUT_AABB2, LeafMode, Count>(h, ld, qs, n, out, counts, s);
         case BVH_LAYOUT_BVH4:
-            return launch_layout<BVH_LAYOUT_BVH4, LeafMode, Count, SL>(h, ld, qs, n, out, counts, s);
+            return launch_layout<BVH_LAYOUT_BVH4, LeafMode, Count>(h, ld, qs, n, out, counts, s);
         case BVH_LAYOUT_BVH8_Q8:
-            return launch_layout<BVH_LAYOUT_BVH8_Q8, LeafMode, Count, SL>(h, ld, qs, n, out, counts, s);
+            return launch_layout<BVH_LAYOUT_BVH8_Q8, LeafMode, Count>(h, ld, qs, n, out, counts, s);
         case BVH_LAYOUT_PBRT_Q16:
-            return launch_layout<BVH_LAYOUT_PBRT_Q16, LeafMode, Count, SL>(h, ld, qs, n, out, counts, s);
+            return launch_layout<BVH_LAYOUT_PBRT_Q16, LeafMode, Count>(h, ld, qs, n, out, counts, s);
         case BVH_LAYOUT_SG_EQ:
-            return launch_layout<BVH_LAYOUT_SG_EQ, LeafMode, Count, SL>(h, ld, qs, n, out, counts, s);
+            return launch_layout<BVH_LAYOUT_SG_EQ, LeafMode, Count>(h, ld, qs, n, out, counts, s);
         case BVH_LAYOUT_PBRT_SOAOS:
-            return launch_layout<BVH_LAYOUT_PBRT_SOAOS, LeafMode, Count, SL>(h, ld, qs, n, out, counts, s);
+            return launch_layout<BVH_LAYOUT_PBRT_SOAOS, LeafMode, Count>(h, ld, qs, n, out, counts, s);
         case BVH_LAYOUT_PBRT_Q16_SOAOS:
-            return launch_layout<BVH_LAYOUT_PBRT_Q16_SOAOS, LeafMode, Count, SL>(h, ld, qs, n, out,
+            return launch_layout<BVH_LAYOUT_PBRT_Q16_SOAOS, LeafMode, Count>(h, ld, qs, n, out,
                                                                                 counts, s);
         case BVH_LAYOUT_SG_EQ_A16:
-            return launch_layout<BVH_LAYOUT_SG_EQ_A16, LeafMode, Count, SL>(h, ld, qs, n, out, counts, s);
+            return launch_layout<BVH_LAYOUT_SG_EQ_A16, LeafMode, Count>(h, ld, qs, n, out, counts, s);
         default:
-            return launch_layout<BVH_LAYOUT_BVH8_Q16, LeafMode, Count, SL>(h, ld, qs, n, out, counts, s);
+            return launch_layout<BVH_LAYOUT_BVH8_Q16, LeafMode, Count>(h, ld, qs, n, out, counts, s);
     }
 }
 
@@ -872,14 +967,7 @@ int32_t launch_mode(const bvh_handle_s *h, const bvh_point_query *qs, uint64_t n
             k_cpq_slab<LeafMode, Count><<<grid, kTraceBlock, 0, s>>>(
                 static_cast<const bvh_node_slab *>(h->nodes), h->n_nodes, ld, qs, n, out, counts, cs);
     } else {
-        // every stack entry carries a distance, so the LDS ring holds at most
-        // 16 entries per lane (32 would halve the resident waves); left at its
-        // default, the wide layouts (whose kernel also holds the batched leaf
-        // state in LDS) take 8, one more resident block per CU: 3-6 % faster
-        // than 16 on the terrain and the spheres scene
-        const bool eight = h->stack_lds == 8 || (h->stack_lds_default && h->arity > 2);
-        rc = eight ? launch_sl<LeafMode, Count, 8>(h, ld, qs, n, out, counts, s)
-                   : launch_sl<LeafMode, Count, 16>(h, ld, qs, n, out, counts, s);
+        rc = launch_by_layout<LeafMode, Count>(h, ld, qs, n, out, counts, s);
     }
     if (rc != BVH_OK) return rc;
     const hipError_t e = hipGetLastError();

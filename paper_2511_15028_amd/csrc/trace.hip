@@ -3,7 +3,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "traverse.h"
+#include "coop.h"
 
 namespace bvhlib {
 namespace {
@@ -22,20 +22,19 @@ namespace {
 // area in global memory that the lane owns for the launch; rays that outgrow
 // both go to the fallback pass.  Every wave leaves the loop once the queue is
 // drained and its lanes are idle, so the grid always drains.
-constexpr uint32_t kNoRay = 0xFFFFFFFFu;
 constexpr uint32_t kRefillLanes = 16;  // idle lanes of a wave that trigger a refill
-constexpr uint32_t kClaim = 64;        // rays claimed from the queue per atomic
 
 template <int Layout, int LeafMode, int Mode, bool Count, int SL>
 __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes, int64_t n_nodes,
                                                                SceneData ld, const bvh_ray *rays,
                                                                uint64_t n, bvh_hit *hits,
-                                                               uint32_t *counts, Fallback fb,
-                                                               SpillArea sa) {
+                                                               uint32_t *counts, Deal deal,
+                                                               Fallback fb, SpillArea sa) {
     using Tr = typename TracerFor<Layout>::type;
     __shared__ typename Tr::Entry s_stack[SL * kTraceBlock];
     __shared__ WaveLeafLds s_wl[kWavesPerBlock];
     WaveLeafLds *wl = &s_wl[threadIdx.x >> 6];
+    using Finish = FinishRays<Tr, LeafMode, Mode>;
     RingStack<typename Tr::Entry, SL> st(s_stack, sa);
     uint32_t ray = kNoRay;
     Ray r{};
@@ -50,8 +49,10 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
     const uint32_t waves = gridDim.x * (kTraceBlock / 64u);
     const uint32_t wave =  // the same in every lane: keep it scalar
         blockIdx.x * (kTraceBlock / 64u) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t static_rounds = (n * 3u / 4u) / ((uint64_t)waves * kClaim);
-    const uint64_t static_end = static_rounds * waves * kClaim;
+    // a launch that gives every wave at most one chunk deals all its rays so
+    const bool one_round = n <= (uint64_t)waves * deal.claim;
+    const uint64_t static_rounds = one_round ? 1u : (n * 3u / 4u) / ((uint64_t)waves * deal.claim);
+    const uint64_t static_end = one_round ? n : static_rounds * waves * deal.claim;
     uint64_t round = 0;  // static chunks taken by this wave
     uint32_t queue = wave % kQueues;  // the wave's current dynamic queue (wave-uniform)
     bool coherent = true;  // the wave's rays at its last refill all pointed into one octant
@@ -65,10 +66,12 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
             uint64_t fresh = 0, fresh_end = 0;  // a newly claimed range
             if (avail < nidle && !drained) {
                 if (round < static_rounds) {
-                    fresh = (round * waves + wave) * kClaim;
-                    fresh_end = fresh + kClaim;
+                    fresh = (round * waves + wave) * deal.claim;
+                    fresh_end = min(fresh + deal.claim, static_end);
+                    fresh = min(fresh, fresh_end);
                     round++;
-                } else if (!claim_dynamic(fb, static_end, n, kClaim,
+                    drained = one_round;
+                } else if (!claim_dynamic(fb, static_end, n, deal.claim,
                                           (uint32_t)__builtin_ctzll(idle), queue, fresh,
                                           fresh_end)) {
                     drained = true;
@@ -109,6 +112,15 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
             coherent = rays_share_octant(r, ray != kNoRay, busy);
             fast = __builtin_amdgcn_ballot_w64(ray != kNoRay && !r.fast) == 0;
         } else if (nidle == 64u) {
+            break;
+        }
+        if (!Count && drained && pool == pool_end &&
+            __builtin_popcountll(__builtin_amdgcn_ballot_w64(ray != kNoRay)) <= deal.items &&
+            __builtin_amdgcn_ballot_w64(ray != kNoRay && (!st.in_ring() || Tr::parked(ts))) == 0) {
+            if (ray != kNoRay && !Tr::done(ts)) st.put(Tr::next(ts), true);
+            Finish f{nodes, n_nodes, ld, rays, hits, fb};
+            coop_finish<Finish, SL>(f, s_stack, ray, st.entries(), ts.best, deal.reserve,
+                                    wl);
             break;
         }
         Tr::template wave<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, coherent, st, ts, wl,
@@ -256,18 +268,22 @@ static_assert(kNoAllocMaxRays == BVH_NOALLOC_MAX_RAYS, "bvh.h states the limit")
 template <int Layout, int LeafMode, int Mode, bool Count, int SL>
 int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_ray *rays, uint64_t n,
                       bvh_hit *hits, uint32_t *counts, const Fallback *fixed, hipStream_t s) {
-    const uint64_t need = (n + kTraceBlock - 1) / kTraceBlock;
     auto kernel = k_trace_persist<Layout, LeafMode, Mode, Count, SL>;
     unsigned resident = 0;
     BVH_TRY(resident_blocks(kernel, resident));
+    // fewer rays than lanes: spread over all the waves that the GPU holds, a
+    // few to each, so that the waves finish them together (coop.h)
+    const uint64_t waves = (uint64_t)resident * (kTraceBlock / 64);
+    const Deal deal = deal_of(n, waves, SL, kRayReserve);
+    const uint64_t need = ((n + deal.claim - 1) / deal.claim + kTraceBlock / 64 - 1) / (kTraceBlock / 64);
     const unsigned grid = (unsigned)std::min<uint64_t>(resident, need);
     TraceArea ta;
     if (fixed)
         ta = TraceArea{*fixed, SpillArea{nullptr, grid * kTraceBlock, 0}};
     else
         BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
-    kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, rays, n, hits, counts, ta.fb,
-                                        ta.sa);
+    kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, rays, n, hits, counts, deal,
+                                        ta.fb, ta.sa);
     k_trace_fallback<Layout, LeafMode, Mode, Count>
         <<<fixed ? kFixedFallbackBlocks : kFallbackBlocks, kTraceBlock, 0, s>>>(
             h->nodes, h->n_nodes, ld, rays, hits, counts, ta.fb);

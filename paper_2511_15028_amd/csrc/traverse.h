@@ -478,6 +478,9 @@ struct RingStack {
                                       ((at & ((SL - 1) * kStep)) | (threadIdx.x * (uint32_t)sizeof(E))));
     }
     __device__ void reset() { sp = lo = 0; }
+    __device__ uint32_t entries() const { return sp / kStep; }
+    // all entries lie in the ring, from its first slot on, with room for one more
+    __device__ bool in_ring() const { return lo == 0 && sp < SL * kStep; }
     // the lane's spill run (the lane's index in the grid), as entries of type E
     __device__ E *run() const {
         return reinterpret_cast<E *>(area.ent + ((size_t)blockIdx.x * kTraceBlock + threadIdx.x) * area.cap);
@@ -1097,6 +1100,34 @@ __device__ inline void wide_test_parked(const SceneData &ld, const Ray &r, Stack
     wide_recull(st, ws);
 }
 
+// Visits one stack entry by itself: an interior node's children that the ray
+// meets, near-first, in kids[0..n), or a leaf's reference.
+template <class Dec>
+__device__ inline void wide_expand(const void *nodes, uint32_t last, const Ray &r,
+                                   const typename Dec::Prep &prep, bool fast, float cull,
+                                   uint64_t entry, uint64_t *kids, uint32_t &n, uint32_t &leaf) {
+    if (!(entry_t(entry) <= cull)) return;
+    if (!(entry_ref(entry) & 1u)) {
+        leaf = entry_ref(entry);
+        return;
+    }
+    constexpr int K = Dec::K;
+    float tn[K];
+    uint32_t ref[K];
+    u32x4 m[Dec::kWords];
+    Dec::fetch(nodes, min(entry_ref(entry) >> 1, last), prep, m);
+    if (fast)
+        Dec::template test<true>(m, r, cull, tn, ref);
+    else
+        Dec::template test<false>(m, r, cull, tn, ref);
+#pragma unroll
+    for (int c = 0; c < K; c++) {
+        kids[c] = entry_of(tn[c], ref[c]);
+        n += tn[c] != INFINITY ? 1u : 0u;
+    }
+    sort_entries<K>(kids);
+}
+
 // One round of the two-phase order (the while-while scheme of Aila and Laine
 // 2009, with speculative traversal), called by every lane of the wave (lanes
 // without a ray hold kRefDone), so that the lanes test nodes together and
@@ -1147,7 +1178,9 @@ __device__ inline void wide_round(const void *nodes, uint32_t last, const SceneD
 //   Entry               stack entry (a reference, or one with its distance)
 //   Prep prep(ray)      per-ray layout constants
 //   State start(nodes, ray), none()   a ray's initial state, that of no ray
-//   done(state)
+//   done(state); parked(state): a leaf waits to be tested; next(state): the
+//                       entry a ray under way visits next
+//   kChildren, expand(...)      the children of one stack entry, or its leaf
 //   step<LeafMode, Mode>(...)   one advance of a lane on its own, and its leaf
 //   wave<LeafMode, Mode>(...)   one round of the wave: every lane calls it,
 //                               lanes without a ray with the state none()
@@ -1161,6 +1194,14 @@ struct WideTracer {
     __device__ static State start(int64_t n_nodes, const Ray &r) { return wide_start(n_nodes, r); }
     __device__ static State none() { return wide_start(0, Ray{}); }
     __device__ static bool done(const State &s) { return !s.live() && s.leaf == kRefDone; }
+    __device__ static bool parked(const State &s) { return s.leaf != kRefDone; }
+    __device__ static Entry next(const State &s) { return s.cur; }
+    static constexpr int kChildren = Dec::K;
+    __device__ static void expand(const void *nodes, int64_t n_nodes, const SceneData &,
+                                  const Ray &r, const Prep &prep, bool fast, float cull, Entry e,
+                                  Entry *kids, uint32_t &n, uint32_t &leaf) {
+        wide_expand<Dec>(nodes, (uint32_t)n_nodes - 1u, r, prep, fast, cull, e, kids, n, leaf);
+    }
     template <int LeafMode, int Mode, class Stack>
     __device__ static void step(const void *nodes, int64_t n_nodes, const SceneData &ld,
                                 const Ray &r, const Prep &prep, bool fast, Stack &st, State &s,
@@ -1192,6 +1233,28 @@ struct BinTracer {
     __device__ static State start(int64_t n_nodes, const Ray &r) { return bin_start(n_nodes, r); }
     __device__ static State none() { return bin_start(0, Ray{}); }
     __device__ static bool done(const State &s) { return s.node == kRefEmpty && s.leaf == kRefEmpty; }
+    __device__ static bool parked(const State &s) { return s.leaf != kRefEmpty; }
+    __device__ static Entry next(const State &s) { return s.node; }
+    static constexpr int kChildren = 2;
+    __device__ static void expand(const void *nodes, int64_t n_nodes, const SceneData &ld,
+                                  const Ray &r, const Prep &, bool fast, float cull, Entry e,
+                                  Entry *kids, uint32_t &n, uint32_t &leaf) {
+        const uint32_t at = min(e, (uint32_t)n_nodes - 1u);  // bounds guard; equal on a valid tree
+        float lo[3], hi[3];
+        uint32_t cnt = 0, off = 0, axis = 0;
+        Node::load(nodes, at, ld, lo, hi, cnt, off, axis);
+        const float tn = fast ? slab<true>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], cull)
+                              : slab<false>(r, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], cull);
+        if (tn == INFINITY) return;
+        if (cnt > 0) {
+            leaf = ref_leaf(off, cnt);
+            return;
+        }
+        const bool neg = axis == 0 ? r.nx : (axis == 1 ? r.ny : (axis == 2 ? r.nz : false));
+        kids[0] = neg ? at + off : at + 1u;
+        kids[1] = neg ? at + 1u : at + off;
+        n = 2;
+    }
     template <int LeafMode, int Mode, class Stack>
     __device__ static void step(const void *nodes, int64_t n_nodes, const SceneData &ld,
                                 const Ray &r, const Prep &, bool fast, Stack &st, State &s,
@@ -1280,6 +1343,8 @@ __device__ inline Best trace_ray(const void *nodes, int64_t n_nodes, const Scene
                                           incomplete);
     return s.best;
 }
+
+constexpr uint32_t kNoRay = 0xFFFFFFFFu;  // ray index of an idle lane
 
 // Work area of the fallback pass: a counter and list of rays that
 // overflowed the LDS stack, and one deep stack per fallback lane.
