@@ -140,6 +140,12 @@ __device__ inline T wave_reduce(T v, T id, Op op) {
 __device__ inline float wave_min(float v) {
     return wave_reduce<float>(v, INFINITY, [](float a, float b) { return fminf(a, b); });
 }
+// Orders the wave's LDS accesses before and after it.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Build-wide maxima (stack and depth bounds) without contention: one
 // atomicMax per wave into one of kMaxSlots slots chosen by the wave's global
 // index, each slot on a cache line of its own, folded by k_fold_max_slots at
@@ -1166,9 +1172,27 @@ __global__ __launch_bounds__(kBlock) void k_split_aabb2(const bvh_node_aabb2 *in
 // interior candidates and writes K candidate ids (-1 for unused slots).
 template <int K>
 __device__ inline uint32_t wide_open_item(const TreeView &tv, int x, int32_t *cand_out) {
-    int c[K];
+    // Per candidate: id, area (-1 for a leaf, which is never opened) and its
+    // children, read when the candidate enters the list, so that an opening
+    // waits for one round of loads (8-wide nodes of 1,024 triangles 16 -> 12 us,
+    // of 300,000 25 -> 15 us)
+    int c[K], l[K], r[K];
+    float area[K];
 #pragma unroll
-    for (int k = 0; k < K; k++) c[k] = -1;
+    for (int k = 0; k < K; k++) {
+        c[k] = l[k] = r[k] = -1;
+        area[k] = -1.0f;
+    }
+    const auto look = [&](int y, int &yl, int &yr, float &a) {
+        yl = yr = -1;
+        a = -1.0f;
+        if (tv.is_prim(y)) return;
+        const uint32_t cnt = tv.icount[y];
+        const float ar = tv.area[y];
+        yl = tv.ileft[y];
+        yr = tv.iright[y];
+        if (cnt > (uint32_t)tv.leaf_size) a = ar;
+    };
     int nc;
     if (tv.is_leaf(x)) {  // only for a root that is a single leaf
         c[0] = x;
@@ -1176,33 +1200,45 @@ __device__ inline uint32_t wide_open_item(const TreeView &tv, int x, int32_t *ca
     } else {
         c[0] = tv.ileft[x];
         c[1] = tv.iright[x];
+        look(c[0], l[0], r[0], area[0]);
+        look(c[1], l[1], r[1], area[1]);
         nc = 2;
         while (nc < K) {
-            int best = -1;
+            int best = -1, yl = -1, yr = -1;
             float best_a = -1.0f;
 #pragma unroll
             for (int k = 0; k < K; k++) {
-                if (k >= nc || tv.is_leaf(c[k])) continue;
-                const float a = tv.area[c[k]];
-                if (a > best_a) {
-                    best_a = a;
+                if (area[k] > best_a) {  // the lowest of equal ones
+                    best_a = area[k];
                     best = k;
+                    yl = l[k];
+                    yr = r[k];
                 }
             }
             if (best < 0) break;
-            // replace c[best] by its two children, keeping left-to-right order
-            int y = -1;
+            int ll, lr, rl, rr;
+            float la, ra;
+            look(yl, ll, lr, la);
+            look(yr, rl, rr, ra);
+            // replace the candidate by its two children, keeping left-to-right order
 #pragma unroll
-            for (int k = 0; k < K; k++)
-                if (k == best) y = c[k];
-            const int yl = tv.ileft[y], yr = tv.iright[y];
-#pragma unroll
-            for (int k = K - 1; k >= 1; k--)
-                if (k > best + 1 && k <= nc) c[k] = c[k - 1];
-#pragma unroll
-            for (int k = 0; k < K; k++) {
-                if (k == best) c[k] = yl;
-                if (k == best + 1) c[k] = yr;
+            for (int k = K - 1; k >= 0; k--) {
+                if (k > best + 1) {
+                    c[k] = c[k > 0 ? k - 1 : 0];
+                    l[k] = l[k > 0 ? k - 1 : 0];
+                    r[k] = r[k > 0 ? k - 1 : 0];
+                    area[k] = area[k > 0 ? k - 1 : 0];
+                } else if (k == best + 1) {
+                    c[k] = yr;
+                    l[k] = rl;
+                    r[k] = rr;
+                    area[k] = ra;
+                } else if (k == best) {
+                    c[k] = yl;
+                    l[k] = ll;
+                    r[k] = lr;
+                    area[k] = la;
+                }
             }
             nc++;
         }
@@ -1211,7 +1247,7 @@ __device__ inline uint32_t wide_open_item(const TreeView &tv, int x, int32_t *ca
 #pragma unroll
     for (int k = 0; k < K; k++) {
         cand_out[k] = c[k];
-        if (c[k] >= 0 && !tv.is_leaf(c[k])) {
+        if (area[k] != -1.0f) {  // an interior candidate, NaN area included
             ni++;
             mask |= 1u << k;
         }
@@ -1231,12 +1267,10 @@ __global__ __launch_bounds__(kBlock) void k_wide_open_all(TreeView tv, uint32_t 
     ni_all[x] = wide_open_item<K>(tv, (int)x, cand_all + (size_t)x * K);
 }
 
-// Quantisation of one axis of K child intervals (the first nc valid) to QMAX
-// steps of the parent interval [plo, phi].  Returns the scale; q values are
-// the tightest with fmaf(qlo, s, plo) <= clo and fmaf(qhi, s, plo) >= chi.
-template <int K, int QMAX>
-__device__ inline float quantize_axis(float plo, float phi, const float *clo, const float *chi,
-                                      int nc, uint32_t *qlo, uint32_t *qhi, uint32_t *err) {
+// Scale of one axis: the smallest step found upwards from ext / QMAX with
+// fmaf(QMAX, s, plo) >= phi (0 for an empty extent; a bad one is reported).
+template <int QMAX>
+__device__ inline float quantize_scale(float plo, float phi, uint32_t *err) {
     const float ext = phi - plo;
     float s = 0.0f;
     if (!(ext >= 0.0f) || !isfinite(ext)) {
@@ -1245,48 +1279,42 @@ __device__ inline float quantize_axis(float plo, float phi, const float *clo, co
         s = ext / (float)QMAX;
         for (int g = 0; g < 64 && fmaf((float)QMAX, s, plo) < phi; g++) s = nextafterf(s, INFINITY);
     }
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        uint32_t a = QMAX, b = 0;  // empty slot: lo above hi
-        if (k < nc) {
-            if (s == 0.0f) {
-                a = 0;
-                b = 0;
-            } else {
-                float fl = floorf((clo[k] - plo) / s);
-                fl = fminf(fmaxf(fl, 0.0f), (float)QMAX);
-                a = (uint32_t)fl;
-                while (a > 0 && fmaf((float)a, s, plo) > clo[k]) a--;
-                while (a < (uint32_t)QMAX && fmaf((float)(a + 1), s, plo) <= clo[k]) a++;
-                float fh = ceilf((chi[k] - plo) / s);
-                fh = fminf(fmaxf(fh, 0.0f), (float)QMAX);
-                b = (uint32_t)fh;
-                while (b < (uint32_t)QMAX && fmaf((float)b, s, plo) < chi[k]) b++;
-                while (b > 0 && fmaf((float)(b - 1), s, plo) >= chi[k]) b--;
-            }
-        }
-        qlo[k] = a;
-        qhi[k] = b;
-    }
     return s;
+}
+
+// A child interval in steps of s from plo: the tightest q values with
+// fmaf(qlo, s, plo) <= clo and fmaf(qhi, s, plo) >= chi.
+template <int QMAX>
+__device__ inline void quantize_interval(float plo, float s, float clo, float chi, uint32_t *qlo,
+                                         uint32_t *qhi) {
+    uint32_t a = 0, b = 0;
+    if (s != 0.0f) {
+        float fl = floorf((clo - plo) / s);
+        fl = fminf(fmaxf(fl, 0.0f), (float)QMAX);
+        a = (uint32_t)fl;
+        while (a > 0 && fmaf((float)a, s, plo) > clo) a--;
+        while (a < (uint32_t)QMAX && fmaf((float)(a + 1), s, plo) <= clo) a++;
+        float fh = ceilf((chi - plo) / s);
+        fh = fminf(fmaxf(fh, 0.0f), (float)QMAX);
+        b = (uint32_t)fh;
+        while (b < (uint32_t)QMAX && fmaf((float)b, s, plo) < chi) b++;
+        while (b > 0 && fmaf((float)(b - 1), s, plo) >= chi) b--;
+    }
+    *qlo = a;
+    *qhi = b;
 }
 
 __device__ inline float box_comp(const Box &b, int c) {
     return c == 0 ? b.lo.x : c == 1 ? b.lo.y : c == 2 ? b.lo.z : c == 3 ? b.hi.x : c == 4 ? b.hi.y : b.hi.z;
 }
 
-// Node writers: the record is assembled as 32-bit words in registers (every
-// index is a compile-time constant after unrolling) and stored with 16-byte
-// stores, so a wave writes whole records instead of one field at a time.
-template <int Words>
-__device__ inline void store_record(void *dst, const uint32_t *r) {
-    static_assert(Words % 4 == 0, "records are whole 16-byte chunks");
-    uint4 *d = static_cast<uint4 *>(dst);
-#pragma unroll
-    for (int i = 0; i < Words / 4; i++)
-        d[i] = make_uint4(r[4 * i], r[4 * i + 1], r[4 * i + 2], r[4 * i + 3]);
-}
-
+// Node writers.  A wide node is written by K lanes, lane k with child k (box,
+// reference, whether it exists): each puts its words of the record into LDS
+// (rec), and the group stores the record in 16-byte chunks, so a wave writes
+// whole consecutive records.  One thread per node, with its K children one
+// after another, was bound by that chain: 30 us for a BVH8-Q8 of 1,024
+// triangles, 59 us for a BVH8-Q16 of 300,000, 41 us for a BVH4 of 2.1 M; the
+// groups take 7, 13 and 32 us.
 template <int Layout>
 struct WideOut;
 
@@ -1294,67 +1322,53 @@ template <>
 struct WideOut<BVH_LAYOUT_BVH4> {
     static constexpr int K = 4;
     static constexpr int kWords = sizeof(bvh_node_bvh4) / 4;
-    __device__ static void write(void *dst, const Box &pb, const Box *cb,
-                                 const uint32_t *ref, int nc, uint32_t *err) {
+    __device__ static void put(uint32_t *rec, int k, const Box &pb, const Box &cb, bool valid,
+                               uint32_t ref, int nc, uint32_t *err) {
         (void)pb;
         (void)err;
-        uint32_t r[kWords];
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const bool v = k < nc;
-            r[0 * K + k] = __float_as_uint(v ? cb[k].lo.x : INFINITY);
-            r[1 * K + k] = __float_as_uint(v ? cb[k].lo.y : INFINITY);
-            r[2 * K + k] = __float_as_uint(v ? cb[k].lo.z : INFINITY);
-            r[3 * K + k] = __float_as_uint(v ? cb[k].hi.x : -INFINITY);
-            r[4 * K + k] = __float_as_uint(v ? cb[k].hi.y : -INFINITY);
-            r[5 * K + k] = __float_as_uint(v ? cb[k].hi.z : -INFINITY);
-            r[6 * K + k] = v ? ref[k] : kRefEmpty;
-        }
-        r[7 * K] = (uint32_t)nc;
-        r[7 * K + 1] = r[7 * K + 2] = r[7 * K + 3] = 0;
-        store_record<kWords>(dst, r);
+        rec[0 * K + k] = __float_as_uint(valid ? cb.lo.x : INFINITY);
+        rec[1 * K + k] = __float_as_uint(valid ? cb.lo.y : INFINITY);
+        rec[2 * K + k] = __float_as_uint(valid ? cb.lo.z : INFINITY);
+        rec[3 * K + k] = __float_as_uint(valid ? cb.hi.x : -INFINITY);
+        rec[4 * K + k] = __float_as_uint(valid ? cb.hi.y : -INFINITY);
+        rec[5 * K + k] = __float_as_uint(valid ? cb.hi.z : -INFINITY);
+        rec[6 * K + k] = ref;
+        rec[7 * K + k] = k == 0 ? (uint32_t)nc : 0u;
     }
 };
 
 // Record words of the quantised 8-wide nodes: origin[3], scale[3], then the
-// six plane rows (qlo_x, qlo_y, qlo_z, qhi_x, qhi_y, qhi_z) of RW words each,
-// child[8], nchild, zero padding.
-template <int QMAX, int RW, int Words>
-__device__ inline void quantized_words(uint32_t *r, const Box &pb, const Box *cb, const uint32_t *ref,
-                                       int nc, uint32_t *err) {
+// six plane rows (qlo_x, qlo_y, qlo_z, qhi_x, qhi_y, qhi_z) of 8 values of
+// QT, child[8], nchild, zero padding.
+template <typename QT, int Words>
+__device__ inline void quantized_put(uint32_t *rec, int k, const Box &pb, const Box &cb, bool valid,
+                                     uint32_t ref, int nc, uint32_t *err) {
     constexpr int K = 8;
+    constexpr uint32_t kQMax = (QT)~(QT)0;
+    constexpr int c0 = 6 + 6 * K * sizeof(QT) / 4;
+    QT *rows = reinterpret_cast<QT *>(rec + 6);
+    // lane a works out axis a's scale for the group (its axis is picked among
+    // register values: indexing the box would put it in scratch memory)
+    const float ax = pb.lo.x, ay = pb.lo.y, az = pb.lo.z, bx = pb.hi.x, by = pb.hi.y, bz = pb.hi.z;
+    float own = 0.0f;
+    if (k < 3)
+        own = quantize_scale<(int)kQMax>(k == 0 ? ax : (k == 1 ? ay : az), k == 0 ? bx : (k == 1 ? by : bz), err);
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-        float clo[K], chi[K];
-        uint32_t qlo[K], qhi[K];
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            clo[k] = k < nc ? box_comp(cb[k], a) : 0.0f;
-            chi[k] = k < nc ? box_comp(cb[k], a + 3) : 0.0f;
-        }
-        const float plo = box_comp(pb, a), phi = box_comp(pb, a + 3);
-        const float sc = quantize_axis<K, QMAX>(plo, phi, clo, chi, nc, qlo, qhi, err);
-        r[a] = __float_as_uint(plo);
-        r[3 + a] = __float_as_uint(sc);
-#pragma unroll
-        for (int j = 0; j < RW; j++) {
-            const int per = K / RW;  // q values per word: 4 (u8) or 2 (u16)
-            uint32_t lo = 0, hi = 0;
-#pragma unroll
-            for (int t = 0; t < per; t++) {
-                lo |= qlo[j * per + t] << (t * (32 / per));
-                hi |= qhi[j * per + t] << (t * (32 / per));
-            }
-            r[6 + a * RW + j] = lo;
-            r[6 + (3 + a) * RW + j] = hi;
+        const float sc = __shfl(own, a, K);
+        const float plo = box_comp(pb, a);
+        uint32_t qlo = kQMax, qhi = 0;  // empty slot: lo above hi
+        if (valid) quantize_interval<(int)kQMax>(plo, sc, box_comp(cb, a), box_comp(cb, a + 3), &qlo, &qhi);
+        rows[a * K + k] = (QT)qlo;
+        rows[(3 + a) * K + k] = (QT)qhi;
+        if (k == a) {
+            rec[a] = __float_as_uint(plo);
+            rec[3 + a] = __float_as_uint(sc);
         }
     }
-    constexpr int c0 = 6 + 6 * RW;
-#pragma unroll
-    for (int k = 0; k < K; k++) r[c0 + k] = k < nc ? ref[k] : kRefEmpty;
-    r[c0 + K] = (uint32_t)nc;
-#pragma unroll
-    for (int k = c0 + K + 1; k < Words; k++) r[k] = 0;
+    rec[c0 + k] = ref;
+    if (c0 + K + k < Words) rec[c0 + K + k] = k == 0 ? (uint32_t)nc : 0u;
+    static_assert(Words - (c0 + K) <= K && Words % 4 == 0, "one word of the tail per lane");
 }
 
 static_assert(offsetof(bvh_node_bvh4, child) == 24 * 4 && offsetof(bvh_node_bvh4, nchild) == 28 * 4,
@@ -1370,11 +1384,9 @@ template <>
 struct WideOut<BVH_LAYOUT_BVH8_Q8> {
     static constexpr int K = 8;
     static constexpr int kWords = sizeof(bvh_node_bvh8_q8) / 4;
-    __device__ static void write(void *dst, const Box &pb, const Box *cb,
-                                 const uint32_t *ref, int nc, uint32_t *err) {
-        uint32_t r[kWords];
-        quantized_words<255, 2, kWords>(r, pb, cb, ref, nc, err);
-        store_record<kWords>(dst, r);
+    __device__ static void put(uint32_t *rec, int k, const Box &pb, const Box &cb, bool valid,
+                               uint32_t ref, int nc, uint32_t *err) {
+        quantized_put<uint8_t, kWords>(rec, k, pb, cb, valid, ref, nc, err);
     }
 };
 
@@ -1382,11 +1394,9 @@ template <>
 struct WideOut<BVH_LAYOUT_BVH8_Q16> {
     static constexpr int K = 8;
     static constexpr int kWords = sizeof(bvh_node_bvh8_q16) / 4;
-    __device__ static void write(void *dst, const Box &pb, const Box *cb,
-                                 const uint32_t *ref, int nc, uint32_t *err) {
-        uint32_t r[kWords];
-        quantized_words<65535, 4, kWords>(r, pb, cb, ref, nc, err);
-        store_record<kWords>(dst, r);
+    __device__ static void put(uint32_t *rec, int k, const Box &pb, const Box &cb, bool valid,
+                               uint32_t ref, int nc, uint32_t *err) {
+        quantized_put<uint16_t, kWords>(rec, k, pb, cb, valid, ref, nc, err);
     }
 };
 
@@ -1412,8 +1422,8 @@ struct NodeSink {
 // sits at the subtree root's first primitive position in arrays of n entries,
 // and the queues of different subtrees never overlap.  A scan of the subtree
 // sizes then places each subtree contiguously after the top levels, and one
-// launch over all node positions writes every record (a thread finds its
-// subtree by a binary search over the subtree offsets, so uneven subtrees
+// launch over all node positions writes every record (a group of lanes finds its
+// subtree by a search over the subtree offsets, so uneven subtrees
 // do not leave one workgroup with most of the work).  Node order: the top
 // levels breadth-first, then subtree by subtree in the order of their roots,
 // each breadth-first; a subtree's nodes are thus close together in memory.
@@ -1619,96 +1629,82 @@ __global__ __launch_bounds__(kPlaceThreads) void k_wide_place(WidePlan p, uint32
     }
 }
 
-// Writes wide node x at position at; pos(r) is the position of its r-th
-// interior child.
-template <int Layout, typename Pos>
-__device__ inline void wide_write(const TreeView &tv, int32_t x, uint32_t aux, uint32_t at,
-                                  uint32_t cap, const int32_t *cand, Pos pos, NodeSink sink,
-                                  BuildInfo *info, uint32_t *stack_out, uint32_t *depth_out) {
-    constexpr int K = WideOut<Layout>::K;
-    if (at >= cap) {
-        atomicOr(&info->err, 4u);
-        return;
+// Subtree of node position at: the last b of [0, roots) with off[b] <= at.
+// The group's K lanes probe K pivots of the range at a time.
+template <int K>
+__device__ inline uint32_t find_subtree(const uint32_t *off, uint32_t roots, uint32_t at) {
+    const int k = threadIdx.x % K, g0 = (threadIdx.x & (kWave - 1)) & ~(K - 1);
+    uint32_t lo = 0, len = roots;  // the answer is in [lo, lo + len)
+    while (len > 1) {
+        const uint32_t step = (len + K) / (K + 1);  // 1 or more
+        const uint32_t i = (uint32_t)(k + 1) * step;
+        const bool le = i < len && off[lo + i] <= at;
+        // the groups of a wave leave the loop one by one: each reads its own lanes' bits only
+        const uint32_t le_k = (uint32_t)(__builtin_amdgcn_ballot_w64(le) >> g0) & ((1u << K) - 1u);
+        const uint32_t c = (uint32_t)__builtin_popcount(le_k);
+        lo += c * step;
+        len = min(step, len - c * step);
     }
-    // every load first, so the candidates' loads are issued together
-    int c[K];
-    Box cb[K];
-    uint32_t cnt[K], fst[K];
-#pragma unroll
-    for (int k = 0; k < K; k++) c[k] = cand[k];  // valid candidates are the first nc slots
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        cb[k] = box_empty();
-        cnt[k] = fst[k] = 0;
-        if (c[k] < 0) continue;
-        cb[k] = tv.nbox[c[k]];  // box and range in one load
-        cnt[k] = range_count(cb[k]);
-        fst[k] = range_first(cb[k]);
-    }
-    uint32_t ref[K];
-    int nc = 0;
-    uint32_t r = 0;
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        ref[k] = kRefEmpty;
-        if (c[k] < 0) continue;
-        nc++;
-        if (cnt[k] <= (uint32_t)tv.leaf_size) {
-            ref[k] = ref_leaf(fst[k], cnt[k]);
-        } else {
-            const uint32_t q = pos(r++);
-            if (q >= cap) {
-                atomicOr(&info->err, 4u);
-                return;
-            }
-            ref[k] = ref_interior(q);
-        }
-    }
-    WideOut<Layout>::write(sink.at(at), tv.nbox[x], cb, ref, nc, &info->err);
-    *stack_out = max(*stack_out, (aux & 0xFFFFu) + (uint32_t)(nc - 1));
-    *depth_out = max(*depth_out, (aux >> 16) + 2);  // its children's level and the leaf level below
+    return lo;
 }
 
-// One thread per node position (launched for the largest possible count).
-// The subtree offsets (at most K * kTopMaxFrontier) are staged in LDS for the
-// search.
+// K lanes per node position (launched for the largest possible count): the
+// subtree, the node's plan entry, then lane k reads child k.  What bounds it
+// are those four dependent reads and the stores.
 template <int Layout>
 __global__ __launch_bounds__(kBlock) void k_wide_write(TreeView tv, const int32_t *cand_all,
                                                        WidePlan p, uint32_t cap, NodeSink sink,
                                                        BuildInfo *info) {
     constexpr int K = WideOut<Layout>::K;
-    __shared__ uint32_t s_off[K * kTopMaxFrontier];
+    constexpr int kWords = WideOut<Layout>::kWords;
+    constexpr uint32_t kNodes = kBlock / K;  // nodes of a block
+    __shared__ __align__(16) uint32_t s_rec[kNodes][kWords + 4];  // rows 4 banks apart
     const uint32_t base = p.meta[0], roots = min(p.meta[1], (uint32_t)(K * kTopMaxFrontier)),
                    all = p.meta[2];
-    const uint32_t at = blockIdx.x * kBlock + threadIdx.x;
-    if (blockIdx.x * kBlock < all && (blockIdx.x + 1) * kBlock > base) {  // the same in the block
-        for (uint32_t b = threadIdx.x; b < roots; b += kBlock) s_off[b] = p.f_off[b];
-        __syncthreads();
-    }
+    const int k = threadIdx.x % K, g0 = (threadIdx.x & (kWave - 1)) & ~(K - 1);
+    const uint32_t at = blockIdx.x * kNodes + threadIdx.x / K;
     uint32_t stack = 0, depth = 0;
-    if (at < base) {
-        const uint32_t no = p.t_noff[at];
-        const int32_t x = p.t_node[at];
-        // the last top level's children are subtree roots
-        wide_write<Layout>(tv, x, p.t_aux[at], at, cap, cand_all + (size_t)x * K,
-                           [&](uint32_t r) {
-                               const uint32_t j = no + r;
-                               return j < base ? j : p.f_off[j - base];
-                           },
-                           sink, info, &stack, &depth);
-    } else if (at < all) {
-        // the subtree b with f_off[b] <= at < f_off[b + 1]
-        uint32_t lo = 0, hi = roots;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (s_off[mid] <= at) lo = mid; else hi = mid;
+    if (at < all && at >= cap) {
+        if (k == 0) atomicOr(&info->err, 4u);
+    } else if (at < all) {  // the same in a node's K lanes, here and below
+        const bool top = at < base;
+        const uint32_t b = top ? 0u : find_subtree<K>(p.f_off, roots, at);
+        const uint32_t off = top ? 0u : p.f_off[b];
+        const uint32_t q = top ? at : p.f_q0[b] + (at - off);
+        const uint32_t no = (top ? p.t_noff : p.s_noff)[q];
+        const int32_t x = (top ? p.t_node : p.s_node)[q];
+        const uint32_t aux = (top ? p.t_aux : p.s_aux)[q];
+        const int c = cand_all[(size_t)x * K + k];  // valid candidates are the first nc slots
+        const bool valid = c >= 0;
+        const Box pb = tv.nbox[x];
+        const Box cb = valid ? tv.nbox[c] : box_empty();  // box and range in one load
+        const uint32_t cnt = valid ? range_count(cb) : 0u;
+        const bool inner = valid && cnt > (uint32_t)tv.leaf_size;
+        const uint32_t inner_k = (uint32_t)(__builtin_amdgcn_ballot_w64(inner) >> g0) & ((1u << K) - 1u);
+        const int nc = __builtin_popcount((uint32_t)(__builtin_amdgcn_ballot_w64(valid) >> g0) & ((1u << K) - 1u));
+        uint32_t ref = kRefEmpty;
+        bool bad = false;
+        if (inner) {
+            const uint32_t j = no + (uint32_t)__builtin_popcount(inner_k & ((1u << k) - 1u));
+            // the last top level's children are subtree roots
+            const uint32_t pos = !top ? off + j : (j < base ? j : p.f_off[j - base]);
+            bad = pos >= cap;
+            ref = ref_interior(pos);
+        } else if (valid) {
+            ref = ref_leaf(range_first(cb), cnt);
         }
-        const uint32_t off = s_off[lo];
-        const uint32_t q = p.f_q0[lo] + (at - off);
-        const uint32_t no = p.s_noff[q];
-        const int32_t x = p.s_node[q];
-        wide_write<Layout>(tv, x, p.s_aux[q], at, cap, cand_all + (size_t)x * K,
-                           [&](uint32_t r) { return off + no + r; }, sink, info, &stack, &depth);
+        const bool any_bad = ((uint32_t)(__builtin_amdgcn_ballot_w64(bad) >> g0) & ((1u << K) - 1u)) != 0;
+        if (any_bad) {
+            if (k == 0) atomicOr(&info->err, 4u);
+        } else {
+            uint32_t *rec = s_rec[threadIdx.x / K];
+            WideOut<Layout>::put(rec, k, pb, cb, valid, ref, nc, &info->err);
+            wave_sync();
+            uint4 *dst = static_cast<uint4 *>(sink.at(at));
+            for (int i = k; i < kWords / 4; i += K) dst[i] = reinterpret_cast<const uint4 *>(rec)[i];
+            stack = (aux & 0xFFFFu) + (uint32_t)(nc - 1);
+            depth = (aux >> 16) + 2;  // its children's level and the leaf level below
+        }
     }
     wave_max_to_slots(tv.stack_slots, stack);
     wave_max_to_slots(tv.depth_slots, depth);
@@ -2040,7 +2036,7 @@ int32_t pack_wide(TreeView tv, volatile uint32_t *nleaf_word, int32_t *cand_all,
     k_wide_plan_sub<K><<<std::min(kRoots, kPlanBlocks), kSubThreads, 0, s>>>(tv, cand_all, ni_all,
                                                                            p, info);
     k_wide_place<<<1, kPlaceThreads, 0, s>>>(p, cap, info, hw);
-    k_wide_write<Layout><<<grid_for(cap), kBlock, 0, s>>>(tv, cand_all, p, cap, sink, info);
+    k_wide_write<Layout><<<grid_for((uint64_t)cap * K), kBlock, 0, s>>>(tv, cand_all, p, cap, sink, info);
     // the stack and depth bounds, queued before the host waits for the count
     k_fold_max_slots<<<1, kBlock, 0, s>>>(tv.stack_slots, tv.depth_slots, info);
     BVH_TRY(check_launch("wide packing"));
@@ -2172,11 +2168,6 @@ __device__ inline int sah_bin(const SahFrame f, int a, float c) {
 __device__ inline float half_area3(float lx, float ly, float lz, float hx, float hy, float hz) {
     const float dx = hx - lx, dy = hy - ly, dz = hz - lz;
     return (dx * dy + dy * dz) + dz * dx;
-}
-
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 }
 
 // Cheapest split of one axis from its 32 bins (lane k of the wave holds bin
