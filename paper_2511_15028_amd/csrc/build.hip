@@ -2092,11 +2092,17 @@ int32_t pack_wide(TreeView tv, volatile uint32_t *nleaf_word, int32_t *cand_all,
 // and m gets id m-1 (unique), except that the root takes id 0 and the node
 // with natural id 0 takes the root's natural id.
 //
-// Large nodes (more than kSahSmall primitives) are processed level by level
-// with many blocks each: centroid bounds, binning into per-node global bins,
-// one wave per node for the sweep, then a stable partition by one global
-// scan.  Nodes of at most kSahSmall primitives are finished by one wave
-// each with the primitives held in the lanes.
+// Large nodes (more than kSahSmall primitives) are processed level by level,
+// in chunks of kSahChunk primitives with a block each: binning, one wave per
+// node for the sweep, then a stable partition, which also takes the centroid
+// bounds of the children that the next level bins.  A chunk's bins hold what
+// the partition needs of the other chunks (how many of their primitives go
+// left), so no flag is written and nothing is scanned over the whole array.
+// A level costs its launches' latency rather than memory traffic: 300,000
+// triangles spend 600 us on 19 levels (with separate launches for bounds, flags,
+// their scan and the counts' publication: 1,110 us).  Nodes of at most
+// kSahSmall primitives are finished by one wave each with the primitives held
+// in the lanes.
 // ---------------------------------------------------------------------------
 constexpr int kSahBins = 32;
 constexpr uint32_t kSahSmall = 64;
@@ -2115,7 +2121,9 @@ struct SahSplit {
     int32_t k;     // last bin of the left side (-1: index median)
     uint32_t nl;   // primitives on the left
     uint32_t id;   // the node's id
+    uint32_t slot[2];  // per side: the child's task in the next level (kNoSlot: small)
 };
+constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 
 // Floats as order-preserving ints, so min/max can use integer atomics.
 __device__ inline int f2o(float f) {
@@ -2170,50 +2178,11 @@ __device__ inline float half_area3(float lx, float ly, float lz, float hx, float
     return (dx * dy + dy * dz) + dz * dx;
 }
 
-// Cheapest split of one axis from its 32 bins (lane k of the wave holds bin
-// k: count and box as floats; empty bins hold an empty box).  Returns, in
-// every lane, the minimal cost and its split k (the lowest k on ties), or
-// +inf when no split leaves both sides non-empty.
-__device__ inline void sah_sweep(uint32_t cnt, float lx, float ly, float lz, float hx, float hy,
-                                 float hz, float &best_cost, int &best_k, uint32_t &best_nl) {
-    const int lane = threadIdx.x & (kWave - 1);
-    // inclusive prefix over lanes 0..k and suffix over lanes k..31 (lanes 32-63
-    // hold empty bins and scan among themselves)
-    const auto add = [](uint32_t x, uint32_t y) { return x + y; };
-    const auto mn = [](float x, float y) { return fminf(x, y); };
-    const auto mx = [](float x, float y) { return fmaxf(x, y); };
-    const uint32_t pc = half_scan<uint32_t>(cnt, 0u, add);
-    const uint32_t sc = half_suffix_scan<uint32_t>(cnt, 0u, add, lane);
-    const float in[6] = {lx, ly, lz, hx, hy, hz};
-    float p[6], q[6];
-#pragma unroll
-    for (int j = 0; j < 3; j++) {
-        p[j] = half_scan<float>(in[j], INFINITY, mn);
-        q[j] = half_suffix_scan<float>(in[j], INFINITY, mn, lane);
-        p[3 + j] = half_scan<float>(in[3 + j], -INFINITY, mx);
-        q[3 + j] = half_suffix_scan<float>(in[3 + j], -INFINITY, mx, lane);
-    }
-    // right side of split k is the suffix starting at bin k + 1 (wave_shl:1)
-    const uint32_t rc = dpp<0x130, 0xf>(0u, sc);
-    float r[6];
-#pragma unroll
-    for (int j = 0; j < 6; j++) r[j] = dpp<0x130, 0xf>(j < 3 ? INFINITY : -INFINITY, q[j]);
-    float cost = INFINITY;
-    if (lane < kSahBins - 1 && pc > 0 && rc > 0)
-        cost = half_area3(p[0], p[1], p[2], p[3], p[4], p[5]) * (float)pc +
-               half_area3(r[0], r[1], r[2], r[3], r[4], r[5]) * (float)rc;
-    // minimum over the lanes, lowest k on ties
-    const float c = wave_min(cost);
-    const uint64_t at = __builtin_amdgcn_ballot_w64(lane < kSahBins - 1 && cost == c);
-    best_cost = c;
-    best_k = (c < INFINITY && at != 0) ? (int)__builtin_ctzll(at) : -1;
-    best_nl = readlane_t(pc, best_k < 0 ? 0 : best_k);
-}
-
-// Two sweeps at once: the bins of one axis in lanes 0-31 and of another in
-// lanes 32-63 (the scans above stay within each half).  Per half: the lowest
-// cost, the lowest bin among equal costs (-1 when no split has a finite
-// cost) and its left count, exactly as sah_sweep gives them for one axis.
+// Cheapest splits of two axes from their 32 bins each: bin k of one axis in
+// lane k, of the other in lane 32 + k (the scans stay within each half): count
+// and box as floats; empty bins hold an empty box.  Per half, in every lane:
+// the lowest cost (+inf when no split leaves both sides non-empty), the lowest
+// bin among equal costs (-1 when no split has a finite cost) and its left count.
 __device__ inline void sah_sweep2(uint32_t cnt, float lx, float ly, float lz, float hx, float hy,
                                   float hz, float &cost0, int &k0, uint32_t &nl0, float &cost1,
                                   int &k1, uint32_t &nl1) {
@@ -2302,33 +2271,22 @@ struct SahLevel {
     int *cbins;               // per chunk: kSahBinWords (the chunk's partial bins)
     int *gbins;               // merge groups > 1: per task and group, kSahBinWords
     uint32_t groups;          // chunk groups per task in the merge (1 or kMergeGroups)
+    uint32_t *ccnt;           // per chunk: kSahCounts running counts over each axis's bins
+    uint32_t *cleft;          // per chunk of a task with several: left primitives before it
 };
+constexpr uint32_t kSahCounts = 3 * kSahBins;
+constexpr int kSahRows = kSahChunk / kBlock;  // primitives per thread of a chunk's block
+static_assert(kSahRows * kBlock == (int)kSahChunk, "a chunk is a whole number of rows");
 
 // Chunk groups of a task of nch chunks in a level merged with `groups` groups.
 __device__ inline uint32_t merge_groups(uint32_t nch, uint32_t groups) { return min(nch, groups); }
 
-__global__ __launch_bounds__(kBlock) void k_sah_clear(int *cb, uint32_t ntask) {
-    const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int inf = f2o(INFINITY), ninf = f2o(-INFINITY);
-    if (i < (uint64_t)ntask * 6) cb[i] = (i % 6) < 3 ? inf : ninf;
-}
-
-__global__ __launch_bounds__(kBlock) void k_sah_bounds(SahLevel lv, const uint32_t *ord,
-                                                       const Box *pbox) {
-    __shared__ float red[6][kBlock / kWave];
-    const uint32_t t = lv.chunk[blockIdx.x];
-    const SahTask tk = lv.task[t];
-    const uint32_t p0 = lv.cstart[blockIdx.x], p1 = min(p0 + kSahChunk, tk.first + tk.count);
-    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    for (uint32_t p = p0 + threadIdx.x; p < p1; p += kBlock) {
-        const Box b = pbox[ord[p]];
-        for (int a = 0; a < 3; a++) {
-            const float c = sah_centroid(b, a);
-            v[a] = fminf(v[a], c);
-            v[3 + a] = fmaxf(v[3 + a], c);
-        }
-    }
+// Centroid bounds of a block's primitives into a task's words: v of each
+// thread (lo xyz, hi xyz), red scratch of the block.  Every thread calls it.
+__device__ inline void sah_fold_bounds(const float (&v)[6], float (*red)[kBlock / kWave], int *cb) {
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    __syncthreads();  // red may hold an earlier fold's values
+#pragma unroll
     for (int j = 0; j < 6; j++) {
         const float r = j < 3 ? wave_min(v[j]) : wave_max(v[j]);
         if (lane == 0) red[j][w] = r;
@@ -2338,9 +2296,31 @@ __global__ __launch_bounds__(kBlock) void k_sah_bounds(SahLevel lv, const uint32
         const int j = threadIdx.x;
         float r = red[j][0];
         for (int k = 1; k < kBlock / kWave; k++) r = j < 3 ? fminf(r, red[j][k]) : fmaxf(r, red[j][k]);
-        if (j < 3) atomicMin(&lv.cb[6 * t + j], f2o(r));
-        else atomicMax(&lv.cb[6 * t + j], f2o(r));
+        if (j < 3) atomicMin(&cb[j], f2o(r));
+        else atomicMax(&cb[j], f2o(r));
     }
+}
+
+__device__ inline void sah_clear_bounds(int *cb) {
+#pragma unroll
+    for (int j = 0; j < 6; j++) cb[j] = f2o(j < 3 ? INFINITY : -INFINITY);
+}
+
+// The root's centroid bounds (k_sah_init has cleared them).
+__global__ __launch_bounds__(kBlock) void k_sah_bounds(uint32_t n, const Box *pbox, int *cb) {
+    __shared__ float red[6][kBlock / kWave];
+    const uint32_t p0 = blockIdx.x * kSahChunk, p1 = min(p0 + kSahChunk, n);
+    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (uint32_t p = p0 + threadIdx.x; p < p1; p += kBlock) {
+        const Box b = pbox[p];
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            const float c = sah_centroid(b, a);
+            v[a] = fminf(v[a], c);
+            v[3 + a] = fmaxf(v[3 + a], c);
+        }
+    }
+    sah_fold_bounds(v, red, cb);
 }
 
 __device__ inline SahFrame sah_task_frame(const int *cb) {
@@ -2366,16 +2346,30 @@ __global__ __launch_bounds__(kBlock) void k_sah_bin(SahLevel lv, const uint32_t 
     const uint32_t t = lv.chunk[blockIdx.x];
     const SahTask tk = lv.task[t];
     const uint32_t p0 = lv.cstart[blockIdx.x], p1 = min(p0 + kSahChunk, tk.first + tk.count);
+    // every box is asked for before the bins are cleared
+    uint32_t prim[kSahRows];
+    Box box[kSahRows];
+#pragma unroll
+    for (int r = 0; r < kSahRows; r++) {
+        const uint32_t p = p0 + r * kBlock + threadIdx.x;
+        if (p < p1) prim[r] = ord[p];
+    }
+#pragma unroll
+    for (int r = 0; r < kSahRows; r++)
+        if (p0 + r * kBlock + threadIdx.x < p1) box[r] = pbox[prim[r]];
+    const SahFrame f = sah_task_frame(lv.cb + 6 * t);
     const int inf = f2o(INFINITY), ninf = f2o(-INFINITY);
     for (uint32_t i = threadIdx.x; i < kBinCopies * kBinCopyStride; i += kBlock) {
         const uint32_t w = (i % kBinCopyStride) % 7;
         sb[i] = w == 0 ? 0 : (w <= 3 ? inf : ninf);
     }
     __syncthreads();
-    const SahFrame f = sah_task_frame(lv.cb + 6 * t);
     int *mine = sb + (threadIdx.x % kBinCopies) * kBinCopyStride;
-    for (uint32_t p = p0 + threadIdx.x; p < p1; p += kBlock) {
-        const Box b = pbox[ord[p]];
+#pragma unroll
+    for (int r = 0; r < kSahRows; r++) {
+        if (p0 + r * kBlock + threadIdx.x >= p1) break;
+        const Box b = box[r];
+#pragma unroll
         for (int a = 0; a < 3; a++) {
             if (!f.ok(a)) continue;
             int *bin = mine + (a * kSahBins + sah_bin(f, a, sah_centroid(b, a))) * 7;
@@ -2401,6 +2395,13 @@ __global__ __launch_bounds__(kBlock) void k_sah_bin(SahLevel lv, const uint32_t 
             v = kind == 0 ? v + x : (kind <= 3 ? min(v, x) : max(v, x));
         }
         cbin[i] = v;
+        if (kind == 0) sb[i] = v;  // word i of the copies is this thread's
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * kWave) {  // whole waves; a half of a wave per axis
+        const uint32_t c = threadIdx.x < kSahCounts ? (uint32_t)sb[threadIdx.x * 7] : 0u;
+        const uint32_t run = half_scan<uint32_t>(c, 0u, [](uint32_t x, uint32_t y) { return x + y; });
+        if (threadIdx.x < kSahCounts) lv.ccnt[(size_t)blockIdx.x * kSahCounts + threadIdx.x] = run;
     }
 }
 
@@ -2441,43 +2442,70 @@ __global__ __launch_bounds__(kBlock) void k_sah_merge(SahLevel lv) {
     }
 }
 
-// The sweep and record of node t (one wave); leaves its task, id and left
-// count in tk, id, nl (the same in every lane).
+// The sweep and record of node t (one wave); leaves its task, id and split
+// (but for the slots) in tk and sp, the same in every lane.
 __device__ inline void sah_split_node(SahLevel lv, SahTree tr, uint32_t *root_nat, bool root_level,
-                                      uint32_t t, int lane, SahTask &tk, uint32_t &id,
-                                      uint32_t &nl_out) {
+                                      uint32_t t, int lane, SahTask &tk, SahSplit &sp) {
     tk = lv.task[t];
-    const uint32_t nch = (tk.count + kSahChunk - 1) / kSahChunk;
+    const uint32_t nch = (tk.count + kSahChunk - 1) / kSahChunk, c0 = lv.tc0[t];
     const uint32_t ng = nch < 2 ? 1u : merge_groups(nch, lv.groups);
     // one chunk: its chunk's bins; several in one group: the merged bins;
     // several groups: the groups' partial bins, combined here
-    const int *gb = nch < 2 ? lv.cbins + (size_t)lv.tc0[t] * kSahBinWords
+    const int *gb = nch < 2 ? lv.cbins + (size_t)c0 * kSahBinWords
                             : (ng > 1 ? lv.gbins + (size_t)t * kMergeGroups * kSahBinWords
                                       : lv.bins + (size_t)t * kSahBinWords);
     const SahFrame f = sah_task_frame(lv.cb + 6 * t);
+    // x's bins in lanes 0-31 and y's in lanes 32-63, then z's in lanes 0-31
+    const int *bin0 = gb + lane * 7, *bin1 = gb + (2 * kSahBins + (lane & (kSahBins - 1))) * 7;
+    int w0[7], w1[7];
+#pragma unroll
+    for (int j = 0; j < 7; j++) {
+        w0[j] = bin0[j];
+        w1[j] = bin1[j];
+    }
+#pragma unroll 4
+    for (uint32_t g = 1; g < ng; g++) {
+        const size_t at = (size_t)g * kSahBinWords;
+#pragma unroll
+        for (int j = 0; j < 7; j++) {
+            w0[j] = bin_combine((uint32_t)j, w0[j], bin0[at + j]);
+            w1[j] = bin_combine((uint32_t)j, w1[j], bin1[at + j]);
+        }
+    }
+    const bool v0 = f.ok(0), v1 = f.ok(1), v2 = f.ok(2);
     float best = INFINITY;
     int axis = -1, bk = -1;
     uint32_t nl = 0;
-    for (int a = 0; a < 3; a++) {
-        if (!f.ok(a)) continue;
-        const int *bin = gb + (a * kSahBins + (lane < kSahBins ? lane : 0)) * 7;
-        const bool in = lane < kSahBins;
-        int wv[7];
-        for (int j = 0; j < 7; j++) wv[j] = bin[j];
-        for (uint32_t g = 1; g < ng; g++)
-            for (int j = 0; j < 7; j++) wv[j] = bin_combine((uint32_t)j, wv[j], bin[(size_t)g * kSahBinWords + j]);
-        const uint32_t c = in ? (uint32_t)wv[0] : 0u;
-        float cost;
-        int k;
-        uint32_t l;
-        sah_sweep(c, in ? o2f(wv[1]) : INFINITY, in ? o2f(wv[2]) : INFINITY,
-                  in ? o2f(wv[3]) : INFINITY, in ? o2f(wv[4]) : -INFINITY,
-                  in ? o2f(wv[5]) : -INFINITY, in ? o2f(wv[6]) : -INFINITY, cost, k, l);
-        if (cost < best) {
-            best = cost;
-            axis = a;
-            bk = k;
-            nl = l;
+    // the costs are compared in axis order with a strict <: a lower axis wins a tie
+    if (v0 || v1) {
+        float cx, cy;
+        int kx, ky;
+        uint32_t lx, ly;
+        sah_sweep2((uint32_t)w0[0], o2f(w0[1]), o2f(w0[2]), o2f(w0[3]), o2f(w0[4]), o2f(w0[5]),
+                   o2f(w0[6]), cx, kx, lx, cy, ky, ly);
+        if (v0 && cx < best) {
+            best = cx;
+            axis = 0;
+            bk = kx;
+            nl = lx;
+        }
+        if (v1 && cy < best) {
+            best = cy;
+            axis = 1;
+            bk = ky;
+            nl = ly;
+        }
+    }
+    if (v2) {
+        float cz, unused_c;
+        int kz, unused_k;
+        uint32_t lz, unused_l;
+        sah_sweep2((uint32_t)w1[0], o2f(w1[1]), o2f(w1[2]), o2f(w1[3]), o2f(w1[4]), o2f(w1[5]),
+                   o2f(w1[6]), cz, kz, lz, unused_c, unused_k, unused_l);
+        if (cz < best) {
+            axis = 2;
+            bk = kz;
+            nl = lz;
         }
     }
     if (axis < 0) {
@@ -2488,12 +2516,19 @@ __device__ inline void sah_split_node(SahLevel lv, SahTree tr, uint32_t *root_na
     const uint32_t m = tk.first + nl;
     if (root_level && lane == 0) *root_nat = m - 1;
     const uint32_t rn = root_level ? m - 1 : *root_nat;
-    id = sah_node_id(m, tk.parent < 0, rn);
-    nl_out = nl;
-    if (lane == 0) {
-        lv.split[t] = SahSplit{axis, bk, nl, id};
-        sah_write_node(tr, id, tk.first, tk.count, axis, nl, tk.parent, tk.side);
+    sp = SahSplit{axis, bk, nl, sah_node_id(m, tk.parent < 0, rn), {kNoSlot, kNoSlot}};
+    if (nch > 1 && bk >= 0) {  // the left primitives before each chunk
+        uint32_t carry = 0;
+        for (uint32_t j0 = 0; j0 < nch; j0 += kWave) {
+            const uint32_t j = j0 + lane;
+            const uint32_t v = j < nch ? lv.ccnt[(size_t)(c0 + j) * kSahCounts + axis * kSahBins + bk] : 0u;
+            uint32_t run = half_scan<uint32_t>(v, 0u, [](uint32_t x, uint32_t y) { return x + y; });
+            if (lane >= kSahBins) run += readlane_t(run, kSahBins - 1);
+            if (j < nch) lv.cleft[c0 + j] = carry + run - v;
+            carry += readlane_t(run, kWave - 1);
+        }
     }
+    if (lane == 0) sah_write_node(tr, sp.id, tk.first, tk.count, axis, nl, tk.parent, tk.side);
 }
 
 // One wave per node: the sweep over the three axes, then the node's id and
@@ -2502,16 +2537,21 @@ __device__ inline void sah_split_node(SahLevel lv, SahTree tr, uint32_t *root_na
 // for the next level.  The queue slots of a block's nodes are taken with one
 // device atomic per queue and block (per-node atomics on the three counters
 // serialised across the XCDs: 0.2-0.45 ms per level with thousands of nodes).
-constexpr int kSplitThreads = 1024;
-constexpr int kSplitWaves = kSplitThreads / kWave;
+// Levels of few nodes use small blocks, which start sooner and spread over the
+// GPU (SAH builds of 5,000 to 300,000 triangles 4-7 % faster); levels of many
+// use large ones, for fewer atomics (2,000,000 triangles 2 % faster).
+constexpr int kSplitFewThreads = 256, kSplitManyThreads = 1024;
+constexpr uint32_t kSplitFewTasks = 2048;
 
+template <int kSplitThreads>
 __global__ __launch_bounds__(kSplitThreads) void k_sah_split(SahLevel lv, SahTree tr,
                                                              uint32_t *root_nat, bool root_level,
                                                              SahTask *next, uint32_t *next_chunk,
                                                              uint32_t *next_cstart,
-                                                             uint32_t *next_tc0,
+                                                             uint32_t *next_tc0, int *next_cb,
                                                              uint32_t *counters, SahTask *small,
                                                              uint32_t *small_count) {
+    constexpr int kSplitWaves = kSplitThreads / kWave;
     __shared__ uint32_t need[3][kSplitWaves];  // per wave: small tasks, next tasks, next chunks
     __shared__ uint32_t base[3];
     const int wv = threadIdx.x / kWave;
@@ -2519,8 +2559,9 @@ __global__ __launch_bounds__(kSplitThreads) void k_sah_split(SahLevel lv, SahTre
     const bool live = t < lv.ntask;
     const int lane = threadIdx.x & (kWave - 1);
     SahTask tk{0, 0, -1, 0};
-    uint32_t id = 0, nl = 0;
-    if (live) sah_split_node(lv, tr, root_nat, root_level, t, lane, tk, id, nl);
+    SahSplit sp{0, -1, 0, 0, {kNoSlot, kNoSlot}};
+    if (live) sah_split_node(lv, tr, root_nat, root_level, t, lane, tk, sp);
+    const uint32_t nl = sp.nl;
     // the node's children that need queue slots
     const uint32_t cf[2] = {tk.first, tk.first + nl}, cc[2] = {nl, tk.count - nl};
     uint32_t ns = 0, nn = 0, nc = 0;
@@ -2557,12 +2598,14 @@ __global__ __launch_bounds__(kSplitThreads) void k_sah_split(SahLevel lv, SahTre
     }
     for (int sd = 0; sd < 2; sd++) {
         if (cc[sd] < 2) continue;
-        const SahTask ch{cf[sd], cc[sd], (int32_t)id, (uint32_t)sd};
+        const SahTask ch{cf[sd], cc[sd], (int32_t)sp.id, (uint32_t)sd};
         if (cc[sd] <= kSahSmall) {
             small[so++] = ch;
         } else {
             const uint32_t slot = no++;
+            sp.slot[sd] = slot;
             next[slot] = ch;
+            sah_clear_bounds(next_cb + 6 * (size_t)slot);
             next_tc0[slot] = co;
             const uint32_t nch = (cc[sd] + kSahChunk - 1) / kSahChunk;
             for (uint32_t j = 0; j < nch; j++) {
@@ -2572,46 +2615,101 @@ __global__ __launch_bounds__(kSplitThreads) void k_sah_split(SahLevel lv, SahTre
             co += nch;
         }
     }
+    lv.split[t] = sp;
 }
 
-
-__global__ __launch_bounds__(kBlock) void k_sah_flags(SahLevel lv, const uint32_t *ord,
-                                                      const Box *pbox, uint32_t *flags) {
-    const uint32_t t = lv.chunk[blockIdx.x];
-    const SahTask tk = lv.task[t];
-    const SahSplit sp = lv.split[t];
-    const uint32_t p0 = lv.cstart[blockIdx.x], p1 = min(p0 + kSahChunk, tk.first + tk.count);
-    const SahFrame f = sah_task_frame(lv.cb + 6 * t);
-    for (uint32_t p = p0 + threadIdx.x; p < p1; p += kBlock) {
-        bool left;
-        if (sp.k < 0) left = p - tk.first < sp.nl;
-        else left = sah_bin(f, sp.axis, sah_centroid(pbox[ord[p]], sp.axis)) <= sp.k;
-        flags[p] = left ? 1u : 0u;
-    }
-}
-
+// The stable partition of one chunk: each wave takes consecutive rows of it, so
+// a primitive's rank among the left ones is that of the chunk (cleft), of the
+// waves before and of the lanes and rows before.  Also folds the centroid
+// bounds of the children that the next level bins, and the first block tells
+// the host the next level's sizes (final since the split), so that the host's
+// answer overlaps the partition.
 __global__ __launch_bounds__(kBlock) void k_sah_scatter(SahLevel lv, const uint32_t *ord,
-                                                        const uint32_t *flags, const uint32_t *offs,
-                                                        uint32_t *ord_next, uint32_t *perm,
+                                                        const Box *pbox, uint32_t *ord_next,
+                                                        uint32_t *perm, int *next_cb,
+                                                        const uint32_t *counters,
+                                                        const uint32_t *small_count, uint32_t *host,
                                                         uint32_t *err) {
+    constexpr int W = kBlock / kWave;
+    __shared__ float red[6][W];
+    __shared__ uint32_t wleft[W];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        host[0] = counters[0];
+        host[1] = counters[1];
+        host[2] = *small_count;
+        __threadfence_system();  // the host polls the words
+    }
     const uint32_t t = lv.chunk[blockIdx.x];
     const SahTask tk = lv.task[t];
     const SahSplit sp = lv.split[t];
     const uint32_t p0 = lv.cstart[blockIdx.x], p1 = min(p0 + kSahChunk, tk.first + tk.count);
-    const uint32_t base = offs[tk.first];
-    for (uint32_t p = p0 + threadIdx.x; p < p1; p += kBlock) {
-        const uint32_t lrank = offs[p] - base;
-        const bool left = flags[p] != 0u;
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const uint32_t rows = (p1 - p0 + kBlock - 1) / kBlock;
+    const uint32_t q0 = p0 + (uint32_t)w * rows * kWave + lane;  // row r: q0 + r * kWave
+    uint32_t prim[kSahRows];
+    Box box[kSahRows];
+#pragma unroll
+    for (int r = 0; r < kSahRows; r++) {
+        const uint32_t p = q0 + r * kWave;
+        if (r < (int)rows && p < p1) prim[r] = ord[p];
+    }
+#pragma unroll
+    for (int r = 0; r < kSahRows; r++)
+        if (r < (int)rows && q0 + r * kWave < p1) box[r] = pbox[prim[r]];
+    const SahFrame f = sah_task_frame(lv.cb + 6 * t);
+    float v[2][6];
+#pragma unroll
+    for (int j = 0; j < 6; j++) v[0][j] = v[1][j] = j < 3 ? INFINITY : -INFINITY;
+    uint64_t lmask[kSahRows];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int r = 0; r < kSahRows; r++) {
+        lmask[r] = 0;
+        if (r >= (int)rows) break;  // the same in the block
+        const uint32_t p = q0 + r * kWave;
+        bool left = false;
+        if (p < p1) {
+            const float c[3] = {sah_centroid(box[r], 0), sah_centroid(box[r], 1), sah_centroid(box[r], 2)};
+            left = sp.k < 0 ? p - tk.first < sp.nl
+                            : sah_bin(f, sp.axis, sp.axis == 0 ? c[0] : (sp.axis == 1 ? c[1] : c[2])) <= sp.k;
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                v[0][a] = fminf(v[0][a], left ? c[a] : INFINITY);
+                v[0][3 + a] = fmaxf(v[0][3 + a], left ? c[a] : -INFINITY);
+                v[1][a] = fminf(v[1][a], left ? INFINITY : c[a]);
+                v[1][3 + a] = fmaxf(v[1][3 + a], left ? -INFINITY : c[a]);
+            }
+        }
+        lmask[r] = __builtin_amdgcn_ballot_w64(left);
+        mine += (uint32_t)__builtin_popcountll(lmask[r]);
+    }
+    if (lane == 0) wleft[w] = mine;
+    __syncthreads();
+    // left primitives of the node before this wave's first row
+    uint32_t lrank0 = sp.k < 0 ? min(p0 - tk.first, sp.nl)
+                               : (tk.count > kSahChunk ? lv.cleft[blockIdx.x] : 0u);
+    for (int k = 0; k < w; k++) lrank0 += wleft[k];
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int r = 0; r < kSahRows; r++) {
+        if (r >= (int)rows) break;
+        const uint32_t p = q0 + r * kWave;
+        const uint32_t lrank = lrank0 + (uint32_t)__builtin_popcountll(lmask[r] & below);
+        lrank0 += (uint32_t)__builtin_popcountll(lmask[r]);
+        if (p >= p1) continue;
+        const bool left = (lmask[r] >> lane) & 1u;
         const uint32_t dst = left ? tk.first + lrank : tk.first + sp.nl + (p - tk.first - lrank);
         if (dst >= tk.first + tk.count || (left ? lrank >= sp.nl : false)) {
-            atomicOr(err, 1u);  // the flags disagree with the split's count
+            atomicOr(err, 1u);  // the primitives disagree with the split's count
             continue;
         }
-        const uint32_t prim = ord[p];
-        ord_next[dst] = prim;
+        ord_next[dst] = prim[r];
         const uint32_t child = left ? sp.nl : tk.count - sp.nl;
-        if (child <= kSahSmall) perm[dst] = prim;
+        if (child <= kSahSmall) perm[dst] = prim[r];
     }
+    // the same in the block
+    if (sp.slot[0] != kNoSlot) sah_fold_bounds(v[0], red, next_cb + 6 * (size_t)sp.slot[0]);
+    if (sp.slot[1] != kNoSlot) sah_fold_bounds(v[1], red, next_cb + 6 * (size_t)sp.slot[1]);
 }
 
 // Finishes nodes of at most kSahSmall primitives, one wave each, with the
@@ -2785,8 +2883,8 @@ __global__ __launch_bounds__(kBlock) void k_sah_small(const SahTask *small, uint
 }
 
 __global__ void k_sah_init(uint32_t *ord, uint32_t *perm, uint32_t n, SahTask *task,
-                           uint32_t *chunk, uint32_t *cstart, uint32_t *tc0, SahTask *small,
-                           uint32_t *nsmall) {
+                           uint32_t *chunk, uint32_t *cstart, uint32_t *tc0, int *cb,
+                           SahTask *small, uint32_t *nsmall) {
     const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i < n) {
         ord[i] = i;
@@ -2797,6 +2895,7 @@ __global__ void k_sah_init(uint32_t *ord, uint32_t *perm, uint32_t n, SahTask *t
         if (n > kSahSmall) {
             task[0] = root;
             tc0[0] = 0;
+            sah_clear_bounds(cb);
         } else {
             small[0] = root;
             *nsmall = 1;
@@ -2817,24 +2916,24 @@ __global__ void k_sah_publish(const uint32_t *src, uint32_t *dst, int k) {
 }
 
 // Host side of the binned-SAH topology: fills perm and the tree arrays.
-int32_t sah_topology(const Box *pbox, uint32_t n, uint32_t *perm, SahTree tr, uint32_t *tile,
-                     int leaf_size, hipStream_t s) {
+int32_t sah_topology(const Box *pbox, uint32_t n, uint32_t *perm, SahTree tr, int leaf_size,
+                     hipStream_t s) {
     if (n < 2) {
         if (n == 1) BVH_HIP_TRY(hipMemsetAsync(perm, 0, sizeof(uint32_t), s));
         return BVH_OK;
     }
     const uint32_t cap_task = n / (kSahSmall + 1) + 1;
     const uint32_t cap_chunk = (n + kSahChunk - 1) / kSahChunk + cap_task;
-    uint32_t *ord[2], *flags, *offs, *chunk[2], *cstart[2], *tc0[2], *counters, *small_count,
+    uint32_t *ord[2], *ccnt, *cleft, *chunk[2], *cstart[2], *tc0[2], *counters, *small_count,
         *root_nat;
     SahTask *task[2], *small;
     SahSplit *split;
-    int *cb, *bins, *cbins, *gbins;
+    int *cb[2], *bins, *cbins, *gbins;
     Arena ar;
     ar.request(&ord[0], n);
     ar.request(&ord[1], n);
-    ar.request(&flags, n);
-    ar.request(&offs, n);
+    ar.request(&ccnt, (size_t)cap_chunk * kSahCounts);
+    ar.request(&cleft, cap_chunk);
     ar.request(&task[0], cap_task);
     ar.request(&task[1], cap_task);
     ar.request(&chunk[0], cap_chunk);
@@ -2842,7 +2941,8 @@ int32_t sah_topology(const Box *pbox, uint32_t n, uint32_t *perm, SahTree tr, ui
     ar.request(&cstart[0], cap_chunk);
     ar.request(&cstart[1], cap_chunk);
     ar.request(&split, cap_task);
-    ar.request(&cb, (size_t)cap_task * 6);
+    ar.request(&cb[0], (size_t)cap_task * 6);
+    ar.request(&cb[1], (size_t)cap_task * 6);
     ar.request(&bins, (size_t)cap_task * kSahBinWords);
     ar.request(&cbins, (size_t)cap_chunk * kSahBinWords);
     ar.request(&gbins, (size_t)kMergeGroupTasks * kMergeGroups * kSahBinWords);
@@ -2855,47 +2955,44 @@ int32_t sah_topology(const Box *pbox, uint32_t n, uint32_t *perm, SahTree tr, ui
     root_nat = small_count + 1;
     uint32_t *err = small_count + 2;
     BVH_HIP_TRY(hipMemsetAsync(counters, 0, (2 * kSahMaxLevels + 4) * sizeof(uint32_t), s));
-    BVH_HIP_TRY(hipMemsetAsync(flags, 0, (size_t)n * sizeof(uint32_t), s));
     k_sah_init<<<grid_for(n), kBlock, 0, s>>>(ord[0], perm, n, task[0], chunk[0], cstart[0], tc0[0],
-                                              small, small_count);
+                                              cb[0], small, small_count);
     BVH_TRY(check_launch("sah init"));
     uint32_t *hw = host_words();
     if (!hw) return set_error(BVH_ENOMEM, "hipHostMalloc failed");
     volatile uint32_t *vw = hw + 8;
     uint32_t ntask = n > kSahSmall ? 1u : 0u;
     uint32_t nchunk = (n + kSahChunk - 1) / kSahChunk;
+    uint32_t nsmall = ntask > 0 ? 0u : 1u;
     int cur = 0;
+    if (ntask > 0) k_sah_bounds<<<nchunk, kBlock, 0, s>>>(n, pbox, cb[0]);
     for (int level = 0; ntask > 0; level++) {
         if (level >= kSahMaxLevels)
             return set_error(BVH_EUNSUPPORTED,
                              "bvh_build: SAH tree deeper than the traversal stack bound %d", kStackMax);
         // few tasks with several chunks each: merge them with several groups
         const uint32_t groups = (ntask <= kMergeGroupTasks && nchunk >= 2 * ntask) ? kMergeGroups : 1u;
-        SahLevel lv{task[cur], chunk[cur], cstart[cur], cb, bins, split, ntask, tc0[cur], cbins,
-                    gbins, groups};
-        k_sah_clear<<<grid_for((uint64_t)ntask * 6), kBlock, 0, s>>>(cb, ntask);
-        k_sah_bounds<<<nchunk, kBlock, 0, s>>>(lv, ord[cur], pbox);
+        SahLevel lv{task[cur], chunk[cur], cstart[cur], cb[cur], bins, split, ntask, tc0[cur], cbins,
+                    gbins, groups, ccnt, cleft};
         k_sah_bin<<<nchunk, kBlock, 0, s>>>(lv, ord[cur], pbox);
-        k_sah_merge<<<dim3(ntask, groups), kBlock, 0, s>>>(lv);
-        k_sah_split<<<(ntask + kSplitWaves - 1) / kSplitWaves, kSplitThreads, 0, s>>>(
+        if (nchunk > ntask) k_sah_merge<<<dim3(ntask, groups), kBlock, 0, s>>>(lv);
+        const bool few = ntask <= kSplitFewTasks;
+        const int threads = few ? kSplitFewThreads : kSplitManyThreads;
+        (few ? k_sah_split<kSplitFewThreads> : k_sah_split<kSplitManyThreads>)<<<
+            grid_for((uint64_t)ntask * kWave, threads), threads, 0, s>>>(
             lv, tr, root_nat, level == 0, task[cur ^ 1], chunk[cur ^ 1], cstart[cur ^ 1],
-            tc0[cur ^ 1], counters + 2 * level, small, small_count);
-        k_sah_flags<<<nchunk, kBlock, 0, s>>>(lv, ord[cur], pbox, flags);
-        scan_u32(flags, offs, n, tile, nullptr, s);
-        k_sah_scatter<<<nchunk, kBlock, 0, s>>>(lv, ord[cur], flags, offs, ord[cur ^ 1], perm, err);
-        vw[0] = vw[1] = kPending;
-        k_sah_publish<<<1, 64, 0, s>>>(counters + 2 * level, hw + 8, 2);
+            tc0[cur ^ 1], cb[cur ^ 1], counters + 2 * level, small, small_count);
+        vw[0] = vw[1] = vw[2] = kPending;
+        k_sah_scatter<<<nchunk, kBlock, 0, s>>>(lv, ord[cur], pbox, ord[cur ^ 1], perm, cb[cur ^ 1],
+                                                counters + 2 * level, small_count, hw + 8, err);
         BVH_TRY(check_launch("sah level"));
         BVH_TRY(wait_host_word(vw, s, &ntask));
         BVH_TRY(wait_host_word(vw + 1, s, &nchunk));
+        BVH_TRY(wait_host_word(vw + 2, s, &nsmall));
         if (ntask > cap_task || nchunk > cap_chunk)
             return set_error(BVH_EHIP, "bvh_build: internal error (SAH task overflow)");
         cur ^= 1;
     }
-    vw[2] = kPending;
-    k_sah_publish<<<1, 64, 0, s>>>(small_count, hw + 10, 1);
-    uint32_t nsmall = 0;
-    BVH_TRY(wait_host_word(vw + 2, s, &nsmall));
     if (nsmall > n / 2 + 1) return set_error(BVH_EHIP, "bvh_build: internal error (SAH small overflow)");
     if (nsmall > 0)
         k_sah_small<<<(nsmall + kBlock / kWave - 1) / (kBlock / kWave), kBlock, 0, s>>>(
@@ -3034,7 +3131,7 @@ int32_t build_impl(const float *verts, int64_t n_verts, const int32_t *tris, int
         // a4 alternative: binned-SAH topology over the primitive boxes
         BVH_TRY(check_launch("bounds"));
         SahTree tr{ileft, iright, parent, ifirst, icount, iaxis, n};
-        BVH_TRY(sah_topology(pbox, (uint32_t)n, vals[0], tr, tile, L, s));
+        BVH_TRY(sah_topology(pbox, (uint32_t)n, vals[0], tr, L, s));
         perm = vals[0];
         BVH_TRY(leaf_data_early());
     } else {
