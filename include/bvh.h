@@ -342,8 +342,9 @@ int32_t bvh_version(void);
 int32_t bvh_build(const float *verts, int64_t n_verts, const int32_t *tris, int64_t n_tris,
                   int32_t layout, const bvh_build_opts *opts, void *stream, bvh_handle_t *out);
 
-/* Frees everything the handle owns (synchronises the device first).  NULL is
- * accepted and ignored. */
+/* Releases everything the handle owns (synchronises the device first).  The
+ * library keeps up to 512 MiB of released memory per device for later builds.
+ * NULL is accepted and ignored. */
 int32_t bvh_destroy(bvh_handle_t h);
 
 /* Sizes and shape of a built BVH.  out: host. */

@@ -41,9 +41,11 @@ extern "C" int32_t bvh_destroy(bvh_handle_t h) {
     int prev = 0;
     bool have_prev = hipGetDevice(&prev) == hipSuccess;
     if (hipSetDevice(h->device) == hipSuccess) {
-        (void)hipDeviceSynchronize();
-        if (h->block) (void)hipFree(h->block);
-        if (h->node_block) (void)hipFree(h->node_block);
+        const bool idle = hipDeviceSynchronize() == hipSuccess;
+        for (DeviceBlock *b : {&h->block, &h->node_block}) {
+            if (idle) block_release(h->device, b);
+            else if (b->ptr) (void)hipFree(b->ptr);
+        }
     }
     if (have_prev) (void)hipSetDevice(prev);
     delete h;

@@ -1869,8 +1869,8 @@ int32_t alloc_leaf_block(bvh_handle_s *h) {
     const size_t b_leaf = up(n * (compact ? sizeof(bvh_tri) : sizeof(int32_t)));
     const size_t b_verts = compact ? 0 : up((size_t)h->n_verts * 3 * sizeof(float));
     const size_t b_tris = compact ? 0 : up(n * 3 * sizeof(int32_t));
-    BVH_HIP_TRY(hipMalloc(&h->block, b_leaf + b_verts + b_tris));
-    char *p = static_cast<char *>(h->block);
+    BVH_HIP_TRY(block_alloc(h->device, b_leaf + b_verts + b_tris, &h->block));
+    char *p = static_cast<char *>(h->block.ptr);
     h->leaf = p;
     if (!compact) {
         h->verts = reinterpret_cast<float *>(p + b_leaf);
@@ -1880,9 +1880,9 @@ int32_t alloc_leaf_block(bvh_handle_s *h) {
 }
 
 int32_t alloc_node_block(bvh_handle_s *h, int64_t n_nodes) {
-    BVH_HIP_TRY(hipMalloc(&h->node_block, (size_t)n_nodes * (size_t)h->node_bytes));
+    BVH_HIP_TRY(block_alloc(h->device, (size_t)n_nodes * (size_t)h->node_bytes, &h->node_block));
     h->node_block_cap = (uint32_t)n_nodes;
-    h->nodes = h->node_block;
+    h->nodes = h->node_block.ptr;
     return BVH_OK;
 }
 
@@ -1953,9 +1953,8 @@ int32_t alloc_node_block_ahead(bvh_handle_s *h) {
     const int64_t hint = node_count_hints().get(node_hint_key(h));
     if (hint <= 0) return BVH_OK;
     const int64_t want = std::min<int64_t>(std::max<int64_t>(1, h->n_tris - 1), hint + hint / 64 + 64);
-    if (hipMalloc(&h->node_block, (size_t)want * h->node_bytes) != hipSuccess) {
+    if (block_alloc(h->device, (size_t)want * h->node_bytes, &h->node_block) != hipSuccess) {
         (void)hipGetLastError();  // no block ahead: the exact one comes after packing
-        h->node_block = nullptr;
         return BVH_OK;
     }
     h->node_block_cap = (uint32_t)want;
@@ -2029,7 +2028,7 @@ int32_t pack_wide(TreeView tv, volatile uint32_t *nleaf_word, int32_t *cand_all,
     if (!hw) return set_error(BVH_ENOMEM, "hipHostMalloc failed");
     volatile uint32_t *vw = hw;
     vw[0] = kPending;
-    NodeSink sink{static_cast<uint8_t *>(h->node_block), h->node_block ? h->node_block_cap : 0u,
+    NodeSink sink{static_cast<uint8_t *>(h->node_block.ptr), h->node_block.ptr ? h->node_block_cap : 0u,
                   wnodes, (uint32_t)h->node_bytes};
     const NodeCountHints::Key key = node_hint_key(h);
     k_wide_plan_top<K><<<1, kTopThreads, 0, s>>>(cand_all, ni_all, p);
@@ -2051,29 +2050,29 @@ int32_t pack_wide(TreeView tv, volatile uint32_t *nleaf_word, int32_t *cand_all,
                          (unsigned long long)base * (unsigned long long)h->node_bytes);
     node_count_hints().put(key, base);
     if (sink.spec && base <= sink.spec_cap) {  // every node is in place
-        h->nodes = h->node_block;
+        h->nodes = h->node_block.ptr;
         return BVH_OK;
     }
-    void *spec = h->node_block;  // too small (or absent): move into an exact block
-    h->node_block = nullptr;
+    DeviceBlock spec = h->node_block;  // too small (or absent): move into an exact block
+    h->node_block = DeviceBlock{};
     const int32_t rc = alloc_node_block(h, base);
     if (rc == BVH_OK) {
         const size_t nb0 = (size_t)std::min(base, sink.spec_cap) * h->node_bytes;
         const size_t all = (size_t)base * h->node_bytes;
         hipError_t e = hipSuccess;
-        if (nb0 > 0) e = hipMemcpyAsync(h->nodes, spec, nb0, hipMemcpyDeviceToDevice, s);
+        if (nb0 > 0) e = hipMemcpyAsync(h->nodes, spec.ptr, nb0, hipMemcpyDeviceToDevice, s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(static_cast<uint8_t *>(h->nodes) + nb0, wnodes + nb0, all - nb0,
                                hipMemcpyDeviceToDevice, s);
-        if (e == hipSuccess && spec) e = hipStreamSynchronize(s);
-        if (spec) (void)hipFree(spec);
+        if (e == hipSuccess && spec.ptr) e = hipStreamSynchronize(s);
+        if (spec.ptr) (void)hipFree(spec.ptr);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             return set_error(BVH_EHIP, "wide packing: node copy failed: %s", hipGetErrorString(e));
         }
         return BVH_OK;
     }
-    if (spec) (void)hipFree(spec);
+    if (spec.ptr) (void)hipFree(spec.ptr);
     return rc;
 }
 

@@ -52,6 +52,14 @@ constexpr int kStackMax = 256;
 // ---------------------------------------------------------------------------
 // Handle
 // ---------------------------------------------------------------------------
+// A device allocation that returns to a pool of idle ones (workspace.hip).
+struct DeviceBlock {
+    void *ptr = nullptr;
+    size_t bytes = 0;
+};
+hipError_t block_alloc(int device, size_t bytes, DeviceBlock *out);
+void block_release(int device, DeviceBlock *b);
+
 }  // namespace bvhlib
 
 struct bvh_handle_s {
@@ -74,8 +82,8 @@ struct bvh_handle_s {
     float frame_origin[3] = {0, 0, 0};  // PBRT_Q16, SG_EQ: lo = fmaf(q, frame_scale, frame_origin)
     float frame_scale[3] = {0, 0, 0};
     float frame_top[3] = {0, 0, 0};     // SG_EQ: hi = fmaf(-q, frame_scale, frame_top)
-    void *block = nullptr;       // device allocation of leaf, verts and tris
-    void *node_block = nullptr;  // device allocation of the node records
+    bvhlib::DeviceBlock block;       // device allocation of leaf, verts and tris
+    bvhlib::DeviceBlock node_block;  // device allocation of the node records
     uint32_t node_block_cap = 0; // records node_block holds
     void *nodes = nullptr;       // node records
     void *leaf = nullptr;        // bvh_tri[n_tris] or int32 prim id[n_tris]

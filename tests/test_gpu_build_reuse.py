@@ -1,0 +1,77 @@
+"""Builds that take the device memory of earlier handles, and the SAH build at the sizes where its
+levels change shape.
+
+Released blocks go to the next builds, whatever their thread and stream, so every build must give
+the bytes that it gives in fresh memory, and what stays allocated must be bounded.  The SAH levels
+work in chunks of 2,048 primitives with 64 chunks to a scan step: the trees just above and below
+those sizes must be the oracle's.
+"""
+import threading
+
+import pytest
+
+from paper_2511_15028_amd import workloads as W
+from test_gpu_parity import dev, B
+from test_gpu_sah import check_tree
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+KEPT = 512 << 20  # what the library may keep of released memory
+
+
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 2048 * 64 + 1, 2048 * 65 + 3])
+def test_sah_chunk_edges(orc, n):
+    v, t = W.soup_scene(n, seed=n)
+    check_tree(orc, v, t, 4)
+
+
+def buffers(v, t, layout):
+    h = B().build(v, t, layout)
+    out = h.read_buffer(0), h.read_buffer(1)
+    h.close()
+    return out
+
+
+@pytest.mark.parametrize("layout", ["bvh4", "bvh8_q8", "aabb2"])
+def test_reused_blocks_give_the_same_bytes(layout):
+    meshes = [tuple(dev(x) for x in W.soup_scene(n, seed=n)) for n in (5, 900, 1000, 1100, 40_000)]
+    want = [buffers(v, t, layout) for v, t in meshes]
+    for k in (3, 1, 4, 0, 2, 1, 3):  # sizes that fit another's block and sizes that do not
+        assert buffers(*meshes[k], layout) == want[k]
+
+
+def test_threads_and_streams_share_released_blocks():
+    meshes = [tuple(dev(x) for x in W.soup_scene(n, seed=n)) for n in (2000, 2100, 2200, 2300)]
+    want = [buffers(v, t, "bvh4") for v, t in meshes]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(k):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for i in range(20):
+                j = (k + i) % len(meshes)
+                if buffers(*meshes[j], "bvh4") != want[j]:
+                    bad.append((k, i))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not bad
+
+
+def test_kept_memory_is_bounded():
+    v, t = (dev(x) for x in W.soup_scene(1_000_000, seed=1))
+    B().build(v, t, "bvh4").close()  # the work areas have their sizes now
+    handles = [B().build(v, t, "bvh4") for _ in range(12)]
+    held = sum(h.stats()["nodes_buffer_bytes"] + h.stats()["leaf_buffer_bytes"] for h in handles)
+    assert held > KEPT  # or this test shows nothing
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    for h in handles:
+        h.close()
+    # every allocation may be rounded up to 2 MiB pages
+    assert torch.cuda.mem_get_info()[0] - before >= held - KEPT - (2 << 20) * 24
