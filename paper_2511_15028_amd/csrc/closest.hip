@@ -916,13 +916,15 @@ int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_poin
     BVH_TRY(resident_blocks(kernel, resident));
     // as in the ray kernel: few queries are spread over all resident waves
     const uint64_t waves = (uint64_t)resident * (kTraceBlock / 64);
-    const Deal deal = deal_of(n, waves, kCpqStack, (uint32_t)h->max_stack);
+    const Deal deal = deal_of(n, waves, kCpqStack, depth_first_reserve(h->max_stack));
+    const bool alone = !Count && wholly_coop(deal, n, waves, h->max_stack);
     const uint64_t need = ((n + deal.claim - 1) / deal.claim + kTraceBlock / 64 - 1) / (kTraceBlock / 64);
     const unsigned grid = (unsigned)std::min<uint64_t>(resident, need);
-    TraceArea ta;
-    BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
+    TraceArea ta{Fallback{}, SpillArea{nullptr, grid * kTraceBlock, 0}};
+    if (!alone) BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
     kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, qs, n, out, counts, deal,
                                         ta.fb, ta.sa);
+    if (alone) return BVH_OK;
     k_cpq_fallback<Layout, LeafMode, Count><<<kFallbackBlocks, kTraceBlock, 0, s>>>(
         h->nodes, h->n_nodes, ld, qs, out, counts, ta.fb);
     return BVH_OK;

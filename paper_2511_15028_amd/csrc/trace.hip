@@ -274,16 +274,24 @@ int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_ray 
     // fewer rays than lanes: spread over all the waves that the GPU holds, a
     // few to each, so that the waves finish them together (coop.h)
     const uint64_t waves = (uint64_t)resident * (kTraceBlock / 64);
-    const Deal deal = deal_of(n, waves, SL, kRayReserve);
+    // a few rays per wave have room for the safe reserve
+    Deal deal = deal_of(n, waves, SL, depth_first_reserve(h->max_stack));
+    const bool alone = !Count && wholly_coop(deal, n, waves, h->max_stack);
+    if (!alone) deal = deal_of(n, waves, SL, kRayReserve);
     const uint64_t need = ((n + deal.claim - 1) / deal.claim + kTraceBlock / 64 - 1) / (kTraceBlock / 64);
     const unsigned grid = (unsigned)std::min<uint64_t>(resident, need);
     TraceArea ta;
-    if (fixed)
+    if (fixed) {
         ta = TraceArea{*fixed, SpillArea{nullptr, grid * kTraceBlock, 0}};
-    else
+        if (!alone) clear_header(ta.fb, s);
+    } else if (alone) {
+        ta = TraceArea{Fallback{}, SpillArea{nullptr, grid * kTraceBlock, 0}};
+    } else {
         BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
+    }
     kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, rays, n, hits, counts, deal,
                                         ta.fb, ta.sa);
+    if (alone) return BVH_OK;
     k_trace_fallback<Layout, LeafMode, Mode, Count>
         <<<fixed ? kFixedFallbackBlocks : kFallbackBlocks, kTraceBlock, 0, s>>>(
             h->nodes, h->n_nodes, ld, rays, hits, counts, ta.fb);
@@ -390,12 +398,6 @@ int32_t scratch_address(int dev, void **out) {
     return BVH_OK;
 }
 
-// Clears the first n words at p (the fallback header): a kernel rather than
-// a memset node, so that the call can be captured into a graph.
-__global__ __launch_bounds__(kTraceBlock) void k_zero_words(uint32_t *p, uint32_t n) {
-    for (uint32_t k = threadIdx.x; k < n; k += kTraceBlock) p[k] = 0u;
-}
-
 int32_t validate(bvh_handle_t h, const bvh_ray *rays, int64_t n, bvh_hit *hits, int32_t mode,
                  const char *who) {
     if (!h) return set_error(BVH_EINVAL, "%s: null handle", who);
@@ -450,8 +452,6 @@ extern "C" int32_t bvh_trace_noalloc(bvh_handle_t h, const bvh_ray *rays, int64_
     BVH_TRY(scratch_address(h->device, &ptr));
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const Fallback fb = fallback_view(ptr, (uint64_t)n);
-    k_zero_words<<<1, kTraceBlock, 0, s>>>(static_cast<uint32_t *>(ptr),
-                                            (uint32_t)(kFallbackHeaderBytes / 4));
     return launch<false>(h, rays, (uint64_t)n, hits, mode, nullptr, s, &fb);
 }
 

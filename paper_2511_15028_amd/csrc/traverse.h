@@ -1519,6 +1519,15 @@ struct TraceArea {
     SpillArea sa;
 };
 
+// Clears a fallback header: a kernel rather than a memset node, so that the
+// call can be captured into a graph.
+static __global__ __launch_bounds__(kTraceBlock) void k_zero_words(uint32_t *p, uint32_t n) {
+    for (uint32_t k = threadIdx.x; k < n; k += kTraceBlock) p[k] = 0u;
+}
+inline void clear_header(const Fallback &fb, hipStream_t s) {
+    k_zero_words<<<1, kTraceBlock, 0, s>>>(fb.count, (uint32_t)(kFallbackHeaderBytes / 4));
+}
+
 inline int32_t trace_area(hipStream_t s, uint64_t n, uint32_t lanes, TraceArea &ta) {
     const size_t fb_bytes = (fallback_bytes(n) + 255) & ~(size_t)255;
     const size_t sp_bytes = (size_t)lanes * kSpillCap * 8;
@@ -1529,7 +1538,7 @@ inline int32_t trace_area(hipStream_t s, uint64_t n, uint32_t lanes, TraceArea &
     ta.sa.ent = reinterpret_cast<uint64_t *>(sp);
     ta.sa.lanes = lanes;
     ta.sa.cap = kSpillCap;
-    BVH_HIP_TRY(hipMemsetAsync(ta.fb.count, 0, kFallbackHeaderBytes, s));
+    clear_header(ta.fb, s);
     return BVH_OK;
 }
 
