@@ -389,21 +389,26 @@ __global__ __launch_bounds__(kBlock) void k_prim_bounds(const float *verts, int6
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_bounds_final(const float *partial, uint32_t nparts,
-                                                         BuildInfo *info) {
-    __shared__ float red[12][kBlock / kWave];
+// The workgroups' partial bounds to the scene's, in info and in out (12 words
+// of LDS).  Every thread of the block calls it.
+template <int THREADS>
+__device__ inline void fold_bounds(const float *partial, uint32_t nparts, BuildInfo *info,
+                                   float (*red)[THREADS / kWave], float *out) {
     float v[12];
+#pragma unroll
     for (int k = 0; k < 12; k++) {
         bool is_min = (k < 3) || (k >= 6 && k < 9);
         v[k] = is_min ? INFINITY : -INFINITY;
     }
-    for (uint32_t p = threadIdx.x; p < nparts; p += kBlock)
+    for (uint32_t p = threadIdx.x; p < nparts; p += THREADS)
+#pragma unroll
         for (int k = 0; k < 12; k++) {
             bool is_min = (k < 3) || (k >= 6 && k < 9);
             float x = partial[12 * (size_t)p + k];
             v[k] = is_min ? fminf(v[k], x) : fmaxf(v[k], x);
         }
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+#pragma unroll
     for (int k = 0; k < 12; k++) {
         bool is_min = (k < 3) || (k >= 6 && k < 9);
         float r = is_min ? wave_min(v[k]) : wave_max(v[k]);
@@ -414,12 +419,21 @@ __global__ __launch_bounds__(kBlock) void k_bounds_final(const float *partial, u
         const int k = threadIdx.x;
         bool is_min = (k < 3) || (k >= 6 && k < 9);
         float r = red[k][0];
-        for (int j = 1; j < kBlock / kWave; j++) r = is_min ? fminf(r, red[k][j]) : fmaxf(r, red[k][j]);
+        for (int j = 1; j < THREADS / kWave; j++) r = is_min ? fminf(r, red[k][j]) : fmaxf(r, red[k][j]);
+        out[k] = r;
         if (k < 3) info->slo[k] = r;
         else if (k < 6) info->shi[k - 3] = r;
         else if (k < 9) info->clo[k - 6] = r;
         else info->chi[k - 9] = r;
     }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kBlock) void k_bounds_final(const float *partial, uint32_t nparts,
+                                                         BuildInfo *info) {
+    __shared__ float red[12][kBlock / kWave];
+    __shared__ float out[12];
+    fold_bounds<kBlock>(partial, nparts, info, red, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -436,20 +450,15 @@ __device__ inline uint32_t quantize_axis_bits(float x, float lo, float inv_ext, 
     return (uint32_t)u;
 }
 
-template <typename KeyT>
-__global__ __launch_bounds__(kBlock) void k_morton(const Box *pbox, uint32_t n,
-                                                   const BuildInfo *info, int bits,
-                                                   KeyT *keys, uint32_t *vals) {
-    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    Box b = pbox[i];
+// The key of one box; clo and chi bound the box centres.
+__device__ inline uint64_t morton_key(const Box &b, const float *clo, const float *chi, int bits) {
     float c[3] = {0.5f * b.lo.x + 0.5f * b.hi.x, 0.5f * b.lo.y + 0.5f * b.hi.y,
                   0.5f * b.lo.z + 0.5f * b.hi.z};
     uint32_t q[3];
     for (int a = 0; a < 3; a++) {
-        float ext = info->chi[a] - info->clo[a];
+        float ext = chi[a] - clo[a];
         float inv = ext > 0.0f ? 1.0f / ext : 0.0f;
-        q[a] = quantize_axis_bits(c[a], info->clo[a], inv, bits);
+        q[a] = quantize_axis_bits(c[a], clo[a], inv, bits);
     }
     // bit k of x, y, z goes to key bit 3k+2, 3k+1, 3k
     uint64_t key = 0;
@@ -458,7 +467,17 @@ __global__ __launch_bounds__(kBlock) void k_morton(const Box *pbox, uint32_t n,
         key |= (uint64_t)((q[1] >> bit) & 1u) << (3 * bit + 1);
         key |= (uint64_t)((q[2] >> bit) & 1u) << (3 * bit);
     }
-    keys[i] = (KeyT)key;  // 3 * bits <= the key width (checked by the caller)
+    return key;
+}
+
+template <typename KeyT>
+__global__ __launch_bounds__(kBlock) void k_morton(const Box *pbox, uint32_t n,
+                                                   const BuildInfo *info, int bits,
+                                                   KeyT *keys, uint32_t *vals) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= n) return;
+    // 3 * bits <= the key width (checked by the caller)
+    keys[i] = (KeyT)morton_key(pbox[i], info->clo, info->chi, bits);
     vals[i] = i;
 }
 
@@ -522,6 +541,39 @@ __global__ __launch_bounds__(kBlock) void k_radix_offsets(uint32_t *hist, uint32
     if (threadIdx.x == 0) total[blockIdx.x] = carry;
 }
 
+// Moves a wave's keys (row r of the lane: position first + r * 64) to their
+// places in the sorted order of one digit, stably: run[d] is the place of the
+// wave's next key of digit d.
+template <int ROWS, typename KeyT, typename ValT>
+__device__ inline void rank_rows(const KeyT (&key)[ROWS], const uint32_t (&val)[ROWS], int rows,
+                                 uint32_t first, uint32_t n, int shift, uint32_t *run, KeyT *skey,
+                                 ValT *sval) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+#pragma unroll
+    for (int r = 0; r < ROWS; r++) {
+        if (r >= rows) break;  // the same in the wave
+        const bool valid = first + r * kWave < n;
+        const uint32_t d = (uint32_t)(key[r] >> shift) & (kRadix - 1);
+        uint64_t peers = __ballot(valid);
+#pragma unroll
+        for (int b = 0; b < 8; b++) {
+            const bool bit = (d >> b) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const uint32_t start = valid ? run[d] : 0u;
+        __builtin_amdgcn_wave_barrier();
+        if (valid) {
+            const uint32_t pos = start + (uint32_t)__popcll(peers & lt_mask);
+            skey[pos] = key[r];
+            sval[pos] = (ValT)val[r];
+            if ((peers & lt_mask) == 0) run[d] = start + (uint32_t)__popcll(peers);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 template <typename KeyT>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *keys_in,
                                                           const uint32_t *vals_in,
@@ -574,29 +626,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT *keys_in,
         }
     }
     __syncthreads();
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-    uint32_t *wrun = wcount[w];
-#pragma unroll
-    for (int r = 0; r < kSortItems; r++) {
-        const bool valid = wbase + r * kWave + lane < n;
-        const uint32_t d = (uint32_t)(key[r] >> shift) & (kRadix - 1);
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; b++) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
-        }
-        const uint32_t start = valid ? wrun[d] : 0u;
-        __builtin_amdgcn_wave_barrier();
-        if (valid) {
-            const uint32_t pos = start + (uint32_t)__popcll(peers & lt_mask);
-            skey[pos] = key[r];
-            sval[pos] = val[r];
-            if ((peers & lt_mask) == 0) wrun[d] = start + (uint32_t)__popcll(peers);
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
+    rank_rows<kSortItems>(key, val, kSortItems, wbase + lane, n, shift, wcount[w], skey, sval);
     __syncthreads();
     const uint32_t m = min((uint32_t)kSortTile, n - base);
     for (uint32_t p = threadIdx.x; p < m; p += kBlock) {
@@ -625,10 +655,10 @@ template <typename KeyT>
 struct KeyWindow {
     const KeyT *g;
     const KeyT *lds;
-    int w0;
+    int w0, len;
     __device__ KeyT at(int j) const {
         const unsigned k = (unsigned)(j - w0);
-        return k < (unsigned)kKarrasWindow ? lds[k] : g[j];
+        return k < (unsigned)len ? lds[k] : g[j];
     }
 };
 
@@ -709,7 +739,7 @@ __global__ __launch_bounds__(kBlock) void k_karras(const KeyT *keys, int n, int3
         if (j >= 0 && j < n) sk[k] = keys[j];
     }
     __syncthreads();
-    const KeyWindow<KeyT> kw{keys, sk, w0};
+    const KeyWindow<KeyT> kw{keys, sk, w0, kKarrasWindow};
     const int i = blockIdx.x * kBlock + threadIdx.x;
     uint32_t leaves = 0;
     if (i < n - 1) leaves = karras_node(kw, n, i, ileft, iright, ifirst, icount, iaxis, parent, L);
@@ -721,6 +751,82 @@ __global__ __launch_bounds__(kBlock) void k_karras(const KeyT *keys, int n, int3
     }
 }
 
+
+// Small meshes: the scene bounds, the keys, the whole sort and the hierarchy in
+// one workgroup with the keys in LDS.  Apart they are 12 launches of 2 to 8 us
+// (three of them per sort pass), each a chain of loads that a single workgroup
+// of work does not hide.  Builds of 300 / 1,024 / 2,048 / 4,096 triangles 177 /
+// 168 / 160 / 160 us apart, 137 / 127 / 123 / 147 together; of 8,192 166 and 179,
+// so the line lies where the gain ends.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / kWave;
+constexpr int kSmallRows = 8;
+constexpr uint32_t kSmallMax = 4096;
+static_assert(kSmallMax <= kSmallThreads * kSmallRows && kSmallMax <= 65536, "positions in 16 bits");
+
+__global__ __launch_bounds__(kSmallThreads) void k_small_hierarchy(
+    const Box *pbox, uint32_t n, const float *partial, uint32_t nparts, BuildInfo *info, int bits,
+    uint32_t *perm, int32_t *ileft, int32_t *iright, uint32_t *ifirst, uint32_t *icount,
+    uint8_t *iaxis, int32_t *parent, int L, uint32_t *leaf_slots) {
+    __shared__ uint32_t skey[kSmallMax];
+    __shared__ uint16_t sval[kSmallMax];
+    __shared__ uint32_t wcount[kSmallWaves][kRadix];
+    __shared__ uint32_t wsum[kSmallWaves];
+    __shared__ float red[12][kSmallWaves];
+    __shared__ float bounds[12];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    // each wave holds consecutive rows of 64 primitives
+    const int rows = (int)((n + kSmallThreads - 1) / kSmallThreads);
+    const uint32_t first = (uint32_t)(w * rows) * kWave + lane;
+    uint32_t key[kSmallRows], val[kSmallRows];
+    fold_bounds<kSmallThreads>(partial, nparts, info, red, bounds);
+#pragma unroll
+    for (int r = 0; r < kSmallRows; r++) {
+        key[r] = 0;
+        val[r] = first + r * kWave;
+        if (r < rows && val[r] < n) key[r] = (uint32_t)morton_key(pbox[val[r]], bounds + 6, bounds + 9, bits);
+    }
+    for (int shift = 0; shift < 3 * bits; shift += 8) {
+        for (int k = threadIdx.x; k < kSmallWaves * kRadix; k += kSmallThreads) wcount[0][k] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSmallRows; r++)
+            if (r < rows && first + r * kWave < n) atomicAdd(&wcount[w][(key[r] >> shift) & (kRadix - 1)], 1u);
+        __syncthreads();
+        // thread d: the place of digit d's first key per wave
+        uint32_t sum = 0, tot;
+        if (threadIdx.x < kRadix)
+            for (int k = 0; k < kSmallWaves; k++) sum += wcount[k][threadIdx.x];
+        uint32_t run = block_excl_scan<kSmallThreads>(sum, &tot, wsum);
+        if (threadIdx.x < kRadix)
+            for (int k = 0; k < kSmallWaves; k++) {
+                const uint32_t c = wcount[k][threadIdx.x];
+                wcount[k][threadIdx.x] = run;
+                run += c;
+            }
+        __syncthreads();
+        rank_rows<kSmallRows>(key, val, rows, first, n, shift, wcount[w], skey, sval);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSmallRows; r++) {
+            const uint32_t i = first + r * kWave;
+            if (r >= rows || i >= n) break;
+            key[r] = skey[i];
+            val[r] = sval[i];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kSmallRows; r++)
+        if (r < rows && first + r * kWave < n) perm[first + r * kWave] = val[r];
+    const KeyWindow<uint32_t> kw{nullptr, skey, 0, (int)n};
+    uint32_t leaves = 0;
+    for (int i = threadIdx.x; i < (int)n - 1; i += kSmallThreads)
+        leaves += karras_node(kw, (int)n, i, ileft, iright, ifirst, icount, iaxis, parent, L);
+    if (leaf_slots) {  // as in k_karras
+        leaves = wave_reduce<uint32_t>(leaves, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+        if (lane == 0 && leaves) atomicAdd(&leaf_slots[w * kSlotStride], leaves);
+    }
+}
 
 // ---------------------------------------------------------------------------
 // a5: node boxes.  Every node of the hierarchy covers a contiguous range of
@@ -3095,7 +3201,8 @@ int32_t build_impl(const float *verts, int64_t n_verts, const int32_t *tris, int
     // a1, a2
     const uint32_t nbp = (uint32_t)(((uint64_t)n + kPrimItems * kBlock - 1) / (kPrimItems * kBlock));
     k_prim_bounds<<<nbp, kBlock, 0, s>>>(verts, n_verts, tris, n, pbox, partial, info);
-    k_bounds_final<<<1, kBlock, 0, s>>>(partial, nbp, info);
+    const bool small = h->builder == BVH_BUILDER_LBVH && (uint32_t)n <= kSmallMax;
+    if (!small) k_bounds_final<<<1, kBlock, 0, s>>>(partial, nbp, info);
     const uint32_t *perm = nullptr;
     SideStream *side = nullptr;
     // a8 leaf data for the wide layouts, queued as soon as the order is final,
@@ -3131,6 +3238,15 @@ int32_t build_impl(const float *verts, int64_t n_verts, const int32_t *tris, int
         BVH_TRY(check_launch("bounds"));
         SahTree tr{ileft, iright, parent, ifirst, icount, iaxis, n};
         BVH_TRY(sah_topology(pbox, (uint32_t)n, vals[0], tr, L, s));
+        perm = vals[0];
+        BVH_TRY(leaf_data_early());
+    } else if (small) {
+        // a2, a3, a4 in one launch; at most 3 * 8 key bits at this size
+        karras_leaves = wide && n > 1 ? bound_slots + 2 * kMaxSlots * kSlotStride : nullptr;
+        k_small_hierarchy<<<1, kSmallThreads, 0, s>>>(pbox, (uint32_t)n, partial, nbp, info,
+                                                      morton_bits(n), vals[0], ileft, iright, ifirst,
+                                                      icount, iaxis, parent, L, karras_leaves);
+        BVH_TRY(check_launch("small hierarchy"));
         perm = vals[0];
         BVH_TRY(leaf_data_early());
     } else {

@@ -8,10 +8,11 @@ those sizes must be the oracle's.
 """
 import threading
 
+import numpy as np
 import pytest
 
 from paper_2511_15028_amd import workloads as W
-from test_gpu_parity import dev, B
+from test_gpu_parity import B, check_closest, dev, gpu_trace, oracle_ref
 from test_gpu_sah import check_tree
 
 torch = pytest.importorskip("torch")
@@ -75,3 +76,40 @@ def test_kept_memory_is_bounded():
         h.close()
     # every allocation may be rounded up to 2 MiB pages
     assert torch.cuda.mem_get_info()[0] - before >= held - KEPT - (2 << 20) * 24
+
+
+
+def morton_order(verts, tris, bits):
+    """The stable order of the triangles by the Morton key of their boxes' centres, in float32."""
+    f, p = np.float32, verts[tris]
+    c = f(0.5) * p.min(1) + f(0.5) * p.max(1)
+    lo, ext = c.min(0), c.max(0) - c.min(0)
+    inv = np.where(ext > 0, f(1) / np.where(ext > 0, ext, f(1)), f(0)).astype(f)
+    cells = f(2 ** bits)
+    q = np.clip((c - lo) * inv * cells, f(0), cells - f(1)).astype(np.uint64)
+    key = np.zeros(len(tris), np.uint64)
+    for b in range(bits):
+        for a in range(3):
+            key |= ((q[:, a] >> np.uint64(b)) & np.uint64(1)) << np.uint64(3 * b + 2 - a)
+    return np.argsort(key, kind="stable")
+
+
+@pytest.mark.parametrize("layout", ["bvh4", "bvh8_q16", "aabb2"])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 1023, 1025, 4095, 4096, 4097])
+def test_small_hierarchy(orc, n, layout):
+    """The sizes around which the order and hierarchy of a small mesh, made by one workgroup, change
+    rows, and where the separate kernels take over."""
+    v, t = W.soup_scene(n, seed=90 + n, spread=0.1)
+    t = t.copy()
+    t[n // 2:n // 2 + 40] = t[0]  # equal keys keep the order of the input
+    h = B().build(dev(v), dev(t), layout, 4, "indexed")
+    lg = max(1, (n - 1).bit_length())
+    bits = max(4, (lg + 2) // 3 + 4)
+    if (3 * bits) % 8 in (1, 2, 3):
+        bits -= 1
+    np.testing.assert_array_equal(np.frombuffer(h.read_buffer(1), np.int32), morton_order(v, t, bits))
+    # every triangle is found: the hits are the oracle's
+    rays = W.uniform_rays(2000, seed=n)
+    prim, tuv = gpu_trace(h, rays)
+    check_closest(orc, v, t, rays, prim, tuv, oracle_ref(orc, v, t, rays))
+    h.close()
