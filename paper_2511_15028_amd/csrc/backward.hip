@@ -14,6 +14,8 @@
 // Cramer's rule on the rows d, -e1, -e2 of J^T, whose determinant is
 // d . (e1 x e2) = -det (det = e1 . (d x e2) of the forward test):
 //   lam = -(g_t (e1 x e2) + g_u (d x e2) + g_v (e1 x d)) / det.
+#include <algorithm>
+
 #include "traverse.h"
 
 namespace bvhlib {
@@ -151,14 +153,14 @@ __global__ __launch_bounds__(kBlock) void k_backward(const float *verts, int64_t
 //     range's records from every segment, sums them in a dense LDS
 //     accumulator and adds the sums to grad_verts (the range is its own, so
 //     plain loads and stores).
-// Ranges: shift in [8, 12] with at most kPartMaxRanges ranges, so up to
-// 2^22 vertices; larger meshes use k_backward.
+// Ranges: shift in [8, 12] with at most kPartMaxRanges ranges (kPartMoreRanges
+// for many rays), so up to 2^22 vertices; larger meshes use k_backward.
 // ---------------------------------------------------------------------------
 constexpr int kPartThreads = 256;
 constexpr int kPartRaysPerThread = 4;
 constexpr int kPartRays = kPartThreads * kPartRaysPerThread;
 constexpr int kPartRecs = 3 * kPartRays;
-constexpr int kPartMaxRanges = 1024;
+constexpr int kPartMaxRanges = 1024, kPartMoreRanges = 2048;
 constexpr int kPartMinShift = 8, kPartMaxShift = 12;
 constexpr int kSumThreads = 512;
 
@@ -193,11 +195,12 @@ __device__ inline uint32_t block_excl_scan_u32(uint32_t x, uint32_t *wsum, uint3
     return off + inc - x;
 }
 
+template <int MAX>
 __global__ __launch_bounds__(kPartThreads) void k_backward_part(
     const float *verts, int64_t n_verts, const int32_t *tris, int64_t n_tris, const bvh_ray *rays,
     uint64_t n, const bvh_hit *hits, const float *grad_hits, float *grad_rays, int shift,
     uint32_t n_ranges, VertRec *seg, uint32_t *offs) {
-    __shared__ uint32_t cnt[kPartMaxRanges];
+    __shared__ uint32_t cnt[MAX];
     __shared__ uint32_t wsum[kPartThreads / 64];
     __shared__ VertRec sorted[kPartRecs];
     for (uint32_t p = threadIdx.x; p < n_ranges; p += kPartThreads) cnt[p] = 0;
@@ -227,7 +230,7 @@ __global__ __launch_bounds__(kPartThreads) void k_backward_part(
     }
     __syncthreads();
     // exclusive offsets of the ranges; each thread scans a run of them
-    constexpr int kRun = kPartMaxRanges / kPartThreads;
+    constexpr int kRun = MAX / kPartThreads;
     uint32_t c[kRun], sum = 0;
 #pragma unroll
     for (int k = 0; k < kRun; k++) {
@@ -273,33 +276,55 @@ __global__ __launch_bounds__(kPartThreads) void k_backward_part(
 // has several independent record loads in flight instead of a chain per
 // segment.
 //
-// Summation.  kPrivate (ranges of 2^kSumPrivShift vertices): every wave owns
+// Summation.  kPrivate (ranges of at most 2^kSumPrivShift vertices): every wave owns
 // an LDS accumulator of the range, so no two waves touch one word; within a
 // wave instruction, the lanes holding one vertex find each other with one
-// ballot per bit of the vertex's index in the range, the lowest of them adds
-// the others' values (ds_bpermute) and alone updates the accumulator with a
-// plain read and write.  The copies are added at the end.  LDS float atomics
+// ballot per bit of the vertex's index in the range, their values are added
+// pairwise (ds_bpermute) and the lowest of them alone updates the accumulator
+// with a plain read and write.  (Neighbouring rays see the same vertices: with
+// the others' values taken one by one, a wave waited for its most frequent
+// vertex: 62 us against 38 for 0.9 M camera rays on 10,242 vertices.)  The copies are added at the end.  LDS float atomics
 // (ds_add_f32) cost about 32 LDS cycles per wave instruction, three per
 // record; the plain update costs a read and a write per record.  Larger
 // ranges (whose copies would not fit in LDS) share one accumulator updated
 // with LDS atomics.
 constexpr int kSumMaxBlocks = 2048;  // segments per pass
 constexpr int kSumUnroll = 4;
-constexpr int kSumPrivShift = 8;
+constexpr int kSumPrivShift = 9;
+static_assert(kSumPrivShift == kPartMinShift + 1, "private accumulators: either shift");
 constexpr int kSumWaves = kSumThreads / 64;
+
+// Meshes of few ranges: a range's segments are shared out among several blocks
+// (slices), so that about kSumBlocks blocks, which the GPU holds at once, have
+// work; each writes its sums to the work area and k_backward_fold adds them to
+// grad_verts.  One block per range left most of the GPU idle: 5,907 vertices and
+// 1.7 M rays 324 us in one slice, 67 in 42; 10,242 vertices and 0.9 M camera
+// rays with their trace 812 and 281.
+// A slice has at least kSliceSegs segments and, if every ray hits, kSliceRecs
+// records: with fewer, its fixed cost and the extra launch outweigh them (50,000
+// vertices and rays: 21 us in one slice, 29 in five).
+constexpr uint32_t kSumBlocks = 1024;
+constexpr uint32_t kSliceSegs = 4;
+constexpr uint64_t kSliceRecs = 2048;
+inline uint32_t sum_slices(uint64_t n, uint64_t n_blocks, uint32_t ranges) {
+    const uint64_t s = std::min<uint64_t>({kSumBlocks / ranges, n_blocks / kSliceSegs,
+                                           3 * n / ranges / kSliceRecs});
+    return (uint32_t)std::max<uint64_t>(1, s);
+}
 
 __device__ inline float bperm_f(float x, uint32_t src) {
     return __int_as_float(__builtin_amdgcn_ds_bpermute((int)(src << 2), __float_as_int(x)));
 }
 
-template <bool kPrivate>
+// kPrivate: log2 of the range's vertices, or 0 for the shared accumulator.
+template <int kPrivate>
 __global__ __launch_bounds__(kSumThreads) void k_backward_sum(const VertRec *seg,
                                                               const uint32_t *offs,
                                                               uint32_t n_blocks, int shift,
                                                               uint32_t n_ranges, int64_t n_verts,
-                                                              float *grad_verts) {
-    // kPrivate: kSumWaves copies of 3 * 2^kSumPrivShift floats; otherwise one
-    // copy of 3 * 2^shift floats (dynamic)
+                                                              float *grad_verts, float *partial) {
+    // kPrivate: kSumWaves copies of 3 * 2^kPrivate floats; otherwise one copy of
+    // 3 * 2^shift floats (dynamic)
     extern __shared__ float acc[];
     __shared__ uint32_t lo[kSumMaxBlocks];
     __shared__ uint32_t start[kSumMaxBlocks + 1];
@@ -312,8 +337,12 @@ __global__ __launch_bounds__(kSumThreads) void k_backward_sum(const VertRec *seg
     float *const my = acc + (kPrivate ? (threadIdx.x >> 6) * 3 * nv : 0);
     const uint32_t lane = threadIdx.x & 63;
     constexpr int kPer = kSumMaxBlocks / kSumThreads;
-    for (uint32_t b0 = 0; b0 < n_blocks; b0 += kSumMaxBlocks) {
-        const uint32_t nb = min((uint32_t)kSumMaxBlocks, n_blocks - b0);
+    // this slice's segments: blockIdx.y, + gridDim.y, ... (neighbouring segments see
+    // the same part of the mesh, so every slice takes some of each part)
+    const uint32_t slices = gridDim.y, slice = blockIdx.y;
+    const uint32_t n_mine = (n_blocks - slice + slices - 1) / slices;  // slice < n_blocks
+    for (uint32_t b0 = 0; b0 < n_mine; b0 += kSumMaxBlocks) {
+        const uint32_t nb = min((uint32_t)kSumMaxBlocks, n_mine - b0);
         // this thread's run of kPer segments: their starts and counts
         uint32_t c[kPer], sum = 0;
 #pragma unroll
@@ -321,8 +350,9 @@ __global__ __launch_bounds__(kSumThreads) void k_backward_sum(const VertRec *seg
             const uint32_t j = k * kSumThreads + threadIdx.x;  // coalesced over the rows
             uint32_t l = 0, h = 0;
             if (j < nb) {
-                l = offs[(size_t)p * n_blocks + b0 + j];
-                h = min(offs[(size_t)(p + 1) * n_blocks + b0 + j], (uint32_t)kPartRecs);
+                const uint32_t b = (b0 + j) * slices + slice;
+                l = offs[(size_t)p * n_blocks + b];
+                h = min(offs[(size_t)(p + 1) * n_blocks + b], (uint32_t)kPartRecs);
                 h = h > l ? h : l;
                 lo[j] = l;
             }
@@ -365,7 +395,8 @@ __global__ __launch_bounds__(kSumThreads) void k_backward_sum(const VertRec *seg
                         const uint32_t m = (a + b) >> 1;
                         if (start[m] <= q) a = m; else b = m;
                     }
-                    const VertRec *rec = seg + (size_t)(b0 + a) * kPartRecs + lo[a] + (q - start[a]);
+                    const VertRec *rec = seg + ((size_t)(b0 + a) * slices + slice) * kPartRecs +
+                                         lo[a] + (q - start[a]);
                     x[u] = *reinterpret_cast<const float4 *>(rec);
                 }
             }
@@ -373,28 +404,34 @@ __global__ __launch_bounds__(kSumThreads) void k_backward_sum(const VertRec *seg
             for (int u = 0; u < kSumUnroll; u++) {
                 const uint32_t local = (uint32_t)(__float_as_int(x[u].x) - (int32_t)v0);
                 const bool mine = ok[u] && local < nv;  // always in range for a consistent segment
-                if constexpr (kPrivate) {
+                if constexpr (kPrivate > 0) {
                     uint64_t peers = __builtin_amdgcn_ballot_w64(mine);
+                    if (peers == 0) continue;
 #pragma unroll
-                    for (int b = 0; b < kSumPrivShift; b++) {
+                    for (int b = 0; b < kPrivate; b++) {
                         const bool bit = (local >> b) & 1u;
                         const uint64_t m = __builtin_amdgcn_ballot_w64(bit);
                         peers &= bit ? m : ~m;
                     }
-                    const uint64_t self = uint64_t(1) << lane;
-                    const bool leader = mine && (peers & (self - 1)) == 0;
-                    uint64_t rest = leader ? peers & ~self : 0;
+                    if (!mine) peers = 0;
+                    const uint64_t below = (uint64_t(1) << lane) - 1;
+                    const bool leader = mine && (peers & below) == 0;
                     float gx = x[u].y, gy = x[u].z, gz = x[u].w;
-                    while (__builtin_amdgcn_ballot_w64(rest != 0)) {
-                        const uint32_t src = rest ? (uint32_t)__builtin_ctzll(rest) : lane;
-                        const float ax = bperm_f(x[u].y, src), ay = bperm_f(x[u].z, src),
-                                    az = bperm_f(x[u].w, src);
-                        if (rest) {
+                    // of the lanes left in a group, every second one gives its sum
+                    // to the one before it and drops out
+                    for (;;) {
+                        const uint64_t above = peers & ~(below | (uint64_t(1) << lane));
+                        const bool even = (__builtin_popcountll(peers & below) & 1) == 0;
+                        const bool take = even && above != 0;
+                        if (__builtin_amdgcn_ballot_w64(take) == 0) break;
+                        const uint32_t src = take ? (uint32_t)__builtin_ctzll(above) : lane;
+                        const float ax = bperm_f(gx, src), ay = bperm_f(gy, src), az = bperm_f(gz, src);
+                        if (take) {
                             gx += ax;
                             gy += ay;
                             gz += az;
-                            rest &= rest - 1;
                         }
+                        peers = even ? peers & __builtin_amdgcn_ballot_w64(even) : 0;
                     }
                     if (leader) {
                         float *a = my + 3 * local;
@@ -413,19 +450,57 @@ __global__ __launch_bounds__(kSumThreads) void k_backward_sum(const VertRec *seg
     }
     const int64_t cnt = min((int64_t)nv, n_verts - v0);
     float *g = grad_verts + 3 * v0;
+    float *part = partial + 3 * ((int64_t)slice * n_verts + v0);
     for (int64_t q = threadIdx.x; q < 3 * cnt; q += kSumThreads) {
         float a = acc[q];
         for (uint32_t w = 1; w < n_acc; w++) a += acc[w * 3 * nv + q];
-        g[q] += a;
+        if (slices == 1) g[q] += a;
+        else part[q] = a;
     }
 }
 
+// grad_verts (m floats) += the slices' sums.
+__global__ __launch_bounds__(kBlock) void k_backward_fold(const float *partial, uint32_t slices,
+                                                          int64_t m, float *grad_verts) {
+    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (q >= m) return;
+    float a = 0.0f;
+#pragma unroll 8
+    for (uint32_t s = 0; s < slices; s++) a += partial[(int64_t)s * m + q];
+    grad_verts[q] += a;
+}
+
 // Smallest range shift (within [kPartMinShift, kPartMaxShift]) that covers
-// n_verts with at most kPartMaxRanges ranges; -1 when none does.
-inline int part_shift(int64_t n_verts) {
+// n_verts with at most max_ranges ranges; -1 when none does.
+inline int part_shift(int64_t n_verts, int64_t max_ranges) {
     for (int s = kPartMinShift; s <= kPartMaxShift; s++)
-        if (((n_verts + (int64_t(1) << s) - 1) >> s) <= kPartMaxRanges) return s;
+        if (((n_verts + (int64_t(1) << s) - 1) >> s) <= max_ranges) return s;
     return -1;
+}
+
+// Launch plan for n rays on n_verts vertices.  Above 2^19 vertices, twice as
+// many, smaller ranges when each still gets kDenseRecs records if every ray
+// hits (the parting kernel pays for the larger table with a third of its
+// resident blocks): 700,000 vertices and 1 M rays 138 -> 88 us, but 100,000
+// rays 34 -> 40.  Ranges of 2^9 vertices have private accumulators under the
+// same condition (490,000 vertices, 500,000 rays: 65 -> 50 us; 1 M vertices,
+// 20,000 rays 29 -> 45), those of 2^8 always.
+constexpr uint64_t kDenseRecs = 1024;
+struct BackwardPlan {
+    int shift;
+    uint32_t ranges;
+    bool more, priv;
+};
+inline BackwardPlan backward_plan(int64_t n_verts, uint64_t n) {
+    BackwardPlan p{};
+    p.more = n_verts > (int64_t(kPartMaxRanges) << 9) && 3 * n >= kDenseRecs * kPartMoreRanges;
+    p.shift = part_shift(n_verts, p.more ? kPartMoreRanges : kPartMaxRanges);
+    // 2^22 vertices are the limit of either table
+    if (n_verts > (int64_t(kPartMaxRanges) << kPartMaxShift)) p.shift = -1;
+    if (p.shift < 0) return p;
+    p.ranges = (uint32_t)((n_verts + (int64_t(1) << p.shift) - 1) >> p.shift);
+    p.priv = p.shift < kSumPrivShift || (p.shift == kSumPrivShift && 3 * n >= kDenseRecs * p.ranges);
+    return p;
 }
 
 }  // namespace
@@ -448,26 +523,33 @@ extern "C" int32_t bvh_trace_backward(const float *verts, int64_t n_verts, const
     if ((uint64_t)n > (uint64_t)0xFFFFFFFFu * kBlock)
         return set_error(BVH_EUNSUPPORTED, "bvh_trace_backward: too many rays");
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const int shift = part_shift(n_verts);
+    const BackwardPlan plan = backward_plan(n_verts, (uint64_t)n);
+    const int shift = plan.shift;
     if (n_verts > 0 && shift >= 0) {
-        const uint32_t ranges = (uint32_t)((n_verts + (int64_t(1) << shift) - 1) >> shift);
+        const uint32_t ranges = plan.ranges;
         const uint64_t blocks = ((uint64_t)n + kPartRays - 1) / kPartRays;
         const size_t seg_bytes = (size_t)blocks * kPartRecs * sizeof(VertRec);
         const size_t off_bytes = (size_t)blocks * (ranges + 1) * sizeof(uint32_t);
+        const uint32_t slices = sum_slices((uint64_t)n, blocks, ranges);
+        const size_t part_bytes = slices > 1 ? (size_t)slices * (size_t)n_verts * 3 * sizeof(float) : 0;
         void *ws = nullptr;
-        BVH_TRY(stream_workspace(s, kAreaBackward, seg_bytes + off_bytes, &ws));
+        BVH_TRY(stream_workspace(s, kAreaBackward, seg_bytes + off_bytes + part_bytes, &ws));
         VertRec *seg = static_cast<VertRec *>(ws);
         uint32_t *offs = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + seg_bytes);
-        k_backward_part<<<(unsigned)blocks, kPartThreads, 0, s>>>(
+        auto part = plan.more ? k_backward_part<kPartMoreRanges> : k_backward_part<kPartMaxRanges>;
+        part<<<(unsigned)blocks, kPartThreads, 0, s>>>(
             verts, n_verts, tris, n_tris, rays, (uint64_t)n, hits, grad_hits, grad_rays, shift,
             ranges, seg, offs);
-        if (shift == kSumPrivShift)
-            k_backward_sum<true><<<ranges, kSumThreads, kSumWaves * (3u << shift) * sizeof(float),
-                                   s>>>(seg, offs, (uint32_t)blocks, shift, ranges, n_verts,
-                                        grad_verts);
-        else
-            k_backward_sum<false><<<ranges, kSumThreads, (3u << shift) * sizeof(float), s>>>(
-                seg, offs, (uint32_t)blocks, shift, ranges, n_verts, grad_verts);
+        float *partial = reinterpret_cast<float *>(static_cast<char *>(ws) + seg_bytes + off_bytes);
+        const dim3 grid(ranges, slices);
+        auto sum = !plan.priv ? k_backward_sum<0>
+                              : (shift == kSumPrivShift ? k_backward_sum<kSumPrivShift>
+                                                        : k_backward_sum<kPartMinShift>);
+        sum<<<grid, kSumThreads, (plan.priv ? kSumWaves : 1) * (3u << shift) * sizeof(float), s>>>(
+            seg, offs, (uint32_t)blocks, shift, ranges, n_verts, grad_verts, partial);
+        if (slices > 1)
+            k_backward_fold<<<(unsigned)((3 * n_verts + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+                partial, slices, 3 * n_verts, grad_verts);
     } else {
         const unsigned grid = (unsigned)(((uint64_t)n + kBlock - 1) / kBlock);
         k_backward<<<grid, kBlock, 0, s>>>(verts, n_verts, tris, n_tris, rays, (uint64_t)n, hits,
