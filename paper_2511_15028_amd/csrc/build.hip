@@ -2283,14 +2283,17 @@ int32_t pack_wide(TreeView tv, volatile uint32_t *nleaf_word, int32_t *cand_all,
 // bounds of the children that the next level bins.  A chunk's bins hold what
 // the partition needs of the other chunks (how many of their primitives go
 // left), so no flag is written and nothing is scanned over the whole array.
+// Nodes of at most kSahMid primitives leave the levels: a workgroup each takes
+// them down to small ones.
 // A level costs its launches' latency rather than memory traffic: 300,000
-// triangles spend 600 us on 19 levels (with separate launches for bounds, flags,
-// their scan and the counts' publication: 1,110 us).  Nodes of at most
+// triangles spend 430 us on 13 levels (with separate launches for bounds, flags,
+// their scan and the counts' publication, 58 us a level).  Nodes of at most
 // kSahSmall primitives are finished by one wave each with the primitives held
 // in the lanes.
 // ---------------------------------------------------------------------------
 constexpr int kSahBins = 32;
 constexpr uint32_t kSahSmall = 64;
+constexpr uint32_t kSahMid = 1024;
 constexpr uint32_t kSahChunk = 2048;
 constexpr int kSahMaxLevels = kStackMax + 1;
 constexpr uint32_t kSahBinWords = 3 * kSahBins * 7;  // per node: count + ordered box per bin
@@ -2306,7 +2309,7 @@ struct SahSplit {
     int32_t k;     // last bin of the left side (-1: index median)
     uint32_t nl;   // primitives on the left
     uint32_t id;   // the node's id
-    uint32_t slot[2];  // per side: the child's task in the next level (kNoSlot: small)
+    uint32_t slot[2];  // per side: the child's task in the next level (kNoSlot: none)
 };
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 
@@ -2627,40 +2630,15 @@ __global__ __launch_bounds__(kBlock) void k_sah_merge(SahLevel lv) {
     }
 }
 
-// The sweep and record of node t (one wave); leaves its task, id and split
-// (but for the slots) in tk and sp, the same in every lane.
-__device__ inline void sah_split_node(SahLevel lv, SahTree tr, uint32_t *root_nat, bool root_level,
-                                      uint32_t t, int lane, SahTask &tk, SahSplit &sp) {
-    tk = lv.task[t];
-    const uint32_t nch = (tk.count + kSahChunk - 1) / kSahChunk, c0 = lv.tc0[t];
-    const uint32_t ng = nch < 2 ? 1u : merge_groups(nch, lv.groups);
-    // one chunk: its chunk's bins; several in one group: the merged bins;
-    // several groups: the groups' partial bins, combined here
-    const int *gb = nch < 2 ? lv.cbins + (size_t)c0 * kSahBinWords
-                            : (ng > 1 ? lv.gbins + (size_t)t * kMergeGroups * kSahBinWords
-                                      : lv.bins + (size_t)t * kSahBinWords);
-    const SahFrame f = sah_task_frame(lv.cb + 6 * t);
-    // x's bins in lanes 0-31 and y's in lanes 32-63, then z's in lanes 0-31
-    const int *bin0 = gb + lane * 7, *bin1 = gb + (2 * kSahBins + (lane & (kSahBins - 1))) * 7;
-    int w0[7], w1[7];
-#pragma unroll
-    for (int j = 0; j < 7; j++) {
-        w0[j] = bin0[j];
-        w1[j] = bin1[j];
-    }
-#pragma unroll 4
-    for (uint32_t g = 1; g < ng; g++) {
-        const size_t at = (size_t)g * kSahBinWords;
-#pragma unroll
-        for (int j = 0; j < 7; j++) {
-            w0[j] = bin_combine((uint32_t)j, w0[j], bin0[at + j]);
-            w1[j] = bin_combine((uint32_t)j, w1[j], bin1[at + j]);
-        }
-    }
+// The cheapest split of a node of `count` primitives from its bins: lane l has
+// bin l % 32 of x (lanes 0-31) or y in w0, of z in w1 (7 words each).  Without
+// a split of finite cost, the index median: axis 0, bk -1.
+__device__ inline void sah_choose(const SahFrame f, const int (&w0)[7], const int (&w1)[7],
+                                  uint32_t count, int &axis, int &bk, uint32_t &nl) {
     const bool v0 = f.ok(0), v1 = f.ok(1), v2 = f.ok(2);
     float best = INFINITY;
-    int axis = -1, bk = -1;
-    uint32_t nl = 0;
+    axis = bk = -1;
+    nl = 0;
     // the costs are compared in axis order with a strict <: a lower axis wins a tie
     if (v0 || v1) {
         float cx, cy;
@@ -2696,8 +2674,43 @@ __device__ inline void sah_split_node(SahLevel lv, SahTree tr, uint32_t *root_na
     if (axis < 0) {
         axis = 0;
         bk = -1;
-        nl = tk.count / 2;
+        nl = count / 2;
     }
+}
+
+// The sweep and record of node t (one wave); leaves its task, id and split
+// (but for the slots) in tk and sp, the same in every lane.
+__device__ inline void sah_split_node(SahLevel lv, SahTree tr, uint32_t *root_nat, bool root_level,
+                                      uint32_t t, int lane, SahTask &tk, SahSplit &sp) {
+    tk = lv.task[t];
+    const uint32_t nch = (tk.count + kSahChunk - 1) / kSahChunk, c0 = lv.tc0[t];
+    const uint32_t ng = nch < 2 ? 1u : merge_groups(nch, lv.groups);
+    // one chunk: its chunk's bins; several in one group: the merged bins;
+    // several groups: the groups' partial bins, combined here
+    const int *gb = nch < 2 ? lv.cbins + (size_t)c0 * kSahBinWords
+                            : (ng > 1 ? lv.gbins + (size_t)t * kMergeGroups * kSahBinWords
+                                      : lv.bins + (size_t)t * kSahBinWords);
+    const SahFrame f = sah_task_frame(lv.cb + 6 * t);
+    // x's bins in lanes 0-31 and y's in lanes 32-63, then z's in lanes 0-31
+    const int *bin0 = gb + lane * 7, *bin1 = gb + (2 * kSahBins + (lane & (kSahBins - 1))) * 7;
+    int w0[7], w1[7];
+#pragma unroll
+    for (int j = 0; j < 7; j++) {
+        w0[j] = bin0[j];
+        w1[j] = bin1[j];
+    }
+#pragma unroll 4
+    for (uint32_t g = 1; g < ng; g++) {
+        const size_t at = (size_t)g * kSahBinWords;
+#pragma unroll
+        for (int j = 0; j < 7; j++) {
+            w0[j] = bin_combine((uint32_t)j, w0[j], bin0[at + j]);
+            w1[j] = bin_combine((uint32_t)j, w1[j], bin1[at + j]);
+        }
+    }
+    int axis, bk;
+    uint32_t nl;
+    sah_choose(f, w0, w1, tk.count, axis, bk, nl);
     const uint32_t m = tk.first + nl;
     if (root_level && lane == 0) *root_nat = m - 1;
     const uint32_t rn = root_level ? m - 1 : *root_nat;
@@ -2735,10 +2748,11 @@ __global__ __launch_bounds__(kSplitThreads) void k_sah_split(SahLevel lv, SahTre
                                                              uint32_t *next_cstart,
                                                              uint32_t *next_tc0, int *next_cb,
                                                              uint32_t *counters, SahTask *small,
-                                                             uint32_t *small_count) {
+                                                             uint32_t *small_count, SahTask *mid,
+                                                             uint32_t *mid_count) {
     constexpr int kSplitWaves = kSplitThreads / kWave;
-    __shared__ uint32_t need[3][kSplitWaves];  // per wave: small tasks, next tasks, next chunks
-    __shared__ uint32_t base[3];
+    __shared__ uint32_t need[4][kSplitWaves];  // per wave: small, next tasks, next chunks, middle
+    __shared__ uint32_t base[4];
     const int wv = threadIdx.x / kWave;
     const uint32_t t = blockIdx.x * kSplitWaves + wv;
     const bool live = t < lv.ntask;
@@ -2749,12 +2763,14 @@ __global__ __launch_bounds__(kSplitThreads) void k_sah_split(SahLevel lv, SahTre
     const uint32_t nl = sp.nl;
     // the node's children that need queue slots
     const uint32_t cf[2] = {tk.first, tk.first + nl}, cc[2] = {nl, tk.count - nl};
-    uint32_t ns = 0, nn = 0, nc = 0;
+    uint32_t ns = 0, nn = 0, nc = 0, nm = 0;
     if (live) {
         for (int sd = 0; sd < 2; sd++) {
             if (cc[sd] < 2) continue;
             if (cc[sd] <= kSahSmall) {
                 ns++;
+            } else if (cc[sd] <= kSahMid) {
+                nm++;
             } else {
                 nn++;
                 nc += (cc[sd] + kSahChunk - 1) / kSahChunk;
@@ -2765,27 +2781,32 @@ __global__ __launch_bounds__(kSplitThreads) void k_sah_split(SahLevel lv, SahTre
         need[0][wv] = ns;
         need[1][wv] = nn;
         need[2][wv] = nc;
+        need[3][wv] = nm;
     }
     __syncthreads();
-    if (threadIdx.x < 3) {
+    if (threadIdx.x < 4) {
         uint32_t tot = 0;
         for (int w = 0; w < kSplitWaves; w++) tot += need[threadIdx.x][w];
-        uint32_t *ctr = threadIdx.x == 0 ? small_count : &counters[threadIdx.x - 1];
+        uint32_t *ctr = threadIdx.x == 0 ? small_count
+                                         : (threadIdx.x == 3 ? mid_count : &counters[threadIdx.x - 1]);
         base[threadIdx.x] = tot ? atomicAdd(ctr, tot) : 0u;
     }
     __syncthreads();
     if (!live || lane != 0) return;
-    uint32_t so = base[0], no = base[1], co = base[2];
+    uint32_t so = base[0], no = base[1], co = base[2], mo = base[3];
     for (int w = 0; w < wv; w++) {
         so += need[0][w];
         no += need[1][w];
         co += need[2][w];
+        mo += need[3][w];
     }
     for (int sd = 0; sd < 2; sd++) {
         if (cc[sd] < 2) continue;
         const SahTask ch{cf[sd], cc[sd], (int32_t)sp.id, (uint32_t)sd};
         if (cc[sd] <= kSahSmall) {
             small[so++] = ch;
+        } else if (cc[sd] <= kSahMid) {
+            mid[mo++] = ch;
         } else {
             const uint32_t slot = no++;
             sp.slot[sd] = slot;
@@ -2813,7 +2834,7 @@ __global__ __launch_bounds__(kBlock) void k_sah_scatter(SahLevel lv, const uint3
                                                         const Box *pbox, uint32_t *ord_next,
                                                         uint32_t *perm, int *next_cb,
                                                         const uint32_t *counters,
-                                                        const uint32_t *small_count, uint32_t *host,
+                                                        const uint32_t *mid_count, uint32_t *host,
                                                         uint32_t *err) {
     constexpr int W = kBlock / kWave;
     __shared__ float red[6][W];
@@ -2821,7 +2842,7 @@ __global__ __launch_bounds__(kBlock) void k_sah_scatter(SahLevel lv, const uint3
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         host[0] = counters[0];
         host[1] = counters[1];
-        host[2] = *small_count;
+        host[2] = *mid_count;
         __threadfence_system();  // the host polls the words
     }
     const uint32_t t = lv.chunk[blockIdx.x];
@@ -2890,11 +2911,164 @@ __global__ __launch_bounds__(kBlock) void k_sah_scatter(SahLevel lv, const uint3
         }
         ord_next[dst] = prim[r];
         const uint32_t child = left ? sp.nl : tk.count - sp.nl;
-        if (child <= kSahSmall) perm[dst] = prim[r];
+        if (child <= kSahMid) perm[dst] = prim[r];
     }
     // the same in the block
     if (sp.slot[0] != kNoSlot) sah_fold_bounds(v[0], red, next_cb + 6 * (size_t)sp.slot[0]);
     if (sp.slot[1] != kNoSlot) sah_fold_bounds(v[1], red, next_cb + 6 * (size_t)sp.slot[1]);
+}
+
+// Splits tasks of kSahSmall to kSahMid primitives down to small ones: one
+// workgroup per task, with its boxes and order in LDS, a wave per node, level
+// by level.  The levels of many such nodes cost four launches and a round
+// trip to the host each, some 30 us, of which little is work.  Builds of 1,000,
+// 5,000, 200,000, 300,000 and 2,000,000 triangles: 376, 532, 768, 1,037, 3,117 ->
+// 286, 475, 686, 997, 2,992 us (512 and 1,024 primitives measured the same).
+constexpr int kMidThreads = 512;
+constexpr int kMidWaves = kMidThreads / kWave;
+constexpr uint32_t kMidNodes = kSahMid / (kSahSmall + 1) + 1;  // nodes of a level at most
+
+__global__ __launch_bounds__(kMidThreads) void k_sah_mid(const SahTask *mid, const Box *pbox,
+                                                         uint32_t *perm, SahTree tr,
+                                                         uint32_t *root_nat_p, SahTask *small,
+                                                         uint32_t *small_count, uint32_t *err) {
+    __shared__ float s_box[6][kSahMid];
+    __shared__ uint32_t s_prim[kSahMid];
+    __shared__ uint16_t s_ord[2][kSahMid];  // by level parity: positions in the arrays above
+    __shared__ int s_bin[kMidWaves][kSahBinWords];
+    __shared__ SahTask s_node[2][kMidNodes];  // ranges within the task
+    __shared__ SahTask s_small[kSahMid / 2];
+    __shared__ uint32_t s_n[2], s_nsmall, s_root, s_base;
+    const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const SahTask tk = mid[blockIdx.x];
+    for (uint32_t i = threadIdx.x; i < tk.count; i += kMidThreads) {
+        const uint32_t prim = perm[tk.first + i];
+        const Box b = pbox[prim];
+        s_prim[i] = prim;
+        s_ord[0][i] = (uint16_t)i;
+        s_box[0][i] = b.lo.x;
+        s_box[1][i] = b.lo.y;
+        s_box[2][i] = b.lo.z;
+        s_box[3][i] = b.hi.x;
+        s_box[4][i] = b.hi.y;
+        s_box[5][i] = b.hi.z;
+    }
+    if (threadIdx.x == 0) {
+        s_node[0][0] = SahTask{0u, tk.count, tk.parent, tk.side};
+        s_n[0] = 1;
+        s_n[1] = 0;
+        s_nsmall = 0;
+        s_root = tk.parent < 0 ? 0u : *root_nat_p;
+    }
+    __syncthreads();
+    int *const bins = s_bin[w];
+    for (int cur = 0; s_n[cur] > 0; cur ^= 1) {  // the same in every thread
+        for (uint32_t k = w; k < s_n[cur]; k += kMidWaves) {
+            const SahTask nd = s_node[cur][k];
+            const uint16_t *const ord = s_ord[cur] + nd.first;
+            const auto centre = [&](uint32_t p, int a) { return 0.5f * s_box[a][p] + 0.5f * s_box[3 + a][p]; };
+            float cl[3], ch[3];
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                cl[a] = INFINITY;
+                ch[a] = -INFINITY;
+            }
+            for (uint32_t i = lane; i < nd.count; i += kWave) {
+                const uint32_t p = ord[i];
+#pragma unroll
+                for (int a = 0; a < 3; a++) {
+                    const float c = centre(p, a);
+                    cl[a] = fminf(cl[a], c);
+                    ch[a] = fmaxf(ch[a], c);
+                }
+            }
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                cl[a] = wave_min(cl[a]);
+                ch[a] = wave_max(ch[a]);
+            }
+            const SahFrame f = sah_frame(cl, ch);
+            for (uint32_t i = lane; i < kSahBinWords; i += kWave) {
+                const uint32_t kind = i % 7;
+                bins[i] = kind == 0 ? 0 : f2o(kind <= 3 ? INFINITY : -INFINITY);
+            }
+            wave_sync();
+            for (uint32_t i = lane; i < nd.count; i += kWave) {
+                const uint32_t p = ord[i];
+                int q[6];
+#pragma unroll
+                for (int j = 0; j < 6; j++) q[j] = f2o(s_box[j][p]);
+#pragma unroll
+                for (int a = 0; a < 3; a++) {
+                    if (!f.ok(a)) continue;
+                    int *bin = bins + (a * kSahBins + sah_bin(f, a, centre(p, a))) * 7;
+                    atomicAdd(bin, 1);
+#pragma unroll
+                    for (int j = 0; j < 3; j++) {
+                        atomicMin(bin + 1 + j, q[j]);
+                        atomicMax(bin + 4 + j, q[3 + j]);
+                    }
+                }
+            }
+            wave_sync();
+            int w0[7], w1[7];
+#pragma unroll
+            for (int j = 0; j < 7; j++) {
+                w0[j] = bins[lane * 7 + j];
+                w1[j] = bins[(2 * kSahBins + (lane & (kSahBins - 1))) * 7 + j];
+            }
+            wave_sync();
+            int axis, bk;
+            uint32_t nl;
+            sah_choose(f, w0, w1, nd.count, axis, bk, nl);
+            const uint32_t m = tk.first + nd.first + nl;
+            const bool is_root = nd.parent < 0;
+            const uint32_t id = sah_node_id(m, is_root, is_root ? m - 1 : s_root);
+            // stable partition; small children are final in this kernel
+            const uint32_t cc[2] = {nl, nd.count - nl};
+            uint32_t lrun = 0;
+            for (uint32_t i0 = 0; i0 < nd.count; i0 += kWave) {
+                const uint32_t i = i0 + lane;
+                const bool in = i < nd.count;
+                const uint32_t p = in ? ord[i] : 0u;
+                const float c = axis == 0 ? centre(p, 0) : (axis == 1 ? centre(p, 1) : centre(p, 2));
+                const bool left = in && (bk < 0 ? i < nl : sah_bin(f, axis, c) <= bk);
+                const uint64_t lmask = __builtin_amdgcn_ballot_w64(left);
+                const uint32_t rank = lrun + (uint32_t)__builtin_popcountll(lmask & below);
+                lrun += (uint32_t)__builtin_popcountll(lmask);
+                const uint32_t dst = left ? rank : nl + (i - rank);
+                if (in && (dst >= nd.count || (left && rank >= nl))) {
+                    atomicOr(err, 1u);  // the primitives disagree with the split's count
+                } else if (in) {
+                    s_ord[cur ^ 1][nd.first + dst] = (uint16_t)p;
+                    if ((left ? cc[0] : cc[1]) <= kSahSmall) perm[tk.first + nd.first + dst] = s_prim[p];
+                }
+            }
+            if (lane == 0) {
+                if (is_root) {  // the only node of the first level
+                    s_root = m - 1;
+                    *root_nat_p = m - 1;
+                }
+                sah_write_node(tr, id, tk.first + nd.first, nd.count, axis, nl, nd.parent, nd.side);
+#pragma unroll
+                for (int sd = 0; sd < 2; sd++) {
+                    const uint32_t cf = sd == 0 ? nd.first : nd.first + nl;
+                    if (cc[sd] < 2) continue;
+                    if (cc[sd] <= kSahSmall)
+                        s_small[atomicAdd(&s_nsmall, 1u)] = SahTask{tk.first + cf, cc[sd], (int32_t)id, (uint32_t)sd};
+                    else
+                        s_node[cur ^ 1][atomicAdd(&s_n[cur ^ 1], 1u)] = SahTask{cf, cc[sd], (int32_t)id, (uint32_t)sd};
+                }
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) s_n[cur] = 0;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) s_base = s_nsmall ? atomicAdd(small_count, s_nsmall) : 0u;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < s_nsmall; i += kMidThreads) small[s_base + i] = s_small[i];
 }
 
 // Finishes tasks of at most kSahSmall primitives, one wave each, with the
@@ -2907,159 +3081,161 @@ __global__ __launch_bounds__(kBlock) void k_sah_scatter(SahLevel lv, const uint3
 // largest node has primitives.  One node after another, each with its 32 bins
 // in LDS and their prefix and suffix scans, took 290 us for 300,000 triangles;
 // the levels take 200.
-__global__ __launch_bounds__(kBlock) void k_sah_small(const SahTask *small, uint32_t nsmall,
+__global__ __launch_bounds__(kBlock) void k_sah_small(const SahTask *small, const uint32_t *small_count,
+                                                      uint32_t small_cap,
                                                       const Box *pbox, uint32_t *perm, SahTree tr,
                                                       const uint32_t *root_nat_p, uint32_t leaf_size) {
     constexpr int W = kBlock / kWave;
     __shared__ float4 s_a[W][kSahSmall], s_b[W][kSahSmall];
     __shared__ unsigned long long s_key[W][kSahSmall];
     const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    const uint32_t t = blockIdx.x * W + w;
-    if (t >= nsmall) return;
-    const SahTask tk = small[t];
-    const bool root_task = tk.parent < 0;
-    uint32_t root_nat = root_task ? 0u : *root_nat_p;
-    float4 *const va = s_a[w], *const vb = s_b[w];
-    unsigned long long *const keys = s_key[w];
-    uint32_t prim = 0;
-    float4 lo = make_float4(0.0f, 0.0f, 0.0f, 0.0f), hi = lo;
-    if ((uint32_t)lane < tk.count) {
-        prim = perm[tk.first + lane];
-        const Box b = pbox[prim];
-        lo = b.lo;
-        hi = b.hi;
-    }
-    // the lane's node: its lanes, parent and side
-    uint32_t sf = 0, sc = (uint32_t)lane < tk.count ? tk.count : 0u, sd = tk.side;
-    int32_t par = tk.parent;
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    while (__builtin_amdgcn_ballot_w64(sc >= 2) != 0) {
-        const bool act = sc >= 2;
-        // a node of at most leaf_size primitives becomes one leaf whatever its
-        // subtree: it is split at the index median without binning (no
-        // reordering), so only the order inside the leaf differs from a full
-        // SAH split
-        const bool binned = act && sc > leaf_size;
-        const uint32_t steps = wave_reduce<uint32_t>(binned ? sc : 0u, 0u,
-                                                     [](uint32_t x, uint32_t y) { return max(x, y); });
-        int axis = -1, bk = -1;
-        uint32_t bins = 0;
-        if (steps > 0) {
-            float c[3], cl[3], ch[3];
-            c[0] = 0.5f * lo.x + 0.5f * hi.x;  // as sah_centroid
-            c[1] = 0.5f * lo.y + 0.5f * hi.y;
-            c[2] = 0.5f * lo.z + 0.5f * hi.z;
-            va[lane] = make_float4(c[0], c[1], c[2], 0.0f);
-            keys[lane] = ~0ull;
-            wave_sync();
-#pragma unroll
-            for (int a = 0; a < 3; a++) {
-                cl[a] = INFINITY;
-                ch[a] = -INFINITY;
-            }
-            const uint32_t mine = binned ? sc : 0u;
-            for (uint32_t j = 0; j < steps; j++) {
-                if (j >= mine) continue;
-                const float4 q = va[sf + j];
-                cl[0] = fminf(cl[0], q.x);
-                cl[1] = fminf(cl[1], q.y);
-                cl[2] = fminf(cl[2], q.z);
-                ch[0] = fmaxf(ch[0], q.x);
-                ch[1] = fmaxf(ch[1], q.y);
-                ch[2] = fmaxf(ch[2], q.z);
-            }
-            const SahFrame f = sah_frame(cl, ch);
-#pragma unroll
-            for (int a = 0; a < 3; a++)
-                if (f.ok(a)) bins |= (uint32_t)sah_bin(f, a, c[a]) << (8 * a);
-            wave_sync();
-            va[lane] = make_float4(lo.x, lo.y, lo.z, __uint_as_float(bins));
-            vb[lane] = hi;
-            wave_sync();
-            // per axis: the union of the boxes up to the lane's bin and beyond it
-            float l[3][6], r[3][6];
-            uint32_t nleft[3] = {0, 0, 0};
-#pragma unroll
-            for (int a = 0; a < 3; a++)
-#pragma unroll
-                for (int k = 0; k < 6; k++) l[a][k] = r[a][k] = k < 3 ? INFINITY : -INFINITY;
-            for (uint32_t j = 0; j < steps; j++) {
-                if (j >= mine) continue;
-                const float4 p = va[sf + j], q = vb[sf + j];
-                const uint32_t pb = __float_as_uint(p.w);
-                const float v[6] = {p.x, p.y, p.z, q.x, q.y, q.z};
+    const uint32_t nsmall = min(*small_count, small_cap);
+    for (uint32_t t = blockIdx.x * W + w; t < nsmall; t += gridDim.x * W) {
+        const SahTask tk = small[t];
+        const bool root_task = tk.parent < 0;
+        uint32_t root_nat = root_task ? 0u : *root_nat_p;
+        float4 *const va = s_a[w], *const vb = s_b[w];
+        unsigned long long *const keys = s_key[w];
+        uint32_t prim = 0;
+        float4 lo = make_float4(0.0f, 0.0f, 0.0f, 0.0f), hi = lo;
+        if ((uint32_t)lane < tk.count) {
+            prim = perm[tk.first + lane];
+            const Box b = pbox[prim];
+            lo = b.lo;
+            hi = b.hi;
+        }
+        // the lane's node: its lanes, parent and side
+        uint32_t sf = 0, sc = (uint32_t)lane < tk.count ? tk.count : 0u, sd = tk.side;
+        int32_t par = tk.parent;
+        const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+        while (__builtin_amdgcn_ballot_w64(sc >= 2) != 0) {
+            const bool act = sc >= 2;
+            // a node of at most leaf_size primitives becomes one leaf whatever its
+            // subtree: it is split at the index median without binning (no
+            // reordering), so only the order inside the leaf differs from a full
+            // SAH split
+            const bool binned = act && sc > leaf_size;
+            const uint32_t steps = wave_reduce<uint32_t>(binned ? sc : 0u, 0u,
+                                                         [](uint32_t x, uint32_t y) { return max(x, y); });
+            int axis = -1, bk = -1;
+            uint32_t bins = 0;
+            if (steps > 0) {
+                float c[3], cl[3], ch[3];
+                c[0] = 0.5f * lo.x + 0.5f * hi.x;  // as sah_centroid
+                c[1] = 0.5f * lo.y + 0.5f * hi.y;
+                c[2] = 0.5f * lo.z + 0.5f * hi.z;
+                va[lane] = make_float4(c[0], c[1], c[2], 0.0f);
+                keys[lane] = ~0ull;
+                wave_sync();
 #pragma unroll
                 for (int a = 0; a < 3; a++) {
-                    if (((pb >> (8 * a)) & 0xFFu) <= ((bins >> (8 * a)) & 0xFFu)) {
-                        nleft[a]++;
+                    cl[a] = INFINITY;
+                    ch[a] = -INFINITY;
+                }
+                const uint32_t mine = binned ? sc : 0u;
+                for (uint32_t j = 0; j < steps; j++) {
+                    if (j >= mine) continue;
+                    const float4 q = va[sf + j];
+                    cl[0] = fminf(cl[0], q.x);
+                    cl[1] = fminf(cl[1], q.y);
+                    cl[2] = fminf(cl[2], q.z);
+                    ch[0] = fmaxf(ch[0], q.x);
+                    ch[1] = fmaxf(ch[1], q.y);
+                    ch[2] = fmaxf(ch[2], q.z);
+                }
+                const SahFrame f = sah_frame(cl, ch);
 #pragma unroll
-                        for (int k = 0; k < 6; k++) l[a][k] = k < 3 ? fminf(l[a][k], v[k]) : fmaxf(l[a][k], v[k]);
-                    } else {
+                for (int a = 0; a < 3; a++)
+                    if (f.ok(a)) bins |= (uint32_t)sah_bin(f, a, c[a]) << (8 * a);
+                wave_sync();
+                va[lane] = make_float4(lo.x, lo.y, lo.z, __uint_as_float(bins));
+                vb[lane] = hi;
+                wave_sync();
+                // per axis: the union of the boxes up to the lane's bin and beyond it
+                float l[3][6], r[3][6];
+                uint32_t nleft[3] = {0, 0, 0};
 #pragma unroll
-                        for (int k = 0; k < 6; k++) r[a][k] = k < 3 ? fminf(r[a][k], v[k]) : fmaxf(r[a][k], v[k]);
+                for (int a = 0; a < 3; a++)
+#pragma unroll
+                    for (int k = 0; k < 6; k++) l[a][k] = r[a][k] = k < 3 ? INFINITY : -INFINITY;
+                for (uint32_t j = 0; j < steps; j++) {
+                    if (j >= mine) continue;
+                    const float4 p = va[sf + j], q = vb[sf + j];
+                    const uint32_t pb = __float_as_uint(p.w);
+                    const float v[6] = {p.x, p.y, p.z, q.x, q.y, q.z};
+#pragma unroll
+                    for (int a = 0; a < 3; a++) {
+                        if (((pb >> (8 * a)) & 0xFFu) <= ((bins >> (8 * a)) & 0xFFu)) {
+                            nleft[a]++;
+#pragma unroll
+                            for (int k = 0; k < 6; k++) l[a][k] = k < 3 ? fminf(l[a][k], v[k]) : fmaxf(l[a][k], v[k]);
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 6; k++) r[a][k] = k < 3 ? fminf(r[a][k], v[k]) : fmaxf(r[a][k], v[k]);
+                        }
+                    }
+                }
+                // the node's cheapest split: lowest cost, then axis, then bin
+                // (costs are not negative: their bits are in their order)
+                unsigned long long key = ~0ull;
+#pragma unroll
+                for (int a = 0; a < 3; a++) {
+                    if (!f.ok(a) || nleft[a] == mine) continue;
+                    const float cost =
+                        half_area3(l[a][0], l[a][1], l[a][2], l[a][3], l[a][4], l[a][5]) * (float)nleft[a] +
+                        half_area3(r[a][0], r[a][1], r[a][2], r[a][3], r[a][4], r[a][5]) * (float)(mine - nleft[a]);
+                    if (!(cost < INFINITY)) continue;
+                    const unsigned long long k = (unsigned long long)__float_as_uint(cost) << 32 |
+                                                 (unsigned)(a << 8) | ((bins >> (8 * a)) & 0xFFu);
+                    key = k < key ? k : key;
+                }
+                if (binned && key != ~0ull) atomicMin(&keys[sf], key);
+                wave_sync();
+                if (binned) {
+                    key = keys[sf];
+                    if (key != ~0ull) {
+                        axis = (int)((key >> 8) & 3u);
+                        bk = (int)(key & 0xFFu);
                     }
                 }
             }
-            // the node's cheapest split: lowest cost, then axis, then bin
-            // (costs are not negative: their bits are in their order)
-            unsigned long long key = ~0ull;
-#pragma unroll
-            for (int a = 0; a < 3; a++) {
-                if (!f.ok(a) || nleft[a] == mine) continue;
-                const float cost =
-                    half_area3(l[a][0], l[a][1], l[a][2], l[a][3], l[a][4], l[a][5]) * (float)nleft[a] +
-                    half_area3(r[a][0], r[a][1], r[a][2], r[a][3], r[a][4], r[a][5]) * (float)(mine - nleft[a]);
-                if (!(cost < INFINITY)) continue;
-                const unsigned long long k = (unsigned long long)__float_as_uint(cost) << 32 |
-                                             (unsigned)(a << 8) | ((bins >> (8 * a)) & 0xFFu);
-                key = k < key ? k : key;
+            const uint32_t pos = (uint32_t)lane - sf;
+            const bool left = axis < 0 ? pos < sc / 2 : (int)((bins >> (8 * axis)) & 0xFFu) <= bk;
+            const uint64_t seg = act ? (sc == 64u ? ~0ull : ((1ull << sc) - 1ull) << sf) : 0ull;
+            const uint64_t lmask = __builtin_amdgcn_ballot_w64(act && left) & seg;
+            const uint32_t nl = (uint32_t)__builtin_popcountll(lmask);
+            const uint32_t m = tk.first + sf + nl;
+            const bool is_root = root_task && par < 0;
+            if (is_root) root_nat = m - 1;
+            const uint32_t id = sah_node_id(m, is_root, root_nat);
+            if (act && pos == 0)
+                sah_write_node(tr, id, tk.first + sf, sc, axis < 0 ? 0 : axis, nl, par, sd);
+            // stable partition
+            if (steps > 0) {
+                const uint32_t lrank = (uint32_t)__builtin_popcountll(lmask & below);
+                const uint32_t dst = !act ? (uint32_t)lane : (left ? sf + lrank : sf + nl + (pos - lrank));
+                va[dst] = make_float4(lo.x, lo.y, lo.z, __uint_as_float(prim));
+                vb[dst] = hi;
+                wave_sync();
+                lo = va[lane];
+                hi = vb[lane];
+                prim = __float_as_uint(lo.w);
+                wave_sync();
             }
-            if (binned && key != ~0ull) atomicMin(&keys[sf], key);
-            wave_sync();
-            if (binned) {
-                key = keys[sf];
-                if (key != ~0ull) {
-                    axis = (int)((key >> 8) & 3u);
-                    bk = (int)(key & 0xFFu);
-                }
+            if (act) {
+                par = (int32_t)id;
+                sd = pos < nl ? 0u : 1u;
+                sf = pos < nl ? sf : sf + nl;
+                sc = pos < nl ? nl : sc - nl;
             }
         }
-        const uint32_t pos = (uint32_t)lane - sf;
-        const bool left = axis < 0 ? pos < sc / 2 : (int)((bins >> (8 * axis)) & 0xFFu) <= bk;
-        const uint64_t seg = act ? (sc == 64u ? ~0ull : ((1ull << sc) - 1ull) << sf) : 0ull;
-        const uint64_t lmask = __builtin_amdgcn_ballot_w64(act && left) & seg;
-        const uint32_t nl = (uint32_t)__builtin_popcountll(lmask);
-        const uint32_t m = tk.first + sf + nl;
-        const bool is_root = root_task && par < 0;
-        if (is_root) root_nat = m - 1;
-        const uint32_t id = sah_node_id(m, is_root, root_nat);
-        if (act && pos == 0)
-            sah_write_node(tr, id, tk.first + sf, sc, axis < 0 ? 0 : axis, nl, par, sd);
-        // stable partition
-        if (steps > 0) {
-            const uint32_t lrank = (uint32_t)__builtin_popcountll(lmask & below);
-            const uint32_t dst = !act ? (uint32_t)lane : (left ? sf + lrank : sf + nl + (pos - lrank));
-            va[dst] = make_float4(lo.x, lo.y, lo.z, __uint_as_float(prim));
-            vb[dst] = hi;
-            wave_sync();
-            lo = va[lane];
-            hi = vb[lane];
-            prim = __float_as_uint(lo.w);
-            wave_sync();
-        }
-        if (act) {
-            par = (int32_t)id;
-            sd = pos < nl ? 0u : 1u;
-            sf = pos < nl ? sf : sf + nl;
-            sc = pos < nl ? nl : sc - nl;
-        }
+        if ((uint32_t)lane < tk.count) perm[tk.first + lane] = prim;
     }
-    if ((uint32_t)lane < tk.count) perm[tk.first + lane] = prim;
 }
 
 __global__ void k_sah_init(uint32_t *ord, uint32_t *perm, uint32_t n, SahTask *task,
                            uint32_t *chunk, uint32_t *cstart, uint32_t *tc0, int *cb,
-                           SahTask *small, uint32_t *nsmall) {
+                           SahTask *small, uint32_t *nsmall, SahTask *mid, uint32_t *nmid) {
     const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i < n) {
         ord[i] = i;
@@ -3067,17 +3243,20 @@ __global__ void k_sah_init(uint32_t *ord, uint32_t *perm, uint32_t n, SahTask *t
     }
     if (i == 0) {
         const SahTask root{0u, n, -1, 0u};
-        if (n > kSahSmall) {
+        if (n > kSahMid) {
             task[0] = root;
             tc0[0] = 0;
             sah_clear_bounds(cb);
+        } else if (n > kSahSmall) {
+            mid[0] = root;
+            *nmid = 1;
         } else {
             small[0] = root;
             *nsmall = 1;
         }
     }
     const uint32_t nch = (n + kSahChunk - 1) / kSahChunk;
-    if (n > kSahSmall && i < nch) {
+    if (n > kSahMid && i < nch) {
         chunk[i] = 0;
         cstart[i] = i * kSahChunk;
     }
@@ -3097,11 +3276,12 @@ int32_t sah_topology(const Box *pbox, uint32_t n, uint32_t *perm, SahTree tr, in
         if (n == 1) BVH_HIP_TRY(hipMemsetAsync(perm, 0, sizeof(uint32_t), s));
         return BVH_OK;
     }
-    const uint32_t cap_task = n / (kSahSmall + 1) + 1;
+    const uint32_t cap_task = n / (kSahMid + 1) + 1, cap_mid = n / (kSahSmall + 1) + 1;
+    const uint32_t cap_small = n / 2 + 1;
     const uint32_t cap_chunk = (n + kSahChunk - 1) / kSahChunk + cap_task;
     uint32_t *ord[2], *ccnt, *cleft, *chunk[2], *cstart[2], *tc0[2], *counters, *small_count,
         *root_nat;
-    SahTask *task[2], *small;
+    SahTask *task[2], *small, *mid;
     SahSplit *split;
     int *cb[2], *bins, *cbins, *gbins;
     Arena ar;
@@ -3123,22 +3303,23 @@ int32_t sah_topology(const Box *pbox, uint32_t n, uint32_t *perm, SahTree tr, in
     ar.request(&gbins, (size_t)kMergeGroupTasks * kMergeGroups * kSahBinWords);
     ar.request(&tc0[0], cap_task);
     ar.request(&tc0[1], cap_task);
-    ar.request(&small, n / 2 + 1);
+    ar.request(&small, cap_small);
+    ar.request(&mid, cap_mid);
     ar.request(&counters, 2 * kSahMaxLevels + 4);
     BVH_TRY(ar.bind(s, kAreaSah));
     small_count = counters + 2 * kSahMaxLevels;
     root_nat = small_count + 1;
-    uint32_t *err = small_count + 2;
+    uint32_t *err = small_count + 2, *mid_count = small_count + 3;
     BVH_HIP_TRY(hipMemsetAsync(counters, 0, (2 * kSahMaxLevels + 4) * sizeof(uint32_t), s));
     k_sah_init<<<grid_for(n), kBlock, 0, s>>>(ord[0], perm, n, task[0], chunk[0], cstart[0], tc0[0],
-                                              cb[0], small, small_count);
+                                              cb[0], small, small_count, mid, mid_count);
     BVH_TRY(check_launch("sah init"));
     uint32_t *hw = host_words();
     if (!hw) return set_error(BVH_ENOMEM, "hipHostMalloc failed");
     volatile uint32_t *vw = hw + 8;
-    uint32_t ntask = n > kSahSmall ? 1u : 0u;
+    uint32_t ntask = n > kSahMid ? 1u : 0u;
     uint32_t nchunk = (n + kSahChunk - 1) / kSahChunk;
-    uint32_t nsmall = ntask > 0 ? 0u : 1u;
+    uint32_t nmid = n > kSahSmall && n <= kSahMid ? 1u : 0u;
     int cur = 0;
     if (ntask > 0) k_sah_bounds<<<nchunk, kBlock, 0, s>>>(n, pbox, cb[0]);
     for (int level = 0; ntask > 0; level++) {
@@ -3156,22 +3337,26 @@ int32_t sah_topology(const Box *pbox, uint32_t n, uint32_t *perm, SahTree tr, in
         (few ? k_sah_split<kSplitFewThreads> : k_sah_split<kSplitManyThreads>)<<<
             grid_for((uint64_t)ntask * kWave, threads), threads, 0, s>>>(
             lv, tr, root_nat, level == 0, task[cur ^ 1], chunk[cur ^ 1], cstart[cur ^ 1],
-            tc0[cur ^ 1], cb[cur ^ 1], counters + 2 * level, small, small_count);
+            tc0[cur ^ 1], cb[cur ^ 1], counters + 2 * level, small, small_count,
+            mid, mid_count);
         vw[0] = vw[1] = vw[2] = kPending;
         k_sah_scatter<<<nchunk, kBlock, 0, s>>>(lv, ord[cur], pbox, ord[cur ^ 1], perm, cb[cur ^ 1],
-                                                counters + 2 * level, small_count, hw + 8, err);
+                                                counters + 2 * level, mid_count, hw + 8, err);
         BVH_TRY(check_launch("sah level"));
         BVH_TRY(wait_host_word(vw, s, &ntask));
         BVH_TRY(wait_host_word(vw + 1, s, &nchunk));
-        BVH_TRY(wait_host_word(vw + 2, s, &nsmall));
+        BVH_TRY(wait_host_word(vw + 2, s, &nmid));
         if (ntask > cap_task || nchunk > cap_chunk)
             return set_error(BVH_EHIP, "bvh_build: internal error (SAH task overflow)");
         cur ^= 1;
     }
-    if (nsmall > n / 2 + 1) return set_error(BVH_EHIP, "bvh_build: internal error (SAH small overflow)");
-    if (nsmall > 0)
-        k_sah_small<<<(nsmall + kBlock / kWave - 1) / (kBlock / kWave), kBlock, 0, s>>>(
-            small, nsmall, pbox, perm, tr, root_nat, (uint32_t)leaf_size);
+    if (nmid > cap_mid) return set_error(BVH_EHIP, "bvh_build: internal error (SAH middle overflow)");
+    if (nmid > 0)
+        k_sah_mid<<<nmid, kMidThreads, 0, s>>>(mid, pbox, perm, tr, root_nat, small, small_count, err);
+    // the device knows how many small tasks there are
+    constexpr unsigned kSmallBlocks = 4096;
+    k_sah_small<<<std::min(grid_for((uint64_t)cap_small * kWave), kSmallBlocks), kBlock, 0, s>>>(
+        small, small_count, cap_small, pbox, perm, tr, root_nat, (uint32_t)leaf_size);
     vw[3] = kPending;
     k_sah_publish<<<1, 64, 0, s>>>(err, hw + 11, 1);
     BVH_TRY(check_launch("sah small nodes"));

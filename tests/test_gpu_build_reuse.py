@@ -3,8 +3,8 @@ levels change shape.
 
 Released blocks go to the next builds, whatever their thread and stream, so every build must give
 the bytes that it gives in fresh memory, and what stays allocated must be bounded.  The SAH levels
-work in chunks of 2,048 primitives with 64 chunks to a scan step: the trees just above and below
-those sizes must be the oracle's.
+work in chunks of 2,048 primitives with 64 chunks to a scan step, and nodes of 1,024 leave them: the
+trees just above and below those sizes must be the oracle's.
 """
 import threading
 
@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 KEPT = 512 << 20  # what the library may keep of released memory
 
 
-@pytest.mark.parametrize("n", [2047, 2048, 2049, 2048 * 64 + 1, 2048 * 65 + 3])
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 2047, 2048, 2049, 2048 * 64 + 1, 2048 * 65 + 3])
 def test_sah_chunk_edges(orc, n):
     v, t = W.soup_scene(n, seed=n)
     check_tree(orc, v, t, 4)
