@@ -144,7 +144,7 @@ def trimmed_mean(times):
 
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "trace_kernel_counters.txt")
 TRAVERSAL_SOURCES = [os.path.join(ROOT, "paper_2511_15028_amd", "csrc", f)
-                     for f in ("traverse.h", "trace.hip")]
+                     for f in ("traverse.h", "coop.h", "trace.hip")]
 
 
 def traversal_source_digest():
