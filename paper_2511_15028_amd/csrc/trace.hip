@@ -14,8 +14,9 @@ namespace {
 // wave are idle (a wave claims 64 consecutive rays per atomic), so the
 // wave's lanes stay busy on long rays instead of idling until the slowest
 // ray of a fixed group ends.  A wave whose rays were coherent waits until
-// half its lanes are idle and then takes as many consecutive rays, which keeps
-// neighbouring camera rays together (they end at nearly the same time).
+// half its lanes are idle (all of them in a long launch) and then takes as many
+// consecutive rays, which keeps neighbouring camera rays together (they end at
+// nearly the same time).
 // The first three quarters of the rays are dealt to the waves round-robin in
 // 64-ray chunks (no atomics); the rest is claimed from a queue, which
 // balances the tail.  Each lane's stack is a ring in LDS over a spill
@@ -23,9 +24,12 @@ namespace {
 // both go to the fallback pass.  Every wave leaves the loop once the queue is
 // drained and its lanes are idle, so the grid always drains.
 constexpr uint32_t kRefillLanes = 16;  // idle lanes of a wave that trigger a refill
-// A coherent wave waits for half its lanes: 1 M camera rays in BVH8-Q8 take 197
-// us, 210 when it waits for all of them.
+// A coherent wave of a short launch waits for half its lanes, of a long one for
+// all of them: its rays stay neighbours longer, which shows once the end of the
+// launch counts less.  Terrain camera rays in BVH4, half / all: 1 M 205 / 216
+// us, 1.5 M 274 / 276, 2.1 M 347 / 312 (AABB2 747 / 660).
 constexpr uint32_t kCoherentRefillLanes = 32;
+constexpr uint64_t kLongRounds = 4;  // dealt rounds of a short launch at most
 
 template <int Layout, int LeafMode, int Mode, bool Count, int SL>
 __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes, int64_t n_nodes,
@@ -63,7 +67,8 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
     for (;;) {
         const uint64_t idle = __builtin_amdgcn_ballot_w64(ray == kNoRay);
         const uint32_t nidle = (uint32_t)__builtin_popcountll(idle);
-        const uint32_t need = coherent ? kCoherentRefillLanes : kRefillLanes;
+        const uint32_t need =
+            !coherent ? kRefillLanes : (static_rounds > kLongRounds ? 64u : kCoherentRefillLanes);
         if (nidle >= need && !(drained && pool == pool_end)) {
             const uint32_t avail = (uint32_t)(pool_end - pool);
             uint64_t fresh = 0, fresh_end = 0;  // a newly claimed range
