@@ -46,7 +46,7 @@ constexpr float kFastLimit = 1.152921504606846976e18f;  // 2^60
 
 // o * rdir moved outward by at least one ulp: the returned pair (lo, hi)
 // brackets the exact product.
-__device__ inline void bracket_product(float o, float rd, float &lo, float &hi) {
+__host__ __device__ inline void bracket_product(float o, float rd, float &lo, float &hi) {
     const float c = o * rd;
     const float delta = fabsf(c) * 2.384185791015625e-07f + 2.350988701644575e-38f;  // 2^-22, 2^-125
     lo = c - delta;
@@ -54,7 +54,7 @@ __device__ inline void bracket_product(float o, float rd, float &lo, float &hi) 
 }
 
 // coord_max: largest coordinate magnitude of the scene (or +inf).
-__device__ inline Ray load_ray(const bvh_ray *rays, uint64_t i, float coord_max) {
+__host__ __device__ inline Ray load_ray(const bvh_ray *rays, uint64_t i, float coord_max) {
     const float4 *p = reinterpret_cast<const float4 *>(rays + i);
     const float4 a = p[0], b = p[1];
     Ray r;
@@ -64,9 +64,9 @@ __device__ inline Ray load_ray(const bvh_ray *rays, uint64_t i, float coord_max)
     r.rx = 1.0f / r.dx;
     r.ry = 1.0f / r.dy;
     r.rz = 1.0f / r.dz;
-    r.nx = signbit(r.dx);
-    r.ny = signbit(r.dy);
-    r.nz = signbit(r.dz);
+    r.nx = __builtin_signbitf(r.dx);
+    r.ny = __builtin_signbitf(r.dy);
+    r.nz = __builtin_signbitf(r.dz);
     float lo, hi;
     bracket_product(r.ox, r.rx, lo, hi);
     r.knx = -hi; r.kfx = -lo;
@@ -80,6 +80,14 @@ __device__ inline Ray load_ray(const bvh_ray *rays, uint64_t i, float coord_max)
     r.fast = rmax <= kFastLimit && rmin >= 1.0f / kFastLimit && omax <= kFastLimit &&
              coord_max <= kFastLimit;  // false for NaN as well
     return r;
+}
+
+// False for a ray with a NaN or infinite origin or direction component: the
+// ray/triangle test accepts nothing for it (det, or one of U, V and T, is not
+// finite), while its NaN slab distances cull no box.
+__host__ __device__ inline bool ray_finite(const Ray &r) {
+    const float z = r.ox * 0.0f + r.oy * 0.0f + r.oz * 0.0f + r.dx * 0.0f + r.dy * 0.0f + r.dz * 0.0f;
+    return z == 0.0f;
 }
 
 // True when every active lane's ray can use the one-FMA slab distances (a
@@ -114,7 +122,7 @@ __device__ inline bool rays_share_octant(const Ray &r, bool has, uint64_t mask) 
 // error of each distance against the exact (plane - o) / d stays below the
 // far-distance widening, so no box that the ray meets before the best hit is culled.
 template <bool Fast>
-__device__ inline float slab_nf(const Ray &r, float nx, float ny, float nz, float fx, float fy,
+__host__ __device__ inline float slab_nf(const Ray &r, float nx, float ny, float nz, float fx, float fy,
                                 float fz, float cull) {
     float tnx, tny, tnz, tfx, tfy, tfz;
     if (Fast) {
@@ -801,6 +809,7 @@ __device__ inline void bin_test_parked(const SceneData &ld, const Ray &r, BinSta
 // uniform rays on the spheres scene 11.1 -> 9.4 ms).
 // ---------------------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__host__ __device__ inline float as_f32(uint32_t x) { return __builtin_bit_cast(float, x); }
 struct NoPrep {};
 
 // BVH4: the near and far plane arrays of an axis are picked by address (the
@@ -816,7 +825,7 @@ struct DecodeBVH4 {
     struct Prep {
         uint32_t nx, ny, nz;  // byte offsets of the entry-plane arrays in a node
     };
-    __device__ static Prep prep(const Ray &r) {
+    __host__ __device__ static Prep prep(const Ray &r) {
         Prep p;
         p.nx = r.nx ? 48u : 0u;
         p.ny = r.ny ? 64u : 16u;
@@ -827,7 +836,7 @@ struct DecodeBVH4 {
     // offsets of the two plane arrays of an axis (0 and 48, 16 and 64, 32 and
     // 80) turn into each other by one exclusive or, also in 128-byte aligned
     // nodes' addresses.
-    __device__ static void fetch(const void *nodes, uint32_t node, const Prep &p, u32x4 *m) {
+    __host__ __device__ static void fetch(const void *nodes, uint32_t node, const Prep &p, u32x4 *m) {
         const char *b = static_cast<const char *>(nodes);
         const uint32_t o = node << 7, x = o + p.nx, y = o + p.ny, z = o + p.nz;
         m[0] = *reinterpret_cast<const u32x4 *>(b + x);
@@ -839,22 +848,25 @@ struct DecodeBVH4 {
         m[6] = *reinterpret_cast<const u32x4 *>(b + (size_t)o + 96);
     }
     template <bool Fast>
-    __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn, uint32_t *ref) {
+    __host__ __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn,
+                                         uint32_t *ref) {
 #pragma unroll
         for (int c = 0; c < 4; c++) {
-            tn[c] = slab_nf<Fast>(r, __uint_as_float(m[0][c]), __uint_as_float(m[1][c]),
-                                  __uint_as_float(m[2][c]), __uint_as_float(m[3][c]),
-                                  __uint_as_float(m[4][c]), __uint_as_float(m[5][c]), cull);
+            tn[c] = slab_nf<Fast>(r, as_f32(m[0][c]), as_f32(m[1][c]), as_f32(m[2][c]),
+                                  as_f32(m[3][c]), as_f32(m[4][c]), as_f32(m[5][c]), cull);
             ref[c] = m[6][c];
+            // an empty slot's infinite planes cull it, unless every distance is NaN
+            // (not with Fast, whose 1/d is finite and not zero)
+            if (!Fast && ref[c] == kRefEmpty) tn[c] = INFINITY;
         }
     }
 };
 
 // Byte c of the 8 packed bytes held in words (w0, w1).
-__device__ inline uint32_t byte_of(uint32_t w0, uint32_t w1, int c) {
+__host__ __device__ inline uint32_t byte_of(uint32_t w0, uint32_t w1, int c) {
     return ((c < 4 ? w0 : w1) >> (8 * (c & 3))) & 0xFFu;
 }
-__device__ inline uint32_t half_of(const uint32_t *w, int c) {
+__host__ __device__ inline uint32_t half_of(const uint32_t *w, int c) {
     return (w[c >> 1] >> (16 * (c & 1))) & 0xFFFFu;
 }
 
@@ -868,8 +880,8 @@ struct DecodeBVH8 {
     // 0.620 / 0.632 / 0.665 ms at 16 / 32 / 40 / 48 / 56)
     static constexpr uint32_t kStall = 40;
     using Prep = NoPrep;
-    __device__ static Prep prep(const Ray &) { return Prep{}; }
-    __device__ static void fetch(const void *nodes, uint32_t node, const Prep &, u32x4 *m) {
+    __host__ __device__ static Prep prep(const Ray &) { return Prep{}; }
+    __host__ __device__ static void fetch(const void *nodes, uint32_t node, const Prep &, u32x4 *m) {
         const char *b = static_cast<const char *>(nodes) + (size_t)(node * (uint32_t)NodeBytes);
 #pragma unroll
         for (int k = 0; k < Words; k++) m[k] = reinterpret_cast<const u32x4 *>(b)[k];
@@ -878,12 +890,13 @@ struct DecodeBVH8 {
 
 struct DecodeBVH8Q8 : DecodeBVH8<sizeof(bvh_node_bvh8_q8), 7> {
     template <bool Fast>
-    __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn, uint32_t *ref) {
+    __host__ __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn,
+                                         uint32_t *ref) {
         uint32_t w[28];
 #pragma unroll
         for (int k = 0; k < 28; k++) w[k] = m[k / 4][k % 4];
-        const float ox = __uint_as_float(w[0]), oy = __uint_as_float(w[1]), oz = __uint_as_float(w[2]);
-        const float sx = __uint_as_float(w[3]), sy = __uint_as_float(w[4]), sz = __uint_as_float(w[5]);
+        const float ox = as_f32(w[0]), oy = as_f32(w[1]), oz = as_f32(w[2]);
+        const float sx = as_f32(w[3]), sy = as_f32(w[4]), sz = as_f32(w[5]);
         // words: lo_x 6-7, lo_y 8-9, lo_z 10-11, hi_x 12-13, hi_y 14-15, hi_z 16-17
         uint32_t n[6], f[6];
 #pragma unroll
@@ -912,12 +925,13 @@ struct DecodeBVH8Q8 : DecodeBVH8<sizeof(bvh_node_bvh8_q8), 7> {
 
 struct DecodeBVH8Q16 : DecodeBVH8<sizeof(bvh_node_bvh8_q16), 10> {
     template <bool Fast>
-    __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn, uint32_t *ref) {
+    __host__ __device__ static void test(const u32x4 *m, const Ray &r, float cull, float *tn,
+                                         uint32_t *ref) {
         uint32_t w[40];
 #pragma unroll
         for (int k = 0; k < 40; k++) w[k] = m[k / 4][k % 4];
-        const float ox = __uint_as_float(w[0]), oy = __uint_as_float(w[1]), oz = __uint_as_float(w[2]);
-        const float sx = __uint_as_float(w[3]), sy = __uint_as_float(w[4]), sz = __uint_as_float(w[5]);
+        const float ox = as_f32(w[0]), oy = as_f32(w[1]), oz = as_f32(w[2]);
+        const float sx = as_f32(w[3]), sy = as_f32(w[4]), sz = as_f32(w[5]);
         // words: lo_x 6-9, lo_y 10-13, lo_z 14-17, hi_x 18-21, hi_y 22-25, hi_z 26-29
         uint32_t n[12], f[12];
 #pragma unroll
@@ -1020,7 +1034,7 @@ __device__ inline WideState wide_start(int64_t n_nodes, const Ray &r) {
     WideState ws;
     ws.best = Best{INFINITY, 0.0f, 0.0f, 0xFFFFFFFFu};
     ws.cull = fminf(r.tmax, INFINITY) * kFarScale;  // a NaN tmax culls no box (and accepts no hit)
-    ws.cur = entry_of(0.0f, n_nodes > 0 ? ref_interior(0) : kRefDone);
+    ws.cur = entry_of(0.0f, n_nodes > 0 && ray_finite(r) ? ref_interior(0) : kRefDone);
     ws.leaf = kRefDone;
     return ws;
 }
