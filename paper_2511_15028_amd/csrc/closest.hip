@@ -649,7 +649,7 @@ struct FinishQueries {
         return false;
     }
     __device__ void store(uint32_t item, const Best &best) const { store_closest(out, item, best); }
-    __device__ void list(uint32_t item) const { fallback_append(fb, item); }
+    __device__ bool list(uint32_t item) const { return fallback_append(fb, item); }
 };
 
 // Persistent kernel: lanes take query after query.  A wave hands new queries

@@ -83,7 +83,8 @@ __device__ inline float group_min(float x, uint32_t lg) {
 //                              nearest first, or its leaf's triangles
 //   leaves(want, first, cnt, best, wl)         tests the lanes' leaves; true
 //                              in a lane that needs no more (every lane calls it)
-//   store(item, best), list(item)              result, or to the fallback pass
+//   store(item, best)          the result
+//   list(item)                 to the fallback pass; false where none follows
 //
 // Called by every lane of the wave (converged); lanes whose item is not
 // kNoRay hold one under way, at least one and at most kCoopItems of them.
@@ -187,8 +188,9 @@ __device__ inline void coop_finish(F &f, typename F::Entry *stack, uint32_t item
     }
     const uint64_t winners = __builtin_amdgcn_ballot_w64(key == least) & group;
     if (live && lane == (uint32_t)__builtin_ctzll(winners)) {
-        if (over) f.list(item);
-        else f.store(item, best);
+        // a launch without a fallback pass has the reserve that rules `over` out
+        // (wholly_coop); were it reached all the same, the best so far is stored
+        if (!over || !f.list(item)) f.store(item, best);
     }
 }
 
@@ -231,7 +233,7 @@ struct FinishRays {
         return wave_test_leaves<LeafMode, Mode>(ld, r, want, first, cnt, best, ntri, wl);
     }
     __device__ void store(uint32_t item, const Best &best) const { store_hit(hits, item, best); }
-    __device__ void list(uint32_t item) const { fallback_append(fb, item); }
+    __device__ bool list(uint32_t item) const { return fallback_append(fb, item); }
 };
 
 }  // namespace bvhlib

@@ -295,13 +295,11 @@ int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_ray 
     // grid, whose coherent waves end together and leave the last chunks to run by
     // themselves; scattered rays lose less (1 M uniform ones 264 against 210).
     const unsigned grid = (unsigned)(fixed ? need : std::min<uint64_t>(resident, need));
-    TraceArea ta;
-    if (fixed) {
-        ta = TraceArea{*fixed, SpillArea{nullptr, grid * kTraceBlock, 0}};
-        if (!alone) clear_header(ta.fb, s);
-    } else if (alone) {
-        ta = TraceArea{Fallback{}, SpillArea{nullptr, grid * kTraceBlock, 0}};
-    } else {
+    TraceArea ta{Fallback{}, SpillArea{nullptr, grid * kTraceBlock, 0}};
+    if (fixed && !alone) {
+        ta.fb = *fixed;
+        clear_header(ta.fb, s);
+    } else if (!alone) {
         BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
     }
     kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, rays, n, hits, counts, deal,

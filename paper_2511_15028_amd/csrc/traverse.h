@@ -1430,9 +1430,12 @@ __device__ inline bool claim_dynamic(const Fallback &fb, uint64_t static_end, ui
     return false;
 }
 
-__device__ inline void fallback_append(const Fallback &fb, uint32_t ray) {
-    const uint32_t k = atomicAdd(fb.count, 1u);
+// Leaves a ray to the fallback pass; false where the launch has none (no list).
+__host__ __device__ inline bool fallback_append(const Fallback &fb, uint32_t ray) {
+    if (!fb.count) return false;
+    const uint32_t k = __hip_atomic_fetch_add(fb.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     fb.list[k] = ray;
+    return true;
 }
 
 // ---------------------------------------------------------------------------
