@@ -39,6 +39,27 @@ def _scratch_kernels(remarks: str) -> list:
     return out
 
 
+# Persistent kernels hold four waves per SIMD, what their LDS allows (512
+# registers a lane of a SIMD), and wait for memory: one wave fewer costs up to
+# a quarter.
+MAX_VGPRS = 128
+PERSISTENT = ("k_trace_persist", "k_batch_trace", "k_cpq_persist")
+
+
+def _large_kernels(remarks: str) -> list:
+    """Persistent kernels whose report shows more registers than that:
+    (name, registers)."""
+    out, name = [], None
+    for line in remarks.splitlines():
+        m = re.search(r"Function Name: (\S+)", line)
+        if m:
+            name = m.group(1)
+        m = re.search(r"\bVGPRs: (\d+)", line)
+        if m and int(m.group(1)) > MAX_VGPRS and any(k in (name or "") for k in PERSISTENT):
+            out.append((name, int(m.group(1))))
+    return out
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
     cmd = [HIPCC, *CXXFLAGS, "-Rpass-analysis=kernel-resource-usage", "-c",
@@ -51,6 +72,9 @@ def _compile(src: str) -> str:
     bad = _scratch_kernels(r.stderr)
     if bad:
         raise RuntimeError(f"{src}: kernels using scratch memory: {bad}")
+    large = _large_kernels(r.stderr)
+    if large:
+        raise RuntimeError(f"{src}: persistent kernels of more than {MAX_VGPRS} registers: {large}")
     return obj
 
 
