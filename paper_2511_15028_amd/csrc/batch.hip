@@ -542,7 +542,8 @@ int32_t make_graph(bvh_batch_s *b, const bvh_ray *rays, const int64_t *offsets, 
         uint32_t *ctr = counters + g;
         const bvh_ray *r = rays;
         bvh_hit *hh = hits;
-        Deal deal = deal_of(group_rays, resident * waves_per_block, kv.first.second, kRayReserve);
+        Deal deal = deal_of(group_rays, resident * waves_per_block, kv.first.second, kRayReserve,
+                            resident * waves_per_block);
         // fallback work area of this group (list sized for all its rays),
         // then the per-lane stack spill area of its grid
         const uint32_t lanes = grid * kTraceBlock;

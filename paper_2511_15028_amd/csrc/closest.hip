@@ -916,7 +916,7 @@ int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_poin
     BVH_TRY(resident_blocks(kernel, resident));
     // as in the ray kernel: few queries are spread over all resident waves
     const uint64_t waves = (uint64_t)resident * (kTraceBlock / 64);
-    const Deal deal = deal_of(n, waves, kCpqStack, depth_first_reserve(h->max_stack));
+    const Deal deal = deal_of(n, waves, kCpqStack, depth_first_reserve(h->max_stack), waves);
     const bool alone = !Count && wholly_coop(deal, n, waves, h->max_stack);
     const uint64_t need = ((n + deal.claim - 1) / deal.claim + kTraceBlock / 64 - 1) / (kTraceBlock / 64);
     const unsigned grid = (unsigned)std::min<uint64_t>(resident, need);

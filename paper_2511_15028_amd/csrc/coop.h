@@ -38,20 +38,26 @@ constexpr uint32_t kCoopItems = 16;
 // max_stack, with room for one more node's children.
 constexpr uint32_t depth_first_reserve(int32_t max_stack) { return (uint32_t)max_stack + 8u; }
 
-// Rays that a wave takes at least, once they are more than it finishes in
-// groups from the start.  The 8-wide layouts do better with fewer, fuller waves
-// than with all the resident ones (100,003 rays on the terrains, 25 / 32 a wave,
-// BVH8-Q16: camera 65 / 62 us, uniform 81 / 76); the binary ones with more
-// (uniform rays 5 % slower at 32) and BVH4 the same.
-constexpr uint32_t least_claim(int children) { return children == 8 ? 32u : 1u; }
+// The waves among which rays are spread that are more than the waves finish in
+// groups from the start: three of four for BVH8-Q16, whose 160-byte nodes fill
+// the vector L1 with the lines of three waves per SIMD (70,000 to 160,000 rays in
+// three / four: terrain camera rays 100 / 108, shadow rays 100 / 104, uniform rays
+// 100 / 102 on average), all of them otherwise (BVH8-Q8 at 160,000: camera rays
+// 10 % faster in three, shadow rays 7 % and uniform ones 3 % slower).
+constexpr uint64_t spread_waves(int layout, uint64_t waves) {
+    return layout == BVH_LAYOUT_BVH8_Q16 ? waves * 3 / 4 : waves;
+}
 
 // n rays or queries on a grid of `waves` resident waves, with a ring of sl
 // entries per lane: a group of 64 / items lanes has sl * 64 / items entries,
-// at least 48 of them beside its reserve.
-inline Deal deal_of(uint64_t n, uint64_t waves, int sl, uint32_t reserve, uint32_t least = 1) {
+// at least 48 of them beside its reserve.  spread: spread_waves().
+inline Deal deal_of(uint64_t n, uint64_t waves, int sl, uint32_t reserve, uint64_t spread) {
     Deal d;
-    d.claim = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, (n + waves - 1) / waves));
-    if (d.claim > kCoopItems) d.claim = std::max(d.claim, least);
+    const auto share = [n](uint64_t w) {
+        return (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, (n + w - 1) / w));
+    };
+    d.claim = share(waves);
+    if (d.claim > kCoopItems) d.claim = share(spread);
     d.reserve = reserve;
     d.items = kCoopItems;
     while (d.items > 0 && 64u * (uint32_t)sl / d.items < reserve + 48u) d.items >>= 1;

@@ -64,7 +64,6 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
     uint32_t queue = wave % kQueues;  // the wave's current dynamic queue (wave-uniform)
     bool coherent = true;  // the wave's rays at its last refill all pointed into one octant
     bool fast = true;      // and can all use the one-FMA slab distances
-    bool tail = false;     // the wave's last rays are left to its groups of lanes
     for (;;) {
         const uint64_t idle = __builtin_amdgcn_ballot_w64(ray == kNoRay);
         const uint32_t nidle = (uint32_t)__builtin_popcountll(idle);
@@ -126,7 +125,6 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
         if (!Count && drained && pool == pool_end &&
             __builtin_popcountll(__builtin_amdgcn_ballot_w64(ray != kNoRay)) <= deal.items &&
             __builtin_amdgcn_ballot_w64(ray != kNoRay && (!st.in_ring() || Tr::parked(ts))) == 0) {
-            tail = true;
             break;
         }
         Tr::template wave<LeafMode, Mode>(nodes, n_nodes, ld, r, prep, fast, coherent, st, ts, wl,
@@ -146,11 +144,12 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_persist(const void *nodes
             }
         }
     }
-    // Outside the loop: within it, the loop's registers stayed allocated through
-    // the tail, and several kernels held 3 waves per SIMD instead of 4 (BVH8-Q16
-    // 137 registers, now 105: 4 M rays on 4 M triangles of spheres 12.1 -> 10.2
-    // ms; indexed BVH4 129, now 92; indexed AABB2 111, now 80).
-    if (tail) {
+    // The wave's last rays, if it has any left.  Outside the loop: within it, the
+    // loop's registers stayed allocated through the tail, and several kernels held
+    // 3 waves per SIMD instead of 4 (BVH8-Q16 137 registers, now 105: 4 M rays on
+    // 4 M triangles of spheres 12.1 -> 10.2 ms; indexed BVH4 129, now 92; indexed
+    // AABB2 111, now 80).
+    if (!Count && __builtin_amdgcn_ballot_w64(ray != kNoRay) != 0) {
         if (ray != kNoRay && !Tr::done(ts)) st.put(Tr::next(ts), true);
         Finish f{nodes, n_nodes, ld, rays, hits, fb};
         coop_finish<Finish, SL>(f, s_stack, ray, st.entries(), ts.best, deal.reserve, wl);
@@ -291,10 +290,10 @@ int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_ray 
     // few to each, so that the waves finish them together (coop.h)
     const uint64_t waves = (uint64_t)resident * (kTraceBlock / 64);
     // a few rays per wave have room for the safe reserve
-    constexpr uint32_t least = least_claim(TracerFor<Layout>::type::kChildren);
-    Deal deal = deal_of(n, waves, SL, depth_first_reserve(h->max_stack), least);
+    const uint64_t spread = spread_waves(Layout, waves);
+    Deal deal = deal_of(n, waves, SL, depth_first_reserve(h->max_stack), spread);
     const bool alone = !Count && wholly_coop(deal, n, waves, h->max_stack);
-    if (!alone) deal = deal_of(n, waves, SL, kRayReserve, least);
+    if (!alone) deal = deal_of(n, waves, SL, kRayReserve, spread);
     const uint64_t need = ((n + deal.claim - 1) / deal.claim + kTraceBlock / 64 - 1) / (kTraceBlock / 64);
     // Without a spill area (fixed) nothing ties a launch to the resident blocks:
     // every wave gets one chunk, and the dispatcher starts a block whenever

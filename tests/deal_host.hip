@@ -42,9 +42,10 @@ int main() {
         for (int sl : {8, 16, 32})
             for (int max_stack : {0, 1, 7, 21, 40, 63, 100, 200, 256}) {
                 int least = 1 << 30, launches = 0;
+                const uint64_t spread = spread_waves(K == 8 ? BVH_LAYOUT_BVH8_Q16 : BVH_LAYOUT_BVH4, waves);
                 for (uint32_t per = 1; per <= 17; per++) {
                     const uint64_t n = waves * per;
-                    const Deal d = deal_of(n, waves, sl, depth_first_reserve(max_stack));
+                    const Deal d = deal_of(n, waves, sl, depth_first_reserve(max_stack), spread);
                     if (!wholly_coop(d, n, waves, max_stack)) continue;
                     launches++;
                     for (uint32_t items = 1; items <= d.claim; items++) {
