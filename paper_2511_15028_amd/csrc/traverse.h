@@ -725,6 +725,22 @@ __device__ inline void split_meta(const void *nodes, uint32_t i, const SceneData
         Node::load_meta(i, sd, cnt, off, axis);
 }
 
+// Whether a round's interior phase ends, with lanes `prog` that can go on and
+// `parked` that have a leaf to test.  A coherent wave leaves at most
+// kCoherentStall lanes behind that have no leaf yet.  Camera rays on a terrain
+// of 382,000 triangles, 1 M without allocation, at 0 / 4 / 8 / 16: 10-bit binary
+// nodes 450 / 398 / 383 / 382 us, AABB2 330 / 305 / 296 / 297, BVH8-Q8 185 / 178 /
+// 177 / 177.  BVH4 waits for every lane: 157 / 155 / 155 / 157, but 2 M in a
+// persistent launch 290 / 295 / 298 / 304.
+template <uint32_t kCoherentStall, uint32_t kStall>
+__device__ inline bool phase_over(bool coherent, uint64_t prog, uint64_t parked) {
+    if (coherent) {
+        const uint32_t late = (uint32_t)__builtin_popcountll(prog & ~parked);
+        return late == 0 || (kCoherentStall > 0 && late <= kCoherentStall && parked != 0);
+    }
+    return prog == 0 || ((uint32_t)__builtin_popcountll(prog) <= kStall && parked != 0);
+}
+
 // Visits bs.node: an interior node whose box the ray meets continues with the
 // near child (split axis and ray direction sign) and stacks the far one; a
 // leaf whose box it meets is parked (or held, if one is parked already).
@@ -822,6 +838,7 @@ struct DecodeBVH4 {
     // lanes (terrain bounce rays: 0.616 / 0.600 / 0.577 / 0.559 / 0.563 /
     // 0.585 / 0.646 ms at 8 / 16 / 24 / 32 / 40 / 48 / 56)
     static constexpr uint32_t kStall = 32;
+    static constexpr uint32_t kCoherentStall = 0;  // see phase_over
     struct Prep {
         uint32_t nx, ny, nz;  // byte offsets of the entry-plane arrays in a node
     };
@@ -879,6 +896,7 @@ struct DecodeBVH8 {
     // as DecodeBVH4::kStall (terrain bounce rays, BVH8-Q8: 0.705 / 0.653 /
     // 0.620 / 0.632 / 0.665 ms at 16 / 32 / 40 / 48 / 56)
     static constexpr uint32_t kStall = 40;
+    static constexpr uint32_t kCoherentStall = 8;
     using Prep = NoPrep;
     __host__ __device__ static Prep prep(const Ray &) { return Prep{}; }
     __host__ __device__ static void fetch(const void *nodes, uint32_t node, const Prep &, u32x4 *m) {
@@ -1148,9 +1166,9 @@ __device__ inline void wide_expand(const void *nodes, uint32_t last, const Ray &
 // triangles together instead of splitting every step between the two:
 //   interior phase: lanes visit interior nodes, park the first leaf they
 //     meet and keep descending; a lane whose next entry is a second leaf
-//     waits.  With coherent rays the phase ends when every lane has a parked
-//     leaf or is done; with scattered rays once at most kStall lanes can
-//     still make progress (waiting for the last stragglers of such a wave
+//     waits.  With coherent rays the phase ends when all lanes but a few have
+//     a parked leaf or are done; with scattered rays once at most kStall lanes
+//     can still make progress (waiting for the last stragglers of such a wave
 //     would idle the rest);
 //   leaf phase: the parked leaves are tested, each in its lane where the
 //     rays are coherent (their lanes hold leaves at the same time), else in
@@ -1166,9 +1184,7 @@ __device__ inline void wide_round(const void *nodes, uint32_t last, const SceneD
         wide_advance<Dec, Mode>(nodes, last, r, prep, fast, st, ws, nfetch, incomplete);
         const uint64_t prog = __builtin_amdgcn_ballot_w64(ws.interior());
         const uint64_t parked = __builtin_amdgcn_ballot_w64(ws.leaf != kRefDone);
-        if (coherent ? (prog & ~parked) == 0
-                     : (prog == 0 || ((uint32_t)__builtin_popcountll(prog) <= Dec::kStall && parked != 0)))
-            break;
+        if (phase_over<Dec::kCoherentStall, Dec::kStall>(coherent, prog, parked)) break;
     }
     if (coherent) {
         if (ws.leaf != kRefDone) wide_test_parked<LeafMode, Mode>(ld, r, st, ws, ntri);
@@ -1243,6 +1259,7 @@ struct BinTracer {
     // node per step and testing leaves in their lanes; 1.24 / 1.10 / 1.07 ms
     // with this round at 16 / 32 / 48)
     static constexpr uint32_t kStall = 40;
+    static constexpr uint32_t kCoherentStall = 8;
     __device__ static Prep prep(const Ray &) { return Prep{}; }
     __device__ static State start(int64_t n_nodes, const Ray &r) { return bin_start(n_nodes, r); }
     __device__ static State none() { return bin_start(0, Ray{}); }
@@ -1288,9 +1305,7 @@ struct BinTracer {
             if (s.progress()) bin_visit<Node>(nodes, n_nodes, ld, r, fast, st, s, nfetch, incomplete);
             const uint64_t prog = __builtin_amdgcn_ballot_w64(s.progress());
             const uint64_t parked = __builtin_amdgcn_ballot_w64(s.leaf != kRefEmpty);
-            if (coherent ? (prog & ~parked) == 0
-                         : (prog == 0 || ((uint32_t)__builtin_popcountll(prog) <= kStall && parked != 0)))
-                break;
+            if (phase_over<kCoherentStall, kStall>(coherent, prog, parked)) break;
         }
         const bool want = s.leaf != kRefEmpty;
         if (coherent) {
