@@ -617,7 +617,8 @@ __device__ inline void store_closest(bvh_closest *out, uint64_t i, const CpqBest
 constexpr uint32_t kNoQuery = kNoRay;
 // LDS stack entries per lane, whatever the handle's: 2^20 queries on the terrain
 // (BVH4) take 5.71 ms with 16, 6.74 with 8 (spills), and 32 would halve the
-// resident waves.
+// resident waves.  BVH8-Q8 with 8 entries: unbounded queries 9 % slower, radius
+// 0.02 30 %.
 constexpr int kCpqStack = 16;
 constexpr uint32_t kCpqRefill = 16;  // idle lanes of a wave that trigger a refill
 
@@ -655,8 +656,16 @@ struct FinishQueries {
 // Persistent kernel: lanes take query after query.  A wave hands new queries
 // to its idle lanes once kCpqRefill of them are idle, from its pool of
 // claimed queries; the first three quarters of the queries are dealt to the
-// waves round-robin in 64-query chunks, the rest is claimed from a queue.
+// waves round-robin in 64-query chunks, the rest is claimed from a queue: in
+// short launches as many queries as there are idle lanes, in long ones 64.
 // Every wave leaves once the queue is drained and its lanes are idle.
+// Dealt rounds of a long launch at least.  In a short one the queue holds a round
+// or two, and its last chunks of 64 would be left to a few waves: 300,007 queries
+// on the spheres (BVH4) 900 -> 733 us, 600,000 (BVH8-Q8) 1,734 -> 1,503.  In a long one
+// it holds a quarter of the work, of which that is little, and the more claims
+// cost more: 1 M queries of radius 0.02 on the terrain (BVH4) 298 us against 285.
+constexpr uint64_t kFineRounds = 3;
+
 template <int Layout, int LeafMode, bool Count>
 __global__ __launch_bounds__(kTraceBlock) void k_cpq_persist(const void *nodes, int64_t n_nodes,
                                                              SceneData ld,
@@ -688,6 +697,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_cpq_persist(const void *nodes, 
     const uint64_t static_end = one_round ? n : static_rounds * waves * deal.claim;
     uint64_t round = 0;
     uint32_t queue = wave % kQueues;  // the wave's current dynamic queue (wave-uniform)
+    const bool fine = static_rounds < kFineRounds;
     for (;;) {
         const uint64_t idle = __builtin_amdgcn_ballot_w64(qi == kNoQuery);
         const uint32_t nidle = (uint32_t)__builtin_popcountll(idle);
@@ -701,7 +711,8 @@ __global__ __launch_bounds__(kTraceBlock) void k_cpq_persist(const void *nodes, 
                     fresh = min(fresh, fresh_end);
                     round++;
                     drained = one_round;
-                } else if (!claim_dynamic(fb, static_end, n, deal.claim,
+                } else if (!claim_dynamic(fb, static_end, n,
+                                          fine ? nidle - avail : deal.claim,
                                           (uint32_t)__builtin_ctzll(idle), queue, fresh,
                                           fresh_end)) {
                     drained = true;
