@@ -38,12 +38,13 @@ constexpr uint32_t kCoopItems = 16;
 // max_stack, with room for one more node's children.
 constexpr uint32_t depth_first_reserve(int32_t max_stack) { return (uint32_t)max_stack + 8u; }
 
-// The waves among which rays are spread that are more than the waves finish in
-// groups from the start: three of four for BVH8-Q16, whose 160-byte nodes fill
-// the vector L1 with the lines of three waves per SIMD (70,000 to 160,000 rays in
-// three / four: terrain camera rays 100 / 108, shadow rays 100 / 104, uniform rays
-// 100 / 102 on average), all of them otherwise (BVH8-Q8 at 160,000: camera rays
-// 10 % faster in three, shadow rays 7 % and uniform ones 3 % slower).
+// The waves among which a launch's rays are spread: three of four for BVH8-Q16,
+// whose 160-byte nodes fill the vector L1 with the lines of three waves per SIMD
+// (three against four: terrain camera rays 14 % faster at 7,428 and 8 % at 70,000
+// to 160,000, uniform rays 8 % at 10,000), but not where fewer waves would have
+// more rays than they finish in groups from the start (65,536 uniform rays 22 %
+// slower).  BVH8-Q8 does not gain (160,000: camera rays 10 % faster in three,
+// shadow rays 7 % and uniform ones 3 % slower).
 constexpr uint64_t spread_waves(int layout, uint64_t waves) {
     return layout == BVH_LAYOUT_BVH8_Q16 ? waves * 3 / 4 : waves;
 }
@@ -53,14 +54,15 @@ constexpr uint64_t spread_waves(int layout, uint64_t waves) {
 // at least 48 of them beside its reserve.  spread: spread_waves().
 inline Deal deal_of(uint64_t n, uint64_t waves, int sl, uint32_t reserve, uint64_t spread) {
     Deal d;
-    const auto share = [n](uint64_t w) {
-        return (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, (n + w - 1) / w));
-    };
-    d.claim = share(waves);
-    if (d.claim > kCoopItems) d.claim = share(spread);
     d.reserve = reserve;
     d.items = kCoopItems;
     while (d.items > 0 && 64u * (uint32_t)sl / d.items < reserve + 48u) d.items >>= 1;
+    const auto share = [n](uint64_t w) {
+        return (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, (n + w - 1) / w));
+    };
+    const auto kind = [&](uint32_t claim) { return claim <= d.items ? 0 : (claim <= kCoopItems ? 1 : 2); };
+    d.claim = share(waves);
+    if (kind(share(spread)) == kind(d.claim)) d.claim = share(spread);
     return d;
 }
 
