@@ -461,7 +461,7 @@ int32_t create_impl(const bvh_scene_desc *scenes, int32_t n_scenes, const bvh_tu
 template <typename T>
 int32_t upload(bvh_batch_s *b, const std::vector<T> &v, T **out) {
     void *p = nullptr;
-    BVH_HIP_TRY(hipMalloc(&p, std::max<size_t>(v.size(), 1) * sizeof(T)));
+    BVH_HIP_TRY(device_malloc(b->device, std::max<size_t>(v.size(), 1) * sizeof(T), &p));
     b->g_mem.push_back(p);
     if (!v.empty()) BVH_HIP_TRY(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
     *out = static_cast<T *>(p);
@@ -548,13 +548,13 @@ int32_t make_graph(bvh_batch_s *b, const bvh_ray *rays, const int64_t *offsets, 
         // then the per-lane stack spill area of its grid
         const uint32_t lanes = grid * kTraceBlock;
         void *ws = nullptr;
-        BVH_HIP_TRY(hipMalloc(&ws, fallback_bytes(group_rays)));
+        BVH_HIP_TRY(device_malloc(b->device, fallback_bytes(group_rays), &ws));
         b->g_mem.push_back(ws);
         Fallback fb = fallback_view(ws, group_rays);
         fb.count = counters + ngroups + g;
         if (lanes > spill_lanes) {  // the shared spill area, sized for the largest grid
             spill_lanes = n_cu * 32u * 64u;  // every lane the GPU can hold
-            BVH_HIP_TRY(hipMalloc(&spill, (size_t)spill_lanes * kBatchSpillCap * 8));
+            BVH_HIP_TRY(device_malloc(b->device, (size_t)spill_lanes * kBatchSpillCap * 8, &spill));
             b->g_mem.push_back(spill);
         }
         SpillArea sa;

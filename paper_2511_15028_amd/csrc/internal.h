@@ -57,6 +57,9 @@ struct DeviceBlock {
     void *ptr = nullptr;
     size_t bytes = 0;
 };
+// hipMalloc on `device` (the current device), tried again without the pool's
+// idle blocks; every device allocation of the library is made by it.
+hipError_t device_malloc(int device, size_t bytes, void **out);
 hipError_t block_alloc(int device, size_t bytes, DeviceBlock *out);
 void block_release(int device, DeviceBlock *b);
 

@@ -62,6 +62,20 @@ void block_trim(int device) {
     }
 }
 
+hipError_t device_malloc(int device, size_t bytes, void **out) {
+    hipError_t e = hipMalloc(out, bytes);
+    if (e != hipSuccess) {  // the idle blocks may be what is missing
+        (void)hipGetLastError();
+        block_trim(device);
+        e = hipMalloc(out, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *out = nullptr;
+    }
+    return e;
+}
+
 // A block of at least `bytes` on `device` (the current device), idle.
 hipError_t block_alloc(int device, size_t bytes, DeviceBlock *out) {
     {
@@ -79,12 +93,7 @@ hipError_t block_alloc(int device, size_t bytes, DeviceBlock *out) {
         }
     }
     void *p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) {  // the idle blocks may be what is missing
-        (void)hipGetLastError();
-        block_trim(device);
-        e = hipMalloc(&p, bytes);
-    }
+    const hipError_t e = device_malloc(device, bytes, &p);
     *out = e == hipSuccess ? DeviceBlock{p, bytes} : DeviceBlock{};
     return e;
 }
@@ -133,17 +142,9 @@ int32_t stream_workspace(hipStream_t s, int purpose, size_t bytes, void **out) {
             a.bytes = 0;
         }
         const size_t grow = bytes + bytes / 4;  // headroom against repeated growth
-        hipError_t e = hipMalloc(&a.ptr, grow);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            block_trim(dev);
-            e = hipMalloc(&a.ptr, grow);
-        }
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            a.ptr = nullptr;
+        const hipError_t e = device_malloc(dev, grow, &a.ptr);
+        if (e != hipSuccess)
             return set_error(BVH_ENOMEM, "work area of %zu bytes: %s", grow, hipGetErrorString(e));
-        }
         a.bytes = grow;
     }
     *out = a.ptr;
