@@ -28,8 +28,9 @@ std::map<std::tuple<int, hipStream_t, int>, Area> g_areas;
 // 197 and 181 us.
 //
 // Bounded: kPoolBlocks blocks and kPoolBytes bytes per device, the longest idle
-// one freed first; a block that kPoolAge releases have passed by is freed too,
-// and so is every block before the library reports an allocation failure.
+// one freed first; a block that kPoolAge of its device's releases have passed by
+// is freed too, and so is every block before the library reports an allocation
+// failure.
 // Safe with any threads and streams: a block enters the pool only once its
 // device is idle (block_release's contract), so whoever takes it next, on any
 // stream, finds no work using it.
@@ -40,12 +41,12 @@ constexpr uint64_t kPoolAge = 64;
 struct IdleBlock {
     int device;
     DeviceBlock block;
-    uint64_t since;  // g_releases when it came in
+    uint64_t since;  // its device's releases when it came in
 };
 
 std::mutex g_pool_mutex;
-std::list<IdleBlock> g_idle;  // oldest first
-uint64_t g_releases = 0;
+std::list<IdleBlock> g_idle;             // oldest first
+std::map<int, uint64_t> g_releases;      // per device
 
 }  // namespace
 
@@ -103,11 +104,12 @@ hipError_t block_alloc(int device, size_t bytes, DeviceBlock *out) {
 void block_release(int device, DeviceBlock *b) {
     if (!b->ptr) return;
     std::lock_guard<std::mutex> lock(g_pool_mutex);
-    g_releases++;
     const DeviceBlock given = *b;
     *b = DeviceBlock{};
+    uint64_t now = 0;
     try {
-        g_idle.push_back(IdleBlock{device, given, g_releases});
+        now = ++g_releases[device];
+        g_idle.push_back(IdleBlock{device, given, now});
     } catch (...) {  // no host memory to remember it with
         (void)hipFree(given.ptr);
         return;
@@ -118,7 +120,7 @@ void block_release(int device, DeviceBlock *b) {
         if (it->device != device) continue;
         blocks++;
         bytes += it->block.bytes;
-        if (blocks > kPoolBlocks || bytes > kPoolBytes || g_releases - it->since > kPoolAge) {
+        if (blocks > kPoolBlocks || bytes > kPoolBytes || now - it->since > kPoolAge) {
             bytes -= it->block.bytes;
             blocks--;
             (void)hipFree(it->block.ptr);

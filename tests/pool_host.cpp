@@ -62,5 +62,26 @@ int main() {
     std::printf("malloc %d used %zu\n", (int)got, g_used[0] / MB);
     const hipError_t not_got = device_malloc(0, 200 * MB, &p);
     std::printf("refused %d null %d last %d\n", (int)not_got, p == nullptr, (int)hipGetLastError());
+    (void)hipFree(g_live.begin()->first);
+
+    // a device's blocks are aged by its own releases only
+    g_budget = 100000 * MB;
+    g_device = 1;
+    block_alloc(1, 40 * MB, &b);
+    block_release(1, &b);
+    g_device = 0;
+    for (int i = 0; i < 200; i++) {
+        block_alloc(0, 10 * MB, &c);
+        block_release(0, &c);
+    }
+    g_device = 1;
+    block_alloc(1, 10 * MB, &c);
+    block_release(1, &c);
+    std::printf("ages %zu %zu\n", g_used[0] / MB, g_used[1] / MB);
+    for (int i = 0; i < 200; i++) {
+        block_alloc(1, 10 * MB, &c);
+        block_release(1, &c);
+    }
+    std::printf("aged %zu %zu\n", g_used[0] / MB, g_used[1] / MB);
     return 0;
 }

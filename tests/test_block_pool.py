@@ -32,6 +32,11 @@ def test_allocations_get_the_idle_blocks(lines):
     assert lines[2] == "refused 2 null 1 last 0"  # and the error does not reach the next call
 
 
+def test_a_device_s_blocks_age_by_its_own_releases(lines):
+    assert lines[3] == "ages 10 50"  # 200 releases on device 0 leave device 1's blocks
+    assert lines[4] == "aged 10 10"  # 64 of its own do not
+
+
 def test_every_device_allocation_is_the_pool_s():
     for path in glob.glob(os.path.join(CSRC, "*")):
         calls = re.findall(r"\bhipMalloc(?:Async)?\(", open(path).read())
