@@ -343,9 +343,14 @@ int32_t bvh_build(const float *verts, int64_t n_verts, const int32_t *tris, int6
                   int32_t layout, const bvh_build_opts *opts, void *stream, bvh_handle_t *out);
 
 /* Releases everything the handle owns (synchronises the device first).  The
- * library keeps up to 512 MiB of released memory per device for later builds.
- * NULL is accepted and ignored. */
+ * library keeps up to 512 MiB of released memory per device for later builds,
+ * until bvh_trim.  NULL is accepted and ignored. */
 int32_t bvh_destroy(bvh_handle_t h);
+
+/* Gives the released memory that the library keeps on the current device back
+ * to it (bvh_build, bvh_batch_create and the work areas of every call do so by
+ * themselves before they fail with ENOMEM). */
+int32_t bvh_trim(void);
 
 /* Sizes and shape of a built BVH.  out: host. */
 int32_t bvh_get_stats(bvh_handle_t h, bvh_stats *out);

@@ -102,6 +102,8 @@ def lib() -> ctypes.CDLL:
         L.bvh_build.restype = _I32
         L.bvh_destroy.argtypes = [_P]
         L.bvh_destroy.restype = _I32
+        L.bvh_trim.argtypes = []
+        L.bvh_trim.restype = _I32
         L.bvh_get_stats.argtypes = [_P, ctypes.POINTER(Stats)]
         L.bvh_get_stats.restype = _I32
         L.bvh_read_buffer.argtypes = [_P, _I32, _P, _I64, ctypes.POINTER(_I64)]
@@ -255,6 +257,12 @@ class BVH:
         _check(lib().bvh_closest_point_counts(self._h, queries.data_ptr(), n, out.data_ptr(),
                                               counts.data_ptr(), _stream(stream)))
         return out, counts
+
+
+def trim():
+    """Gives the released memory that the library keeps for later builds on the
+    current device back to it."""
+    _check(lib().bvh_trim())
 
 
 BUILDERS = {"lbvh": 0, "sah": 1}

@@ -52,6 +52,14 @@ extern "C" int32_t bvh_destroy(bvh_handle_t h) {
     return BVH_OK;
 }
 
+extern "C" int32_t bvh_trim(void) {
+    BVH_TRY(require_device());
+    int dev = 0;
+    BVH_HIP_TRY(hipGetDevice(&dev));
+    block_trim(dev);
+    return BVH_OK;
+}
+
 static int64_t leaf_buffer_bytes(const bvh_handle_s *h) {
     return h->leaf_mode == BVH_LEAF_COMPACT ? h->n_tris * (int64_t)sizeof(bvh_tri)
                                             : h->n_tris * (int64_t)sizeof(int32_t);

@@ -61,6 +61,8 @@ struct DeviceBlock {
 // idle blocks; every device allocation of the library is made by it.
 hipError_t device_malloc(int device, size_t bytes, void **out);
 hipError_t block_alloc(int device, size_t bytes, DeviceBlock *out);
+// Frees the device's idle blocks; the current device is `device`.
+void block_trim(int device);
 void block_release(int device, DeviceBlock *b);
 
 }  // namespace bvhlib

@@ -30,7 +30,7 @@ std::map<std::tuple<int, hipStream_t, int>, Area> g_areas;
 // Bounded: kPoolBlocks blocks and kPoolBytes bytes per device, the longest idle
 // one freed first; a block that kPoolAge of its device's releases have passed by
 // is freed too, and so is every block before the library reports an allocation
-// failure.
+// failure, and on bvh_trim.
 // Safe with any threads and streams: a block enters the pool only once its
 // device is idle (block_release's contract), so whoever takes it next, on any
 // stream, finds no work using it.
@@ -50,7 +50,6 @@ std::map<int, uint64_t> g_releases;      // per device
 
 }  // namespace
 
-// Frees the device's idle blocks; the current device is `device`.
 void block_trim(int device) {
     std::lock_guard<std::mutex> lock(g_pool_mutex);
     for (auto it = g_idle.begin(); it != g_idle.end();) {

@@ -43,7 +43,6 @@ const char *hipGetErrorString(hipError_t) { return "error"; }
 }
 
 namespace bvhlib {
-void block_trim(int device);
 int32_t set_error(int32_t code, const char *, ...) { return code; }
 }  // namespace bvhlib
 
@@ -83,5 +82,7 @@ int main() {
         block_release(1, &c);
     }
     std::printf("aged %zu %zu\n", g_used[0] / MB, g_used[1] / MB);
+    block_trim(0);
+    std::printf("trimmed %zu %zu\n", g_used[0] / MB, g_used[1] / MB);
     return 0;
 }

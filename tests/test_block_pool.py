@@ -37,6 +37,26 @@ def test_a_device_s_blocks_age_by_its_own_releases(lines):
     assert lines[4] == "aged 10 10"  # 64 of its own do not
 
 
+def test_trim_gives_one_device_s_blocks_back(lines):
+    assert lines[5] == "trimmed 0 10"
+
+
+@pytest.mark.gpu
+def test_trim_after_the_last_handle():
+    import torch
+    from paper_2511_15028_amd import bvh, workloads as W
+    v, t = (torch.from_numpy(x).cuda() for x in W.soup_scene(1_000_000, seed=1))
+    h = bvh.build(v, t, "bvh4")  # the work areas have their sizes now
+    held = h.stats()["nodes_buffer_bytes"] + h.stats()["leaf_buffer_bytes"]
+    h.close()
+    bvh.trim()
+    before = torch.cuda.mem_get_info()[0]
+    bvh.build(v, t, "bvh4").close()
+    assert before - torch.cuda.mem_get_info()[0] >= held // 2  # kept for the next build
+    bvh.trim()
+    assert torch.cuda.mem_get_info()[0] == before
+
+
 def test_every_device_allocation_is_the_pool_s():
     for path in glob.glob(os.path.join(CSRC, "*")):
         calls = re.findall(r"\bhipMalloc(?:Async)?\(", open(path).read())
