@@ -559,7 +559,7 @@ int32_t make_graph(bvh_batch_s *b, const bvh_ray *rays, const int64_t *offsets, 
         }
         SpillArea sa;
         sa.ent = static_cast<uint64_t *>(spill);
-        sa.lanes = lanes;
+        sa.per_wave = 64;
         sa.cap = kBatchSpillCap;
         void *args[] = {&d_sc, &d_toff, &nsc, (void *)&total, &ctr, &r, &hh, &deal, &fb, &sa};
         hipKernelNodeParams p{};

@@ -931,8 +931,8 @@ int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_poin
     const bool alone = !Count && wholly_coop(deal, n, waves, h->max_stack);
     const uint64_t need = ((n + deal.claim - 1) / deal.claim + kTraceBlock / 64 - 1) / (kTraceBlock / 64);
     const unsigned grid = (unsigned)std::min<uint64_t>(resident, need);
-    TraceArea ta{Fallback{}, SpillArea{nullptr, grid * kTraceBlock, 0}};
-    if (!alone) BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
+    TraceArea ta{};
+    if (!alone) BVH_TRY(trace_area(s, n, resident, deal.claim, ta));
     kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, qs, n, out, counts, deal,
                                         ta.fb, ta.sa);
     if (alone) return BVH_OK;

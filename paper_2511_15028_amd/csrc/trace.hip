@@ -302,12 +302,12 @@ int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_ray 
     // grid, whose coherent waves end together and leave the last chunks to run by
     // themselves; scattered rays lose less (1 M uniform ones 264 against 210).
     const unsigned grid = (unsigned)(fixed ? need : std::min<uint64_t>(resident, need));
-    TraceArea ta{Fallback{}, SpillArea{nullptr, grid * kTraceBlock, 0}};
+    TraceArea ta{};
     if (fixed && !alone) {
         ta.fb = *fixed;
         clear_header(ta.fb, s);
     } else if (!alone) {
-        BVH_TRY(trace_area(s, n, grid * kTraceBlock, ta));
+        BVH_TRY(trace_area(s, n, resident, deal.claim, ta));
     }
     kernel<<<grid, kTraceBlock, 0, s>>>(h->nodes, h->n_nodes, ld, rays, n, hits, counts, deal,
                                         ta.fb, ta.sa);

@@ -467,8 +467,8 @@ struct GlobalStack {
 // writes or reads one run (a 64-byte line for SL = 16 and 8-byte entries)
 // instead of SL scattered words.
 struct SpillArea {
-    uint64_t *ent;    // [lanes][cap] entries of at most 8 bytes
-    uint32_t lanes;   // lanes of the launch (the grid's threads)
+    uint64_t *ent;    // [waves of the launch][per_wave][cap] entries of at most 8 bytes
+    uint32_t per_wave;  // lanes of a wave that may hold rays, the first ones (64 at most)
     uint32_t cap;     // spill entries per lane
 };
 
@@ -489,9 +489,10 @@ struct RingStack {
     __device__ uint32_t entries() const { return sp / kStep; }
     // all entries lie in the ring, from its first slot on, with room for one more
     __device__ bool in_ring() const { return lo == 0 && sp < SL * kStep; }
-    // the lane's spill run (the lane's index in the grid), as entries of type E
+    // the lane's spill run, as entries of type E
     __device__ E *run() const {
-        return reinterpret_cast<E *>(area.ent + ((size_t)blockIdx.x * kTraceBlock + threadIdx.x) * area.cap);
+        const size_t wave = (size_t)blockIdx.x * (kTraceBlock / 64) + (threadIdx.x >> 6);
+        return reinterpret_cast<E *>(area.ent + (wave * area.per_wave + (threadIdx.x & 63u)) * area.cap);
     }
     __device__ bool room(uint32_t n) {
         while (sp - lo + n * kStep > SL * kStep) {
@@ -1560,15 +1561,25 @@ inline void clear_header(const Fallback &fb, hipStream_t s) {
     k_zero_words<<<1, kTraceBlock, 0, s>>>(fb.count, (uint32_t)(kFallbackHeaderBytes / 4));
 }
 
-inline int32_t trace_area(hipStream_t s, uint64_t n, uint32_t lanes, TraceArea &ta) {
+// Spill runs of a launch that deals n rays, `claim` at a time, on at most
+// `resident` blocks.  Rays spread thin (claim below 64) are dealt in one round, so
+// only the first `claim` lanes of a wave ever hold one: the runs are as many as
+// the rays, not as the lanes of the grid (30,000 rays: 15 MB, not 168).  Never
+// fewer for more rays, so that an area that served a call serves every smaller
+// one, also while its stream is captured.
+constexpr uint64_t spill_runs(uint64_t n, uint64_t resident) {
+    return std::min<uint64_t>(resident * kTraceBlock, (n + kTraceBlock - 1) / kTraceBlock * kTraceBlock + kTraceBlock);
+}
+
+inline int32_t trace_area(hipStream_t s, uint64_t n, uint64_t resident, uint32_t claim, TraceArea &ta) {
     const size_t fb_bytes = (fallback_bytes(n) + 255) & ~(size_t)255;
-    const size_t sp_bytes = (size_t)lanes * kSpillCap * 8;
+    const size_t sp_bytes = (size_t)spill_runs(n, resident) * kSpillCap * 8;
     void *ws = nullptr;
     BVH_TRY(stream_workspace(s, kAreaTrace, fb_bytes + sp_bytes, &ws));
     ta.fb = fallback_view(ws, n);
     char *sp = static_cast<char *>(ws) + fb_bytes;
     ta.sa.ent = reinterpret_cast<uint64_t *>(sp);
-    ta.sa.lanes = lanes;
+    ta.sa.per_wave = std::min(claim, 64u);
     ta.sa.cap = kSpillCap;
     clear_header(ta.fb, s);
     return BVH_OK;

@@ -56,6 +56,26 @@ int main() {
                 }
                 std::printf("%d %d %d %d %d\n", K, sl, max_stack, launches, least);
             }
+    // the spill area of the launches that have one: runs for every lane that can
+    // hold a ray, never fewer for more rays, and few more than rays
+    int short_runs = 0, shrinking = 0;
+    uint64_t before = 0, most = 0;
+    for (uint64_t n = 1; n < 3 * 64 * waves; n += n < 100000 ? 1 : 37) {
+        const uint64_t runs = spill_runs(n, waves / 4);
+        for (uint64_t spread : {waves, waves * 3 / 4})
+            for (uint32_t reserve : {kRayReserve, depth_first_reserve(256)}) {
+                const Deal d = deal_of(n, waves, 16, reserve, spread);
+                const uint64_t blocks = std::min<uint64_t>(waves / 4, ((n + d.claim - 1) / d.claim + 3) / 4);
+                // spread thin: dealt in one round, as the kernels see it
+                if (d.claim < 64 && n > blocks * 4 * d.claim) short_runs++;
+                if (blocks * 4 * std::min(d.claim, 64u) > runs) short_runs++;
+            }
+        shrinking += runs < before;
+        before = runs;
+        most = std::max(most, runs > n ? runs - n : 0);
+    }
+    std::printf("runs %d %d %d\n", short_runs, shrinking, most <= 2 * kTraceBlock);
+
     // the list itself, with a fallback pass and without
     uint32_t count = 0, list[4] = {};
     Fallback fb{};

@@ -28,4 +28,8 @@ def test_groups_without_a_fallback_pass_have_room(lines):
 
 
 def test_no_list_is_written_without_a_fallback_pass(lines):
-    assert lines[81] == "list 1 2 5 9 0"
+    assert lines[82] == "list 1 2 5 9 0"
+
+
+def test_spill_runs_cover_every_ray_and_never_shrink(lines):
+    assert lines[81] == "runs 0 0 1"
