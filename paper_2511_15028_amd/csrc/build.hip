@@ -760,9 +760,9 @@ __global__ __launch_bounds__(kBlock) void k_karras(const KeyT *keys, int n, int3
 // so the line lies where the gain ends.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
-constexpr int kSmallRows = 8;
 constexpr uint32_t kSmallMax = 4096;
-static_assert(kSmallMax <= kSmallThreads * kSmallRows && kSmallMax <= 65536, "positions in 16 bits");
+constexpr int kSmallRows = kSmallMax / kSmallThreads;
+static_assert(kSmallMax == kSmallThreads * kSmallRows && kSmallMax <= 65536, "positions in 16 bits");
 
 __global__ __launch_bounds__(kSmallThreads) void k_small_hierarchy(
     const Box *pbox, uint32_t n, const float *partial, uint32_t nparts, BuildInfo *info, int bits,

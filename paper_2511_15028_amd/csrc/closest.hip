@@ -676,7 +676,6 @@ __global__ __launch_bounds__(kTraceBlock) void k_cpq_persist(const void *nodes, 
     using Wk = typename CpqFor<Layout>::type;
     __shared__ uint64_t s_stack[kCpqStack * kTraceBlock];
     __shared__ WaveLeafLds s_wl[kWavesPerBlock];
-    const uint32_t lane = threadIdx.x & 63u;
     WaveLeafLds *const wl = s_wl + (threadIdx.x >> 6);
     using Finish = FinishQueries<Wk, LeafMode>;
     RingStack<uint64_t, kCpqStack> st(s_stack, sa);
