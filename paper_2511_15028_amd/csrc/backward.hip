@@ -195,15 +195,33 @@ __device__ inline uint32_t block_excl_scan_u32(uint32_t x, uint32_t *wsum, uint3
     return off + inc - x;
 }
 
+// Per-range counters of a block, then its insertion cursors (at most kPartRecs):
+// a word each, or, where the table is large, two to a word, so that three blocks
+// fit a CU whatever the table.
+template <int MAX>
+struct PartTable {
+    static constexpr bool kPacked = MAX > kPartMaxRanges;
+    static constexpr int kWords = kPacked ? MAX / 2 : MAX;
+    static_assert(kPartRecs < 65536, "cursors in 16 bits");
+    uint32_t word[kWords];
+    // counts range p up; its value before
+    __device__ uint32_t add(uint32_t p) {
+        if constexpr (!kPacked) return atomicAdd(&word[p], 1u);
+        const uint32_t sh = (p & 1u) << 4;
+        return (atomicAdd(&word[p >> 1], 1u << sh) >> sh) & 0xFFFFu;
+    }
+};
+
 template <int MAX>
 __global__ __launch_bounds__(kPartThreads) void k_backward_part(
     const float *verts, int64_t n_verts, const int32_t *tris, int64_t n_tris, const bvh_ray *rays,
     uint64_t n, const bvh_hit *hits, const float *grad_hits, float *grad_rays, int shift,
     uint32_t n_ranges, VertRec *seg, uint32_t *offs) {
-    __shared__ uint32_t cnt[MAX];
+    using Table = PartTable<MAX>;
+    __shared__ Table cnt;
     __shared__ uint32_t wsum[kPartThreads / 64];
     __shared__ VertRec sorted[kPartRecs];
-    for (uint32_t p = threadIdx.x; p < n_ranges; p += kPartThreads) cnt[p] = 0;
+    for (uint32_t p = threadIdx.x; p < Table::kWords; p += kPartThreads) cnt.word[p] = 0;
     __syncthreads();
     int32_t rv[kPartRecs / kPartThreads];
     float rg[kPartRecs / kPartThreads][3];
@@ -225,19 +243,25 @@ __global__ __launch_bounds__(kPartThreads) void k_backward_part(
             rg[3 * k + c][0] = w[c] * lam[0];
             rg[3 * k + c][1] = w[c] * lam[1];
             rg[3 * k + c][2] = w[c] * lam[2];
-            if (ok) atomicAdd(&cnt[(uint32_t)idx[c] >> shift], 1u);
+            if (ok) cnt.add((uint32_t)idx[c] >> shift);
         }
     }
     __syncthreads();
     // exclusive offsets of the ranges; each thread scans a run of them
-    constexpr int kRun = MAX / kPartThreads;
+    constexpr int kRun = MAX / kPartThreads, kRunWords = Table::kWords / kPartThreads;
     uint32_t c[kRun], sum = 0;
 #pragma unroll
-    for (int k = 0; k < kRun; k++) {
-        const uint32_t p = threadIdx.x * kRun + k;
-        c[k] = p < n_ranges ? cnt[p] : 0u;
-        sum += c[k];
+    for (int k = 0; k < kRunWords; k++) {  // counters beyond n_ranges are zero
+        const uint32_t x = cnt.word[threadIdx.x * kRunWords + k];
+        if constexpr (Table::kPacked) {
+            c[2 * k] = x & 0xFFFFu;
+            c[2 * k + 1] = x >> 16;
+        } else {
+            c[k] = x;
+        }
     }
+#pragma unroll
+    for (int k = 0; k < kRun; k++) sum += c[k];
     uint32_t total;
     uint32_t run = block_excl_scan_u32<kPartThreads>(sum, wsum, &total);
     // offsets range-major: offs[q * n_blocks + block], q = n_ranges holding
@@ -247,10 +271,10 @@ __global__ __launch_bounds__(kPartThreads) void k_backward_part(
 #pragma unroll
     for (int k = 0; k < kRun; k++) {
         const uint32_t p = threadIdx.x * kRun + k;
-        if (p < n_ranges) {
-            offs[(size_t)p * nbl + blockIdx.x] = run;
-            cnt[p] = run;  // becomes the range's insertion cursor
-        }
+        if (p < n_ranges) offs[(size_t)p * nbl + blockIdx.x] = run;
+        // the counter becomes the range's insertion cursor
+        if constexpr (!Table::kPacked) cnt.word[p] = run;
+        else if (k & 1) cnt.word[p >> 1] = (run - c[k - 1]) | run << 16;
         run += c[k];
     }
     if (threadIdx.x == 0) offs[(size_t)n_ranges * nbl + blockIdx.x] = total;
@@ -258,7 +282,7 @@ __global__ __launch_bounds__(kPartThreads) void k_backward_part(
 #pragma unroll
     for (int r = 0; r < kPartRecs / kPartThreads; r++) {
         if (rv[r] >= 0) {
-            const uint32_t pos = atomicAdd(&cnt[(uint32_t)rv[r] >> shift], 1u);
+            const uint32_t pos = cnt.add((uint32_t)rv[r] >> shift);
             sorted[pos] = VertRec{rv[r], {rg[r][0], rg[r][1], rg[r][2]}};
         }
     }
@@ -480,11 +504,14 @@ inline int part_shift(int64_t n_verts, int64_t max_ranges) {
 
 // Launch plan for n rays on n_verts vertices.  Above 2^19 vertices, twice as
 // many, smaller ranges when each still gets kDenseRecs records if every ray
-// hits (the parting kernel pays for the larger table with a third of its
-// resident blocks): 700,000 vertices and 1 M rays 138 -> 88 us, but 100,000
-// rays 34 -> 40.  Ranges of 2^9 vertices have private accumulators under the
-// same condition (490,000 vertices, 500,000 rays: 65 -> 50 us; 1 M vertices,
-// 20,000 rays 29 -> 45), those of 2^8 always.
+// hits: 700,000 vertices and 1 M camera rays 133 -> 85 us, 894,000 vertices of
+// spheres 292 -> 120, but 100,000 rays 34 -> 40.  Ranges of 2^9 vertices have
+// private accumulators under the same condition (490,000 vertices, 500,000 rays:
+// 65 -> 50 us; 1 M vertices, 20,000 rays 29 -> 45), those of 2^8 always.  What
+// it costs: rays that hit a regular mesh evenly and seldom never wait for one
+// vertex, and pay for the ranges (uniform rays on a terrain of 1 M vertices, a
+// third of them hits: 1 M 74 -> 86 us, 2 M 147 -> 171; camera rays 108 -> 89 and
+// 222 -> 180); the hits are not known before the launch.
 constexpr uint64_t kDenseRecs = 1024;
 struct BackwardPlan {
     int shift;
