@@ -120,7 +120,9 @@ def parse():
 
 def algorithmic_bytes(counts, layout_bytes, leaf_mode):
     """Per-ray bytes the method must move: ray + hit + node records fetched +
-    triangles tested (from the counting kernel)."""
+    triangles tested, as the counting kernel counts them: each ray in a lane of
+    its own.  (The timed kernels visit some nodes more where lanes share a
+    wave's last rays; those are not algorithmic work.)"""
     nodes = counts[:, 0].astype(np.float64)
     tris = counts[:, 1].astype(np.float64)
     return RAY_BYTES + HIT_BYTES + nodes * layout_bytes + tris * LEAF_TRI_BYTES[leaf_mode]

@@ -390,12 +390,14 @@ int32_t bvh_trace(bvh_handle_t h, const bvh_ray *rays, int64_t n, bvh_hit *hits,
  * same hits as bvh_trace, and no call here allocates or frees memory.  The
  * work area (fallback-pass header, list and deep stacks) is a fixed array of
  * 16 MiB + 2,304 B in device memory, one per GPU, held from the library's
- * first use of that GPU until the process ends; each call clears its header
- * with a small kernel before tracing.  Every call on one GPU uses that GPU's
+ * first use of that GPU until the process ends; a call that uses it clears its
+ * header with a small kernel before tracing.  Calls on one GPU share that GPU's
  * array, so calls that overlap in time on one GPU (different streams or host
- * threads) race and give undefined results: serialise them.  Rays run one
- * per lane with the handle's LDS stack; rays that outgrow it are re-traced
- * with a deep stack, as in bvh_trace.
+ * threads) race and give undefined results: serialise them.  Rays run on the
+ * handle's LDS stacks alone, one per lane, and a wave's last rays (all rays of a
+ * small call, which needs no work area) in groups of lanes that share their
+ * stacks; rays that outgrow them are re-traced with a deep stack, as in
+ * bvh_trace.
  *   rays  device, n records;  hits  device, n records (written)
  * Errors: as bvh_trace, plus EINVAL for n > BVH_NOALLOC_MAX_RAYS and
  * EUNSUPPORTED for the SHARED_SLAB layout (its carried-box stacks do not fit
@@ -408,6 +410,9 @@ int32_t bvh_trace_noalloc(bvh_handle_t h, const bvh_ray *rays, int64_t n, bvh_hi
 /*
  * bvh_trace plus per-ray work counters, for measurement: counts[2i] = node
  * records fetched, counts[2i+1] = triangles tested.  Same hits as bvh_trace.
+ * Every ray is counted in a lane of its own: the groups of lanes in which
+ * bvh_trace finishes a wave's last rays visit nodes ahead of the best hit, and
+ * so some more than are counted here.
  *   counts  device, 2n uint32 (written)
  */
 int32_t bvh_trace_counts(bvh_handle_t h, const bvh_ray *rays, int64_t n, bvh_hit *hits,
@@ -433,10 +438,14 @@ int32_t bvh_trace_counts(bvh_handle_t h, const bvh_ray *rays, int64_t n, bvh_hit
  *   grad_hits   device, n x 3 float (dL/dt, dL/du, dL/dv)
  *   grad_verts  device, n_verts x 3 float, ACCUMULATED (+=).  Meshes of up to
  *               2^22 vertices: the contributions are grouped by vertex range
- *               in a work area (16 B per ray contribution; grow-only, kept
- *               per stream) and each range is summed in one workgroup's
- *               LDS (up to 2^18 vertices: one accumulator per wave, no
- *               atomics; beyond: LDS float atomics); larger meshes add
+ *               in a work area (16 B per ray contribution, the ranges' offsets
+ *               and at most 3 MiB of partial sums; grow-only, kept per stream)
+ *               and each range is summed in one workgroup's LDS, or in
+ *               several workgroups' whose sums are then added, while there
+ *               are few ranges.  Ranges of 2^8 vertices (up to 2^18 vertices)
+ *               have one accumulator per wave and no atomics, those of 2^9
+ *               too where the rays are many; wider ones use LDS float
+ *               atomics.  Larger meshes add
  *               per-block partial sums with device float atomics.  Either
  *               way the summation order (last bits) varies between runs.
  *               Calls that share a stream share its work area: they are
@@ -495,7 +504,8 @@ int32_t bvh_closest_point(bvh_handle_t h, const bvh_point_query *queries, int64_
 /*
  * bvh_closest_point plus per-query work counters, for measurement:
  * counts[2i] = node records fetched, counts[2i+1] = triangles measured.
- * Same results as bvh_closest_point.
+ * Same results as bvh_closest_point.  Every query is counted in a lane of its
+ * own, as by bvh_trace_counts.
  *   counts  device, 2n uint32 (written)
  */
 int32_t bvh_closest_point_counts(bvh_handle_t h, const bvh_point_query *queries, int64_t n,

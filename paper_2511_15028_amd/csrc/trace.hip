@@ -26,8 +26,14 @@ namespace {
 constexpr uint32_t kRefillLanes = 16;  // idle lanes of a wave that trigger a refill
 // A coherent wave of a short launch waits for half its lanes, of a long one for
 // all of them: its rays stay neighbours longer, which shows once the end of the
-// launch counts less.  Terrain camera rays in BVH4, half / all: 1 M 205 / 216
-// us, 1.5 M 274 / 276, 2.1 M 347 / 312 (AABB2 747 / 660).
+// launch counts less.  Camera rays, half / all, us:
+//                          0.6 M        1 M          2 M          3 M
+//   2.1 M terrain, BVH4    167 / 169    207 / 219    335 / 335    476 / 458
+//   2.1 M terrain, AABB2   316 / 306    435 / 422    733 / 673  1,012 / 941
+//   540 K spheres, BVH4  1,633 / 1,791  2,012 / 2,241  3,536 / 3,447  4,243 / 4,537
+//   20 K soup, AABB2       409 / 478    541 / 596    932 / 1,089  1,074 / 1,119
+// so the line lies between 1.5 M and 2 M: the scenes that gain from waiting gain
+// above it, the others lose up to 17 % above it and would lose as much below.
 constexpr uint32_t kCoherentRefillLanes = 32;
 constexpr uint64_t kLongRounds = 4;  // dealt rounds of a short launch at most
 
@@ -297,10 +303,13 @@ int32_t launch_layout(const bvh_handle_s *h, const SceneData &ld, const bvh_ray 
     const uint64_t need = ((n + deal.claim - 1) / deal.claim + kTraceBlock / 64 - 1) / (kTraceBlock / 64);
     // Without a spill area (fixed) nothing ties a launch to the resident blocks:
     // every wave gets one chunk, and the dispatcher starts a block whenever
-    // another ends.  On 382,000 terrain triangles in BVH8-Q8 that takes 90 us for
-    // 286,757 camera rays and 180 for 1 M, against 126 and 210 in a persistent
-    // grid, whose coherent waves end together and leave the last chunks to run by
-    // themselves; scattered rays lose less (1 M uniform ones 264 against 210).
+    // another ends.  Coherent waves of a persistent grid end together and leave the
+    // last chunks to run by themselves: 300,007 / 1 M / 2 M camera rays on 382,000
+    // terrain triangles, BVH8-Q8 85 / 177 / 316 us against 120 / 197 / 330, AABB2 141 /
+    // 297 / 527 against 188 / 357 / 561.  Scattered waves run on with fewer lanes
+    // instead of taking more rays, so large launches of them pay: uniform rays,
+    // BVH8-Q8 112 / 251 / 483 against 137 / 205 / 337, AABB2 234 / 506 / 939 against
+    // 221 / 307 / 463 (one ray per lane without rounds: 318 / 652 / 1,207).
     const unsigned grid = (unsigned)(fixed ? need : std::min<uint64_t>(resident, need));
     TraceArea ta{};
     if (fixed && !alone) {
